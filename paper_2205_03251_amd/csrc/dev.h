@@ -165,6 +165,24 @@ hipError_t launch_init(int32_t* pending, const int32_t* init, int64_t n, unsigne
 hipError_t launch_eval(int variant, const EvalParams& p, int grid, hipStream_t s);
 hipError_t launch_fitness(int vtype, const FitParams& p, int64_t n, hipStream_t s);
 hipError_t launch_walk(int vtype, const WalkParams& p, int64_t n_children, hipStream_t s);
+// Result arrays packed for the caller: part q copies rows of row_units units
+// (of 4, 8 or 16 bytes; src rows src_units apart, dst rows dense).  dst is
+// device memory or mapped host memory.
+constexpr int kPackParts = 4;
+struct PackPart {
+    const void* src;
+    void* dst;
+    int64_t rows, row_units, src_units;
+    int32_t unit;                // bytes per unit
+    int32_t first_block;         // set by the launcher
+};
+struct PackParams {
+    PackPart part[kPackParts];
+    int32_t n_parts;
+};
+// Fills part q of p; pointers and sizes must be multiples of 4 bytes.
+void pack_part(PackParams& p, const void* src, void* dst, int64_t rows, int64_t row_bytes, int64_t src_row_bytes);
+hipError_t launch_pack(PackParams& p, hipStream_t s);
 hipError_t launch_splice(const SpliceItem* items, int64_t n_items, uint8_t* out, hipStream_t s);
 
 // Device-side tree index (index.hip).  E(k), the sum of node steps before

@@ -1322,6 +1322,76 @@ hipError_t launch_splice(const SpliceItem* items, int64_t n_items, uint8_t* out,
     return hipGetLastError();
 }
 
+// ------------------------------------------------------- results out
+// Rows of the padded result vectors, and the scores beside them, copied into
+// the caller's dense arrays (device memory, or pinned host memory that the
+// host then reads) by one launch.  Bound by the launch itself for the usual
+// sizes, else by memory.  It replaces hipMemcpy2DAsync and a copy per array:
+// to pageable host memory that copies row by row, about 7 us each.  Whole
+// calls with host results: 1000 rows of 8 bytes 7.29 -> 0.45 ms, 100 rows of
+// 192 bytes 0.81 -> 0.054 ms.
+template <class U>
+__device__ __forceinline__ void pack_rows(const PackPart& q, int64_t first)
+{
+    const int64_t total = q.rows * q.row_units;
+    const U* src = (const U*)q.src;
+    U* dst = (U*)q.dst;
+    UNROLL for (int k = 0; k < 4; ++k) {
+        const int64_t i = first + 256 * k;
+        if (i >= total) return;
+        int64_t from = i;
+        if (q.src_units != q.row_units) {
+            const int64_t r = total <= 0xffffffffLL ? (int64_t)((uint32_t)i / (uint32_t)q.row_units) : i / q.row_units;
+            from = r * q.src_units + (i - r * q.row_units);
+        }
+        dst[i] = src[from];
+    }
+}
+
+__global__ __launch_bounds__(256) void k_pack(PackParams p)
+{
+    int n = 0;
+    while (n + 1 < p.n_parts && (int)blockIdx.x >= p.part[n + 1].first_block) ++n;
+    const PackPart q = p.part[n];
+    const int64_t first = (int64_t)(blockIdx.x - q.first_block) * 1024 + threadIdx.x;
+    if (q.unit == 16) pack_rows<uint4>(q, first);
+    else if (q.unit == 8) pack_rows<uint2>(q, first);
+    else pack_rows<uint32_t>(q, first);
+}
+
+void pack_part(PackParams& p, const void* src, void* dst, int64_t rows, int64_t row_bytes, int64_t src_row_bytes)
+{
+    PackPart& q = p.part[p.n_parts++];
+    const bool dense = rows <= 1 || row_bytes == src_row_bytes;
+    if (dense) {
+        row_bytes *= rows;
+        src_row_bytes = row_bytes;
+        rows = 1;
+    }
+    // the widest unit that every row's start and length allow
+    const uint64_t bits = (uint64_t)(uintptr_t)src | (uint64_t)(uintptr_t)dst | (uint64_t)row_bytes | (uint64_t)src_row_bytes;
+    q.unit = (bits & 15) == 0 ? 16 : (bits & 7) == 0 ? 8 : 4;
+    q.src = src;
+    q.dst = dst;
+    q.rows = rows;
+    q.row_units = row_bytes / q.unit;
+    q.src_units = src_row_bytes / q.unit;
+    q.first_block = 0;
+}
+
+hipError_t launch_pack(PackParams& p, hipStream_t s)
+{
+    int64_t blocks = 0;
+    for (int n = 0; n < p.n_parts; ++n) {
+        p.part[n].first_block = (int32_t)blocks;
+        blocks += (p.part[n].rows * p.part[n].row_units + 1023) / 1024;
+        if (blocks > 0x7fffffff) return hipErrorInvalidValue;
+    }
+    if (blocks == 0) return hipSuccess;
+    hipLaunchKernelGGL(k_pack, dim3((unsigned)blocks), dim3(256), 0, s, p);
+    return hipGetLastError();
+}
+
 hipError_t launch_walk(int vtype, const WalkParams& p, int64_t n_children, hipStream_t s)
 {
     if (n_children <= 0) return hipSuccess;

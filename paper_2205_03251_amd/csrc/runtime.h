@@ -225,7 +225,11 @@ struct Ctx {
     hipEvent_t kev0 = nullptr, kev1 = nullptr;   // around the interpreter launch
     Server* server = nullptr;
     int32_t* ix_scratch = nullptr;          // this device's copy of the index scratch array
+    // pinned host memory that results for the host are packed into (used by
+    // the thread that holds mu; allocated on first use, kept to gp_destroy)
+    uint8_t* stage = nullptr;
 };
+constexpr size_t kStageBytes = size_t(4) << 20;
 
 // ------------------------------------------------------------ internals
 int set_err(Ctx* c, int code, const std::string& msg);

@@ -1209,6 +1209,7 @@ void gp_destroy(gp_ctx* ctx)
     (void)hipStreamSynchronize(ctx->stream);
     ctx->pops.clear();
     ctx->cases.clear();
+    if (ctx->stage) (void)hipHostFree(ctx->stage);
     if (ctx->ev0) (void)hipEventDestroy(ctx->ev0);
     if (ctx->ev1) (void)hipEventDestroy(ctx->ev1);
     if (ctx->kev0) (void)hipEventDestroy(ctx->kev0);
@@ -1523,14 +1524,111 @@ static int lookup(gp_ctx* ctx, gp_handle pop, gp_handle cases, Pop** p, CaseSet*
     return GP_OK;
 }
 
-static int copy_out(gp_ctx* ctx, void* dst, const void* src, int64_t rows, int64_t elems, int64_t stride,
-                    size_t esz, uint32_t flags)
-{
-    if (!dst || rows <= 0) return GP_OK;
-    const hipMemcpyKind kind = (flags & GP_DEVICE_PTR) ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost;
-    HIPC(ctx, hipMemcpy2DAsync(dst, elems * esz, src, stride * esz, elems * esz, rows, kind, ctx->stream));
-    return GP_OK;
-}
+// The result arrays of one call on their way to the caller.  add() names an
+// array (rows dense at dst, stride apart at src), enqueue() starts the copies
+// on the context stream, finish() completes those to host memory once the
+// caller has waited for the stream.  Arrays on the device, and those for the
+// host that fit the pinned staging memory together, are packed by one launch
+// (see k_pack); larger ones for the host are one copy when their rows are
+// dense, else they are packed a stage at a time in finish().  A destination on
+// the device is written by the kernel only when the whole array lies inside
+// one device allocation of this GPU; anything else goes to hipMemcpy, which
+// checks it.
+class ResultCopies {
+public:
+    explicit ResultCopies(Ctx* c) : c_(c) {}
+    void add(void* dst, const void* src, int64_t rows, int64_t row_bytes, int64_t src_row_bytes, bool to_host)
+    {
+        if (dst && rows > 0 && row_bytes > 0) a_[n_++] = Arr{dst, src, rows, row_bytes, src_row_bytes, to_host, -1};
+    }
+    int enqueue()
+    {
+        PackParams p{};
+        for (int i = 0; i < n_; ++i) {
+            Arr& a = a_[i];
+            const int64_t bytes = a.rows * a.row_bytes;
+            const bool cpu = a.to_host && host_writes(a.dst);
+            if (cpu && used_ + bytes <= (int64_t)kStageBytes && stage()) {
+                a.at = used_;
+                used_ += (bytes + 15) & ~int64_t(15);
+                pack_part(p, a.src, c_->stage + a.at, a.rows, a.row_bytes, a.src_row_bytes);
+            } else if (!a.to_host && on_device(a.dst, bytes)) {
+                pack_part(p, a.src, a.dst, a.rows, a.row_bytes, a.src_row_bytes);
+            } else if (cpu && a.row_bytes != a.src_row_bytes && stage()) {
+                a.at = -2;                     // packed in finish()
+            } else {
+                HIPC(c_, hipMemcpy2DAsync(a.dst, a.row_bytes, a.src, a.src_row_bytes, a.row_bytes, a.rows,
+                                          a.to_host ? hipMemcpyDeviceToHost : hipMemcpyDeviceToDevice, c_->stream));
+            }
+        }
+        HIPC(c_, launch_pack(p, c_->stream));
+        return GP_OK;
+    }
+    int finish()
+    {
+        for (int i = 0; i < n_; ++i)
+            if (a_[i].at >= 0) std::memcpy(a_[i].dst, c_->stage + a_[i].at, (size_t)(a_[i].rows * a_[i].row_bytes));
+        for (int i = 0; i < n_; ++i) {
+            const Arr& a = a_[i];
+            if (a.at != -2) continue;
+            const int64_t step = std::max<int64_t>(1, (int64_t)kStageBytes / a.row_bytes);
+            for (int64_t r = 0; r < a.rows; r += step) {
+                const int64_t k = std::min(step, a.rows - r);
+                PackParams p{};
+                pack_part(p, (const uint8_t*)a.src + r * a.src_row_bytes, c_->stage, k, a.row_bytes, a.src_row_bytes);
+                HIPC(c_, launch_pack(p, c_->stream));
+                HIPC(c_, hipStreamSynchronize(c_->stream));
+                std::memcpy((uint8_t*)a.dst + r * a.row_bytes, c_->stage, (size_t)(k * a.row_bytes));
+            }
+        }
+        return GP_OK;
+    }
+
+private:
+    struct Arr {
+        void* dst;
+        const void* src;
+        int64_t rows, row_bytes, src_row_bytes;
+        bool to_host;
+        int64_t at;                            // offset in the stage; -1 copied already, -2 packed in finish()
+    };
+    bool stage()
+    {
+        if (!c_->stage && hipHostMalloc((void**)&c_->stage, kStageBytes, hipHostMallocDefault) != hipSuccess) {
+            (void)hipGetLastError();
+            c_->stage = nullptr;
+        }
+        return c_->stage != nullptr;
+    }
+    // whether a result for the host may be written by this thread: not when dst is device memory
+    bool host_writes(const void* dst) const
+    {
+        hipPointerAttribute_t at{};
+        if (hipPointerGetAttributes(&at, dst) != hipSuccess) {
+            (void)hipGetLastError();
+            return true;
+        }
+        return at.type != hipMemoryTypeDevice;
+    }
+    bool on_device(const void* dst, int64_t bytes) const
+    {
+        if (((uintptr_t)dst & 3) != 0) return false;
+        hipPointerAttribute_t at{};
+        hipDeviceptr_t base = nullptr;
+        size_t size = 0;
+        if (hipPointerGetAttributes(&at, dst) != hipSuccess || at.type != hipMemoryTypeDevice ||
+            at.device != c_->device || hipMemGetAddressRange(&base, &size, (hipDeviceptr_t)dst) != hipSuccess) {
+            (void)hipGetLastError();
+            return false;
+        }
+        const uintptr_t d = (uintptr_t)dst, b = (uintptr_t)base;
+        return d >= b && d - b <= size && size - (d - b) >= (size_t)bytes;
+    }
+    Ctx* c_;
+    Arr a_[kPackParts];
+    int n_ = 0;
+    int64_t used_ = 0;
+};
 
 int gp_evaluate_full(gp_ctx* ctx, gp_handle pop, gp_handle cases, uint32_t flags, void* root_out,
                      void* fitness_out, gp_stats* st)
@@ -1553,14 +1651,15 @@ int gp_evaluate_full(gp_ctx* ctx, gp_handle pop, gp_handle cases, uint32_t flags
     RC(enqueue_full(ctx, p, cases, cs, L, per_tree, graph, ctx->stream, &launches, !graph));
     HIPC(ctx, hipEventRecord(ctx->ev1, ctx->stream));
     const size_t esz = p->vtype == GP_BOOL ? 8 : 4;
-    RC(copy_out(ctx, root_out, p->vecs.p, p->n_trees, cs->n_elems, cs->stride, esz, flags));
-    if (fitness_out) {
-        const hipMemcpyKind kind = (flags & GP_DEVICE_PTR) ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost;
-        HIPC(ctx, hipMemcpyAsync(fitness_out, p->fit.p, (size_t)p->n_trees * 8, kind, ctx->stream));
-    }
+    ResultCopies rc(ctx);
+    const bool host = !(flags & GP_DEVICE_PTR);
+    rc.add(root_out, p->vecs.p, p->n_trees, cs->n_elems * esz, cs->stride * esz, host);
+    rc.add(fitness_out, p->fit.p, 1, p->n_trees * 8, p->n_trees * 8, host);
+    RC(rc.enqueue());
     float ms = 0.f, kms = 0.f;
     if (!(flags & GP_ASYNC)) {
         HIPC(ctx, hipStreamSynchronize(ctx->stream));
+        RC(rc.finish());
         HIPC(ctx, hipEventElapsedTime(&ms, ctx->ev0, ctx->ev1));
         if (!graph) HIPC(ctx, hipEventElapsedTime(&kms, ctx->kev0, ctx->kev1));
     }
@@ -1589,17 +1688,17 @@ int gp_fitness(gp_ctx* ctx, gp_handle cases, const void* outputs, int64_t n, uin
     if (n == 0) return GP_OK;
     const size_t esz = cs->vtype == GP_BOOL ? 8 : 4;
     DevBuf vecs, fit;
-    RC(dev_alloc(ctx, vecs, (size_t)n * cs->stride * esz));
+    RC(dev_alloc(ctx, vecs, (size_t)n * cs->n_elems * esz));
     RC(dev_alloc(ctx, fit, (size_t)n * 8));
     const hipMemcpyKind kin = (flags & GP_DEVICE_PTR) ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice;
-    HIPC(ctx, hipMemcpy2DAsync(vecs.p, cs->stride * esz, outputs, cs->n_elems * esz, cs->n_elems * esz, n, kin,
-                               ctx->stream));
+    // one dense copy: the kernels take any row stride (a pitched copy from pageable memory goes row by row)
+    HIPC(ctx, hipMemcpyAsync(vecs.p, outputs, (size_t)n * cs->n_elems * esz, kin, ctx->stream));
     FitParams f;
     f.vecs = vecs.p;
     f.first_slot = 0;
     f.target = cs->target.p;
     f.fit_out = fit.p;
-    f.stride = cs->stride;
+    f.stride = cs->n_elems;
     f.n_valid = cs->T;
     f.P = cs->P;
     HIPC(ctx, launch_fitness(cs->vtype, f, n, ctx->stream));
@@ -1654,16 +1753,17 @@ int gp_evaluate_incremental_batch(gp_ctx* ctx, gp_handle pop, gp_handle cases, i
         RC(enqueue_incremental(ctx, jobs, cases, cs, root_out != nullptr, ctx->stream, &io, &launches));
     HIPC(ctx, hipEventRecord(ctx->ev1, ctx->stream));
     const size_t esz = p->vtype == GP_BOOL ? 8 : 4;
-    RC(copy_out(ctx, root_out, io.root.p, n_children, cs->n_elems, cs->stride, esz, flags));
-    if (fitness_out) {
-        const hipMemcpyKind kind = (flags & GP_DEVICE_PTR) ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost;
-        HIPC(ctx, hipMemcpyAsync(fitness_out, io.fit.p, (size_t)n_children * 8, kind, ctx->stream));
-    }
     std::vector<int32_t> stop(n_children);
     std::vector<int64_t> interp(n_children);
-    HIPC(ctx, hipMemcpyAsync(stop.data(), io.stop.p, (size_t)n_children * 4, hipMemcpyDeviceToHost, ctx->stream));
-    HIPC(ctx, hipMemcpyAsync(interp.data(), io.interp.p, (size_t)n_children * 8, hipMemcpyDeviceToHost, ctx->stream));
+    ResultCopies rc(ctx);
+    const bool host = !(flags & GP_DEVICE_PTR);
+    rc.add(stop.data(), io.stop.p, 1, n_children * 4, n_children * 4, true);
+    rc.add(interp.data(), io.interp.p, 1, n_children * 8, n_children * 8, true);
+    rc.add(fitness_out, io.fit.p, 1, n_children * 8, n_children * 8, host);
+    rc.add(root_out, io.root.p, n_children, cs->n_elems * esz, cs->stride * esz, host);
+    RC(rc.enqueue());
     HIPC(ctx, hipStreamSynchronize(ctx->stream));
+    RC(rc.finish());
     float ms = 0.f;
     HIPC(ctx, hipEventElapsedTime(&ms, ctx->ev0, ctx->ev1));
     int64_t interp_total = 0;
@@ -1820,13 +1920,13 @@ int gp_population_results(gp_ctx* ctx, gp_handle pop, gp_handle cases, uint32_t 
     if (p->evaluated_with != cases || !p->vecs.p)
         return set_err(ctx, GP_ENOTFOUND, "the population's last full evaluation was not on this case set");
     const size_t esz = p->vtype == GP_BOOL ? 8 : 4;
-    RC(copy_out(ctx, root_out, p->vecs.p, p->n_trees, cs->n_elems, cs->stride, esz, flags));
-    if (fitness_out) {
-        const hipMemcpyKind kind = (flags & GP_DEVICE_PTR) ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost;
-        HIPC(ctx, hipMemcpyAsync(fitness_out, p->fit.p, (size_t)p->n_trees * 8, kind, ctx->stream));
-    }
+    ResultCopies rc(ctx);
+    const bool host = !(flags & GP_DEVICE_PTR);
+    rc.add(root_out, p->vecs.p, p->n_trees, cs->n_elems * esz, cs->stride * esz, host);
+    rc.add(fitness_out, p->fit.p, 1, p->n_trees * 8, p->n_trees * 8, host);
+    RC(rc.enqueue());
     HIPC(ctx, hipStreamSynchronize(ctx->stream));
-    return GP_OK;
+    return rc.finish();
 }
 
 int gp_evolve(gp_ctx* ctx, gp_handle pop, gp_handle cases, const gp_evolve_cfg* cfg, gp_gen_stats* stats,

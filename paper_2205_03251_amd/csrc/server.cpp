@@ -329,10 +329,10 @@ int launch_batch(Server* S, SBatch* b)
         if (L.variant < 0) return GP_EINVAL;
         const int rc = enqueue_full(c, b->pop.get(), ch, cs, L, false, false, s, nullptr);
         if (rc != GP_OK) return rc;
-        if (hipMemcpyAsync(st_fit, b->pop->fit.p, (size_t)n * 8, hipMemcpyDeviceToHost, s) != hipSuccess ||
-            hipMemcpy2DAsync(st_root, vbytes, b->pop->vecs.p, (size_t)cs->stride * esz, vbytes, n,
-                             hipMemcpyDeviceToHost, s) != hipSuccess)
-            return GP_EDEVICE;
+        PackParams pk{};
+        pack_part(pk, b->pop->fit.p, st_fit, 1, n * 8, n * 8);
+        pack_part(pk, b->pop->vecs.p, st_root, n, (int64_t)vbytes, (int64_t)(cs->stride * esz));
+        if (launch_pack(pk, s) != hipSuccess) return GP_EDEVICE;
     } else {
         std::vector<IncJob> ij(n);
         for (int64_t i = 0; i < n; ++i) {
@@ -343,12 +343,12 @@ int launch_batch(Server* S, SBatch* b)
         b->inc = std::make_unique<IncOut>();
         int rc = enqueue_incremental(c, ij, ch, cs, true, s, b->inc.get(), nullptr);
         if (rc != GP_OK) return rc;
-        if (hipMemcpyAsync(st_fit, b->inc->fit.p, (size_t)n * 8, hipMemcpyDeviceToHost, s) != hipSuccess ||
-            hipMemcpyAsync(st_stop, b->inc->stop.p, (size_t)n * 4, hipMemcpyDeviceToHost, s) != hipSuccess ||
-            hipMemcpyAsync(st_int, b->inc->interp.p, (size_t)n * 8, hipMemcpyDeviceToHost, s) != hipSuccess ||
-            hipMemcpy2DAsync(st_root, vbytes, b->inc->root.p, (size_t)cs->stride * esz, vbytes, n,
-                             hipMemcpyDeviceToHost, s) != hipSuccess)
-            return GP_EDEVICE;
+        PackParams pk{};
+        pack_part(pk, b->inc->fit.p, st_fit, 1, n * 8, n * 8);
+        pack_part(pk, b->inc->stop.p, st_stop, 1, n * 4, n * 4);
+        pack_part(pk, b->inc->interp.p, st_int, 1, n * 8, n * 8);
+        pack_part(pk, b->inc->root.p, st_root, n, (int64_t)vbytes, (int64_t)(cs->stride * esz));
+        if (launch_pack(pk, s) != hipSuccess) return GP_EDEVICE;
     }
     if (hipEventRecord(b->done_ev, s) != hipSuccess) return GP_EDEVICE;
     return GP_OK;
