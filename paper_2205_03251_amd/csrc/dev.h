@@ -136,6 +136,7 @@ struct Variant {
     int table;                   // runs the generated table-dispatch loop
     int max_inputs;              // input rows held in registers (0: any count, staged in LDS)
     int max_elems;               // > 0: at most this many case words (Boolean) or cases (float)
+    int rows;                    // float: input rows past the first held in registers (others are read from memory)
 };
 
 // Whether variant v can run a population of value type vtype whose programs

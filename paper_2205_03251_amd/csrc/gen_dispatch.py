@@ -1,10 +1,10 @@
 """Generate the gfx950 dispatch loop of the float32 interpreter.
 
-Writes dispatch_f32.inc: for each (K, S) in VARIANTS two device functions,
-run_f32_dispatch_K_S() (branch-table dispatch) and run_f32d_dispatch_K_S()
-(direct dispatch into handler slots), each holding one inline-asm block that
-runs one chunk's program and stores the chunk's value; and dispatch_bool.inc,
-the Boolean loops.
+Writes dispatch_f32.inc: device functions run_f32_dispatch_K_S()
+(branch-table dispatch), run_f32d_dispatch_K_S() (direct dispatch into handler
+slots) and run_f32r_dispatch_K_S() (direct, with further input rows held in
+registers), each holding one inline-asm block that runs one chunk's program
+and stores the chunk's value; and dispatch_bool.inc, the Boolean loops.
 
 Why assembly: the interpreter spends most of its scalar instructions on
 choosing the handler.  The compiler lowers a switch to a tree of compares
@@ -90,7 +90,22 @@ from __future__ import annotations
 import os
 import sys
 
-VARIANTS = [(4, 10), (8, 10)]
+VARIANTS = [(4, 10, "t"), (4, 10, "d"), (8, 10, "t"), (8, 10, "d"),
+            # at most 64 and 128 cases: one and two cases per lane
+            (1, 10, "d"), (2, 10, "d"),
+            # several inputs (see ROWS)
+            (1, 10, "r"), (2, 10, "r"), (4, 10, "r"), (8, 10, "r")]
+# Only input 0 is folded into instructions; every other terminal is a PUSH.
+# Read from memory, each PUSH is a load and a wait in the middle of the
+# chunk's chain of words.  The "r" loops load input rows 1 .. ROWS[K] into
+# VGPRs when the chunk starts, as they load x, and PUSH moves a row to the stack
+# in GPR index mode.  300 trees of 10^3..10^5 nodes in 1024-node chunks: three
+# inputs and 1500 cases 2.81 -> 1.96 ms (K = 4), five inputs and 100 cases
+# 4.86 ms (compiled switch) -> 1.74 ms (K = 2); one input and 50 cases, which
+# had only the compiled switch, 2.27 -> 0.85 ms (K = 1, direct).  As many rows as leave four (K = 4) and three (K = 8) waves
+# per SIMD; K = 1 and 2 have room for 15.  A PUSH beyond them still reads
+# memory (rows that co-evaluation appends to the case set).
+ROWS = {1: 15, 2: 15, 4: 7, 8: 3}
 # A chunk's output vector is the one value that waves hand to each other
 # inside a launch (the wave that finishes a chunk's last input reads it with
 # LOAD).  It is written and read with agent-scope coherence (sc1, the form of
@@ -107,15 +122,17 @@ TINY = 0x358637BD                     # 1e-6f
 P2 = lambda e: (127 + e) << 23        # bit pattern of 2^e (normal range)
 
 
-def gen_one(K: int, S: int, direct: bool = False, SLOT: int = 128) -> str:
-    """direct=False: the key indexes a table of branches to the handlers (two
-    jumps per word).  direct=True: the key's slot of SLOT bytes at table +
-    key * SLOT holds the handler itself for +, - and x (and the copy of x/x),
-    so those words take one jump; divides, PUSH, LOAD and STORE stay out of
-    line, one branch from their slot."""
-    assert K % 2 == 0, "the range checks pair up slots"
-    V_X = V_ST + S * K
-    V_Q = V_X + K
+def gen_one(K: int, S: int, form: str, SLOT: int = 128) -> str:
+    """form "t": the key indexes a table of branches to the handlers (two
+    jumps per word).  "d": the key's slot of SLOT bytes at table + key * SLOT
+    holds the handler itself for +, - and x (and the copy of x/x), so those
+    words take one jump; divides, PUSH, LOAD and STORE stay out of line, one
+    branch from their slot.  "r": as "d", with input rows 1 .. ROWS[K] held
+    in registers behind x; PUSH of one of them stays in its slot too."""
+    direct = form != "t"
+    rows = ROWS[K] if form == "r" else 0
+    V_X = V_ST + S * K                # rows 0 (x), 1, .. rows of K registers each
+    V_Q = V_X + (rows + 1) * K
     V_Y = V_Q + K
     V_T = V_Y + K
     V_CP = V_T + 5                    # destination of the code-line touches, read by nothing
@@ -177,6 +194,9 @@ def gen_one(K: int, S: int, direct: bool = False, SLOT: int = 128) -> str:
     def reduce_abs(kind, dst, vals):
         """dst = max or min of |v| over vals (NaN operands are passed over,
         so a NaN lane takes the short divide too, where it also gives NaN)."""
+        if len(vals) < 3:
+            a(f"  v_{kind}_f32_e64 {dst}, |{vals[0]}|, |{vals[-1]}|")
+            return
         a(f"  v_{kind}3_f32 {dst}, |{vals[0]}|, |{vals[1]}|, |{vals[2]}|")
         i = 3
         while i + 1 < len(vals):
@@ -218,11 +238,22 @@ def gen_one(K: int, S: int, direct: bool = False, SLOT: int = 128) -> str:
         for k in range(K):
             short_div(dsts[k], nums[k], dens[k])
 
-    lab = lambda name: f".Lgp{'d' if direct else ''}{K}_{S}_{name}_%="
+    lab = lambda name: f".Lgp{form if direct else ''}{K}_{S}_{name}_%="
     # ---------------------------------------------------------- entry
     a(f"  s_mov_b32 {sr('TINY')}, {TINY:#x}")
     for k in range(K):
         a(f"  global_load_dword {xv(k)}, %[voff], %[inb] offset:{256 * k}")
+    if rows:                # row j at inb + j * strideb, for j < n_inputs
+        a(f"  s_mov_b32 {sr('A0')}, %[inb_lo]")
+        a(f"  s_mov_b32 {sr('A1')}, %[inb_hi]")
+        for j in range(1, rows + 1):
+            a(f"  s_cmp_le_u32 %[nin], {j}")
+            a(f"  s_cbranch_scc1 {lab('inok')}")
+            a(f"  s_add_u32 {sr('A0')}, {sr('A0')}, %[strideb]")
+            a(f"  s_addc_u32 {sr('A1')}, {sr('A1')}, 0")
+            for k in range(K):
+                a(f"  global_load_dword v{V_X + j * K + k}, %[voff], {sp('A0')} offset:{256 * k}")
+        a(f"{lab('inok')}:")
     a(f"  s_getpc_b64 {sp('TB0')}")
     a(f"{lab('pc')}:")
     a(f"  s_add_u32 {sr('TB0')}, {sr('TB0')}, {lab('tbl')}-{lab('pc')}")
@@ -244,6 +275,8 @@ def gen_one(K: int, S: int, direct: bool = False, SLOT: int = 128) -> str:
     # step, with div_scale's identity case): used by the short stack / x
     for k in range(K):
         a(f"  v_rcp_f32_e32 {yv(k)}, {xv(k)}")
+    if K == 1:
+        a("  s_nop 0")                        # a transcendental's result is read one instruction later
     for k in range(K):
         a(f"  v_fma_f32 {T[0]}, -{xv(k)}, {yv(k)}, 1.0")
         a(f"  v_fmac_f32_e32 {yv(k)}, {T[0]}, {yv(k)}")
@@ -255,9 +288,11 @@ def gen_one(K: int, S: int, direct: bool = False, SLOT: int = 128) -> str:
     a("  s_mov_b64 vcc, exec")
     for k in range(0, K, 2):
         a(f"  v_cmp_le_f32_e64 {sp('P0')}, |{xv(k)}|, {sr('T0')}")
-        a(f"  v_cmp_le_f32_e64 {sp('J0')}, |{xv(k + 1)}|, {sr('T0')}")
+        if k + 1 < K:
+            a(f"  v_cmp_le_f32_e64 {sp('J0')}, |{xv(k + 1)}|, {sr('T0')}")
         a(f"  s_and_b64 vcc, vcc, {sp('P0')}")
-        a(f"  s_and_b64 vcc, vcc, {sp('J0')}")
+        if k + 1 < K:
+            a(f"  s_and_b64 vcc, vcc, {sp('J0')}")
     a(f"  s_andn2_b64 {sp('A0')}, exec, vcc")
     a(f"  s_cselect_b32 {sr('FLG')}, 0, 1")
     a(f"  s_mov_b32 {sr('T0')}, {P2(-60):#x}")
@@ -295,7 +330,8 @@ def gen_one(K: int, S: int, direct: bool = False, SLOT: int = 128) -> str:
             name = "end"          # never emitted by the compiler; ends the chunk
         handlers[key] = name
     # ---------------------------------------------------------- handlers
-    def emit(key):
+    def emit(key, memory=False):
+        """memory: the PUSH of a row that is not held in registers."""
         f, mode, d = key & 3, (key >> 2) & 7, key >> 5
         if mode == M_XX and f == 3:
             for k in range(K):
@@ -383,20 +419,34 @@ def gen_one(K: int, S: int, direct: bool = False, SLOT: int = 128) -> str:
         elif mode == M_RS:
             for k in range(K):
                 op(f, st(d, k), st(d + 1, k), st(d, k))
-        elif mode == M_PUSH:
+        elif mode == M_PUSH and rows and not memory:
             a(f"  s_lshr_b32 {sr('T0')}, {sr('INS')}, 10")
-            a(f"  s_cmp_eq_u32 {sr('T0')}, 0")
-            a(f"  s_cbranch_scc1 {lab(f'px{d}')}")
+            a(f"  s_cmp_gt_u32 {sr('T0')}, {rows}")
+            a(f"  s_cbranch_scc1 {lab(f'pm{d}')}")
+            if K > 1:
+                a(f"  s_lshl_b32 {sr('T0')}, {sr('T0')}, {K.bit_length() - 1}")
+            a(f"  s_set_gpr_idx_on {sr('T0')}, gpr_idx(SRC0)")
+            for k in range(K):
+                a(f"  v_mov_b32_e32 {st(d, k)}, {xv(k)}")
+            a("  s_set_gpr_idx_off")
+        elif mode == M_PUSH:
+            if rows:
+                a(f"{lab(f'pm{d}')}:")
+            else:
+                a(f"  s_lshr_b32 {sr('T0')}, {sr('INS')}, 10")
+                a(f"  s_cmp_eq_u32 {sr('T0')}, 0")
+                a(f"  s_cbranch_scc1 {lab(f'px{d}')}")
             a(f"  s_mul_i32 {sr('T0')}, {sr('T0')}, %[strideb]")
             a(f"  s_add_u32 {sr('A0')}, %[inb_lo], {sr('T0')}")
             a(f"  s_addc_u32 {sr('A1')}, %[inb_hi], 0")
             for k in range(K):
                 a(f"  global_load_dword {st(d, k)}, %[voff], {sp('A0')} offset:{256 * k}")
             a("  s_waitcnt vmcnt(0)")
-            tail()
-            a(f"{lab(f'px{d}')}:")
-            for k in range(K):
-                a(f"  v_mov_b32_e32 {st(d, k)}, {xv(k)}")
+            if not rows:
+                tail()
+                a(f"{lab(f'px{d}')}:")
+                for k in range(K):
+                    a(f"  v_mov_b32_e32 {st(d, k)}, {xv(k)}")
         elif mode == M_LOAD:
             a(f"  s_lshr_b32 {sr('T0')}, {sr('INS')}, 10")
             a(f"  s_lshl_b32 {sr('T0')}, {sr('T0')}, 2")
@@ -424,7 +474,8 @@ def gen_one(K: int, S: int, direct: bool = False, SLOT: int = 128) -> str:
         dispatch fit the key's slot.  Divides, PUSH, LOAD and STORE are out of
         line, one branch away."""
         f, mode = key & 3, (key >> 2) & 7
-        return handlers[key] == f"h{key}" and (mode == M_XX or (f != 3 and mode in (M_XS, M_SX, M_SS, M_RS)))
+        return handlers[key] == f"h{key}" and (mode == M_XX or (f != 3 and mode in (M_XS, M_SX, M_SS, M_RS)) or
+                                               (rows > 0 and mode == M_PUSH))
 
     if not direct:
         a(f"{lab('tbl')}:")
@@ -441,6 +492,9 @@ def gen_one(K: int, S: int, direct: bool = False, SLOT: int = 128) -> str:
             assert key * SLOT < 64 * 1024
             a(f"{lab(handlers[key])}:")
             emit(key)
+        elif handlers[key] == f"h{key}" and (key >> 2) & 7 == M_PUSH:
+            assert key * SLOT < 64 * 1024
+            emit(key, memory=True)
     if direct:
         a(f"{lab('endjump')}:")
         a(f"  s_add_u32 {sr('TG0')}, {sr('TB0')}, {1024 * SLOT:#x}")
@@ -474,12 +528,13 @@ def gen_one(K: int, S: int, direct: bool = False, SLOT: int = 128) -> str:
     body = "\n".join('        "' + line.replace('"', '\\"') + '\\n"' for line in L)
     vclob = ", ".join(f'"v{i}"' for i in range(V_ST, n_vgpr))
     sclob = ", ".join(f'"s{s[n]}"' for n in names)
+    nin_arg, nin_op, m0 = (", uint32_t nin", ', [nin] "s"(nin)', '"m0", ') if rows else ("", "", "")
     return f"""
-// K = {K} cases per lane, S = {S} stack slots: v{V_ST}..v{n_vgpr - 1}, s{S_BASE}..s{S_BASE + len(names) - 1}.
-__device__ __forceinline__ void run_f32{'d' if direct else ''}_dispatch_{K}_{S}(const GP_CONST uint32_t* code, const float* inb,
+// K = {K} cases per lane, S = {S} stack slots, {rows + 1} input rows: v{V_ST}..v{n_vgpr - 1}, s{S_BASE}..s{S_BASE + len(names) - 1}.
+__device__ __forceinline__ void run_f32{form if direct else ''}_dispatch_{K}_{S}(const GP_CONST uint32_t* code, const float* inb,
                                                      const float* vb, float* rb, const GP_CONST int32_t* cin,
                                                      uint32_t strideb, float* outb, uint32_t voff,
-                                                     uint32_t vc0, uint32_t vc1, uint32_t vc2, uint32_t vc3)
+                                                     uint32_t vc0, uint32_t vc1, uint32_t vc2, uint32_t vc3{nin_arg})
 {{
     const uint64_t inb64 = (uint64_t)inb, vb64 = (uint64_t)vb, rb64 = (uint64_t)rb;
     asm volatile(
@@ -489,8 +544,8 @@ __device__ __forceinline__ void run_f32{'d' if direct else ''}_dispatch_{K}_{S}(
           [vb_lo] "s"((uint32_t)vb64), [vb_hi] "s"((uint32_t)(vb64 >> 32)),
           [rb_lo] "s"((uint32_t)rb64), [rb_hi] "s"((uint32_t)(rb64 >> 32)), [cin] "s"(cin),
           [strideb] "s"(strideb), [outb] "s"(outb), [voff] "v"(voff),
-          [vc0] "v"(vc0), [vc1] "v"(vc1), [vc2] "v"(vc2), [vc3] "v"(vc3)
-        : "memory", "vcc", "scc", {sclob},
+          [vc0] "v"(vc0), [vc1] "v"(vc1), [vc2] "v"(vc2), [vc3] "v"(vc3){nin_op}
+        : "memory", "vcc", "scc", {m0}{sclob},
           {vclob});
 }}
 """
@@ -962,7 +1017,8 @@ def write_if_changed(path: str, text: str) -> None:
 
 def main(out_path: str) -> None:
     head = "// Generated by gen_dispatch.py; do not edit.\n#pragma once\n"
-    write_if_changed(out_path, head + "".join(gen_one(K, S, direct) for K, S in VARIANTS for direct in (False, True)))
+    write_if_changed(out_path, head + "".join(f"constexpr int kF32Rows{K} = {n};\n" for K, n in ROWS.items())
+                     + "".join(gen_one(K, S, form) for K, S, form in VARIANTS))
     write_if_changed(os.path.join(os.path.dirname(out_path), "dispatch_bool.inc"),
                      head + f"constexpr int kBoolDispatchInputs = {BOOL_NI};\n"
                      + "".join(gen_bool(K, S) for K, S in BOOL_VARIANTS) + gen_bool_word())

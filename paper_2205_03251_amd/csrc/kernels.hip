@@ -263,30 +263,43 @@ __global__ __launch_bounds__(64) void k_eval_f32(EvalParams p)
 // which chooses each handler through a branch table.
 #include "dispatch_f32.inc"
 
-template <int K, int S, bool DIRECT>
+// F: how the loop dispatches and what it keeps (see gen_dispatch.py).
+enum class Form { Table, Direct, Rows };
+
+template <int K, int S, Form F>
 __device__ __forceinline__ void run_f32_dispatch(const GP_CONST uint32_t* code, const float* inb, const float* vb,
                                                  float* rb, const GP_CONST int32_t* cin, uint32_t strideb,
-                                                 float* outb, uint32_t voff, uint32_t code_len)
+                                                 float* outb, uint32_t voff, uint32_t code_len, uint32_t nin)
 {
     // lane l touches the code lines at words 16 l + 1024 i, i < 4 (clamped to the chunk's last word)
     const uint32_t last = code_len > 0 ? code_len - 1 : 0, l16 = (voff / 4u) * 16u;
     const uint32_t vc0 = min(l16, last) * 4u, vc1 = min(l16 + 1024u, last) * 4u;
     const uint32_t vc2 = min(l16 + 2048u, last) * 4u, vc3 = min(l16 + 3072u, last) * 4u;
-    if constexpr (K == 4 && S == 10 && !DIRECT)
-        run_f32_dispatch_4_10(code, inb, vb, rb, cin, strideb, outb, voff, vc0, vc1, vc2, vc3);
-    else if constexpr (K == 8 && S == 10 && !DIRECT)
-        run_f32_dispatch_8_10(code, inb, vb, rb, cin, strideb, outb, voff, vc0, vc1, vc2, vc3);
-    else if constexpr (K == 4 && S == 10 && DIRECT)
-        run_f32d_dispatch_4_10(code, inb, vb, rb, cin, strideb, outb, voff, vc0, vc1, vc2, vc3);
-    else if constexpr (K == 8 && S == 10 && DIRECT)
-        run_f32d_dispatch_8_10(code, inb, vb, rb, cin, strideb, outb, voff, vc0, vc1, vc2, vc3);
-    else static_assert(K == 4 && S == 10, "no generated dispatch loop for this K and S");
+#define GP_RUN(form, k, f)                                                                                       \
+    if constexpr (K == k && S == 10 && F == f)                                                                   \
+        run_f32##form##_dispatch_##k##_10(code, inb, vb, rb, cin, strideb, outb, voff, vc0, vc1, vc2, vc3)
+#define GP_RUN_ROWS(k)                                                                                           \
+    if constexpr (K == k && S == 10 && F == Form::Rows)                                                          \
+        run_f32r_dispatch_##k##_10(code, inb, vb, rb, cin, strideb, outb, voff, vc0, vc1, vc2, vc3, nin)
+    GP_RUN(, 4, Form::Table);
+    GP_RUN(, 8, Form::Table);
+    GP_RUN(d, 1, Form::Direct);
+    GP_RUN(d, 2, Form::Direct);
+    GP_RUN(d, 4, Form::Direct);
+    GP_RUN(d, 8, Form::Direct);
+    GP_RUN_ROWS(1);
+    GP_RUN_ROWS(2);
+    GP_RUN_ROWS(4);
+    GP_RUN_ROWS(8);
+#undef GP_RUN
+#undef GP_RUN_ROWS
 }
 
-// DIRECT: the loop that dispatches into handler slots (see gen_dispatch.py).
-template <int K, int S, bool DIRECT = false>
+template <int K, int S, Form F>
 __global__ __launch_bounds__(64) void k_eval_f32_tbl(EvalParams p)
 {
+    static_assert(S == 10 && (F == Form::Table ? K == 4 || K == 8 : K == 1 || K == 2 || K == 4 || K == 8),
+                  "no generated dispatch loop for this K, S and form");
     const int lane = threadIdx.x;
     const uint32_t voff = (uint32_t)lane * 4u;
     const uint32_t strideb = (uint32_t)(p.stride * 4);
@@ -309,8 +322,8 @@ __global__ __launch_bounds__(64) void k_eval_f32_tbl(EvalParams p)
             if (ch.parent >= 0) next = load_chunk(cst(p.chunks) + ch.parent);
             float* rb = (float*)p.recs + (int64_t)ch.rec_base * p.stride + case0;
             float* outb = (float*)p.vecs + (int64_t)ch.out_slot * p.stride + case0;
-            run_f32_dispatch<K, S, DIRECT>(cst(p.code) + ch.code_off, inb, vb, rb, cst(p.chunk_in) + ch.in_off,
-                                           strideb, outb, voff, (uint32_t)ch.code_len);
+            run_f32_dispatch<K, S, F>(cst(p.code) + ch.code_off, inb, vb, rb, cst(p.chunk_in) + ch.in_off, strideb,
+                                      outb, voff, (uint32_t)ch.code_len, (uint32_t)p.n_inputs);
             if (ch.parent < 0) break;
             // The loop wrote the chunk's vector with agent-coherent stores and
             // waited for them to complete, and LOAD reads vectors with
@@ -803,10 +816,16 @@ static Variant g_variants[] = {
     {"f32_k8_s16", 0, 8, 16, (const void*)k_eval_f32<8, 16>, 0},
     {"f32_k4_s10", 0, 4, 10, (const void*)k_eval_f32<4, 10>, 0},
     {"f32_k8_s10", 0, 8, 10, (const void*)k_eval_f32<8, 10>, 0},
-    {"f32t_k4_s10", 0, 4, 10, (const void*)k_eval_f32_tbl<4, 10>, 0, 1, 0},
-    {"f32t_k8_s10", 0, 8, 10, (const void*)k_eval_f32_tbl<8, 10>, 0, 1, 0},
-    {"f32d_k4_s10", 0, 4, 10, (const void*)k_eval_f32_tbl<4, 10, true>, 0, 1, 0},
-    {"f32d_k8_s10", 0, 8, 10, (const void*)k_eval_f32_tbl<8, 10, true>, 0, 1, 0},
+    {"f32t_k4_s10", 0, 4, 10, (const void*)k_eval_f32_tbl<4, 10, Form::Table>, 0, 1, 0},
+    {"f32t_k8_s10", 0, 8, 10, (const void*)k_eval_f32_tbl<8, 10, Form::Table>, 0, 1, 0},
+    {"f32d_k4_s10", 0, 4, 10, (const void*)k_eval_f32_tbl<4, 10, Form::Direct>, 0, 1, 0},
+    {"f32d_k8_s10", 0, 8, 10, (const void*)k_eval_f32_tbl<8, 10, Form::Direct>, 0, 1, 0},
+    {"f32d_k1_s10", 0, 1, 10, (const void*)k_eval_f32_tbl<1, 10, Form::Direct>, 0, 1, 0},
+    {"f32d_k2_s10", 0, 2, 10, (const void*)k_eval_f32_tbl<2, 10, Form::Direct>, 0, 1, 0},
+    {"f32r_k1_s10", 0, 1, 10, (const void*)k_eval_f32_tbl<1, 10, Form::Rows>, 0, 1, 0, 0, kF32Rows1},
+    {"f32r_k2_s10", 0, 2, 10, (const void*)k_eval_f32_tbl<2, 10, Form::Rows>, 0, 1, 0, 0, kF32Rows2},
+    {"f32r_k4_s10", 0, 4, 10, (const void*)k_eval_f32_tbl<4, 10, Form::Rows>, 0, 1, 0, 0, kF32Rows4},
+    {"f32r_k8_s10", 0, 8, 10, (const void*)k_eval_f32_tbl<8, 10, Form::Rows>, 0, 1, 0, 0, kF32Rows8},
     {"bool_k1_s16", 1, 1, 16, (const void*)k_eval_bool<1, 16>, 0},
     {"bool_k2_s16", 1, 2, 16, (const void*)k_eval_bool<2, 16>, 0},
     {"bool_k1_s10", 1, 1, 10, (const void*)k_eval_bool<1, 10>, 0},

@@ -161,9 +161,11 @@ static int default_variant(int vtype, const CaseSet* cs, const Pop* p, int force
     int wantK = 1;
     if (vtype == GP_F32) wantK = cs->n_elems <= 64 ? 1 : cs->n_elems <= 128 ? 2 : 4;
     else wantK = cs->n_elems <= 64 ? 1 : 2;
-    // prefer a table-dispatch interpreter when one fits
-    for (int v = 0; v < variant_count(); ++v)
-        if (ok(v) && vt[v].K == wantK && vt[v].table) return v;
+    // prefer a table-dispatch interpreter when one fits, the kind that holds input rows in registers for
+    // populations of several inputs (for one input its registers would only cost resident waves)
+    for (int kind : {vtype == GP_F32 && p->n_inputs > 1 ? 1 : 0, 0})
+        for (int v = 0; v < variant_count(); ++v)
+            if (ok(v) && vt[v].K == wantK && vt[v].table && (vt[v].rows > 0) == (kind == 1)) return v;
     for (int v = 0; v < variant_count(); ++v)
         if (ok(v) && vt[v].K == wantK) return v;
     for (int v = 0; v < variant_count(); ++v)
@@ -2509,6 +2511,7 @@ int gp_autotune(gp_ctx* ctx, gp_handle pop, gp_handle cases, int* best_variant, 
             if (!variant_fits(vt, qp->vtype, qp->max_stack, qp->n_inputs, cs->n_elems, cs->stride,
                               qp->vtype == GP_BOOL ? 8 : 4))
                 continue;
+            if (vt.rows > 0 && qp->n_inputs == 1) continue;     // registers for rows that are never read
             float t = 0.f;
             RC(time_variant(qp, Launch{v, 0}, &t));
             full.emplace_back(t, v);
