@@ -8,8 +8,9 @@
 // code length); the crossover points' paths are read up the parent index and
 // their records assigned on the host; chunk roots are compacted, numbered and
 // given code offsets (host prefix sums over per-chunk lengths); one thread per
-// chunk counts its LOADs, then writes its code straight into the population's
-// program.  The host keeps only per-chunk and per-record tables.
+// node writes its word straight into the population's program, its place found
+// by prefix sums over the nodes (small populations: one thread per chunk writes
+// the chunk's code).  The host keeps only per-chunk and per-record tables.
 #include <algorithm>
 #include <atomic>
 #include <chrono>
@@ -129,16 +130,20 @@ __global__ __launch_bounds__(256) void k_dc_finish(DcNodes q, uint8_t* flags)
     if (g < q.n) flags[g] = dc_finish(q, g) ? 1 : 0;
 }
 
-// Chunk roots: their chunk ids into cnt, their code lengths and subtree ends out.
+// Chunk roots: their chunk ids into cnt (when ids is given), their code lengths
+// and subtree ends out, and where their LOADs come in the order of all LOADs
+// (key, when given): by parent in prefix order, its first operand before its
+// second (-1 at a tree's root).
 __global__ __launch_bounds__(256) void k_dc_root_info(DcNodes q, const int64_t* roots, const int32_t* ids, int64_t n,
-                                                      int32_t* rlen, int32_t* rend)
+                                                      int32_t* rlen, int32_t* rend, int64_t* key)
 {
     const int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (k >= n) return;
     const int64_t g = roots[k];
-    q.cnt[g] = ids[k];
+    if (ids) q.cnt[g] = ids[k];
     rlen[k] = q.len[g];
     rend[k] = q.endl[g];
+    if (key) key[k] = dc_load_key(q, g, q.offsets[dc_tree_of(q, g)]);
 }
 
 // Subtree ends of listed nodes.
@@ -272,6 +277,183 @@ __global__ __launch_bounds__(256) void k_dc_emit(DcNodes q, DcChunks c, unsigned
         if (pb < pe) pb += __popcll(idle);
         if (busy) busy = dc_emit_step(q, c, st) ? 1 : 0;
         if (!more && pb >= pe && __ballot(busy != 0) == 0) break;
+    }
+}
+
+// ------------------------------------------------ emission, a thread per node
+// A node's code starts, in its chunk, after the code of every operand
+// evaluated before it on its path: at each function with two operands to
+// evaluate, the second one's subtree starts the first one's words later and one
+// stack slot higher.  Those steps are added at the second operand's position
+// and taken off at its end, and one prefix sum over all positions gives every
+// node's place: its sum less its chunk root's (steps of functions above the
+// chunk cover both, steps inside chunks in between have ended).  The same sum
+// over chunk ids (entered at a root, left at its end) tells each node its
+// chunk.  A step holds words << kDcSlotBits | slots; sums wrap around, their
+// differences within a chunk do not.
+//
+// One thread per chunk walking its nodes in order (k_dc_emit) waits for three
+// dependent loads per node, 4 us, for as many nodes as the largest chunk has:
+// 9.2 ms for 4.3e7 nodes in 2048-node chunks, 6.9 ms in 1024-node ones.
+constexpr int64_t kDcPerNode = 65536;           // nodes from which a thread per node emits
+
+__global__ __launch_bounds__(256) void k_dc_steps(DcNodes q, uint32_t* step)
+{
+    const int64_t g = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (g >= q.n) return;
+    int64_t from, to;
+    uint32_t by;
+    if (!dc_second_operand(q, g, &from, &to, &by)) return;
+    atomicAdd(step + from, by);
+    if (to < q.n) atomicAdd(step + to, 0u - by);
+}
+
+// Chunk k's id takes over at its root and its parent's at its end.
+__global__ __launch_bounds__(256) void k_dc_id_steps(int64_t n, const int64_t* root, const int64_t* end,
+                                                     const int32_t* parent, int64_t nch, uint32_t* step)
+{
+    const int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (k >= nch) return;
+    const uint32_t by = (uint32_t)k - (parent[k] < 0 ? 0u : (uint32_t)parent[k]);
+    atomicAdd(step + root[k], by);
+    if (end[k] < n) atomicAdd(step + end[k], 0u - by);
+}
+
+// Inclusive prefix sums of two arrays at once, in place: sums of blocks of
+// kDcSpan positions, a scan of those by one workgroup, then each block's own.
+__device__ __forceinline__ uint2 dc_wave_scan(uint2 v)
+{
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t x = __shfl_up(v.x, o, 64), y = __shfl_up(v.y, o, 64);
+        if ((int)(threadIdx.x & 63) >= o) {
+            v.x += x;
+            v.y += y;
+        }
+    }
+    return v;
+}
+
+// The exclusive prefix of v over the workgroup's threads (W waves); the total in *sum.
+template <int W> __device__ __forceinline__ uint2 dc_block_scan(uint2 v, uint2* sum)
+{
+    __shared__ uint2 ws[W];
+    const uint2 inc = dc_wave_scan(v);
+    const int w = threadIdx.x >> 6;
+    __syncthreads();                            // a caller's earlier reads of ws are done
+    if ((threadIdx.x & 63) == 63) ws[w] = inc;
+    __syncthreads();
+    uint2 before = make_uint2(0, 0), all = make_uint2(0, 0);
+    for (int i = 0; i < W; ++i) {
+        if (i < w) {
+            before.x += ws[i].x;
+            before.y += ws[i].y;
+        }
+        all.x += ws[i].x;
+        all.y += ws[i].y;
+    }
+    *sum = all;
+    return make_uint2(before.x + inc.x - v.x, before.y + inc.y - v.y);
+}
+
+// 16 positions of a step array from position base (a multiple of 16; the array has room for the last block)
+__device__ __forceinline__ void dc_load16(const uint32_t* a, int64_t base, uint32_t (&x)[16])
+{
+    for (int j = 0; j < 4; ++j) {
+        const uint4 v = *(const uint4*)(a + base + 4 * j);
+        x[4 * j] = v.x;
+        x[4 * j + 1] = v.y;
+        x[4 * j + 2] = v.z;
+        x[4 * j + 3] = v.w;
+    }
+}
+
+__global__ __launch_bounds__(256) void k_dc_scan_sums(const uint32_t* a, const uint32_t* b, uint2* bsum)
+{
+    const int64_t base = (int64_t)blockIdx.x * kDcSpan + (int64_t)threadIdx.x * 16;
+    uint32_t x[16], y[16];
+    dc_load16(a, base, x);
+    dc_load16(b, base, y);
+    uint2 v = make_uint2(0, 0), sum;
+    for (int j = 0; j < 16; ++j) {
+        v.x += x[j];
+        v.y += y[j];
+    }
+    dc_block_scan<4>(v, &sum);
+    if (threadIdx.x == 0) bsum[blockIdx.x] = sum;
+}
+
+__global__ __launch_bounds__(1024) void k_dc_scan_top(uint2* bsum, int64_t nb)
+{
+    uint2 run = make_uint2(0, 0);
+    for (int64_t b0 = 0; b0 < nb; b0 += 1024) {
+        const int64_t i = b0 + threadIdx.x;
+        const uint2 v = i < nb ? bsum[i] : make_uint2(0, 0);
+        uint2 sum;
+        const uint2 pre = dc_block_scan<16>(v, &sum);
+        if (i < nb) bsum[i] = make_uint2(run.x + pre.x, run.y + pre.y);
+        run.x += sum.x;
+        run.y += sum.y;
+    }
+}
+
+__global__ __launch_bounds__(256) void k_dc_scan_apply(uint32_t* a, uint32_t* b, const uint2* boff)
+{
+    const int64_t base = (int64_t)blockIdx.x * kDcSpan + (int64_t)threadIdx.x * 16;
+    uint32_t x[16], y[16];
+    dc_load16(a, base, x);
+    dc_load16(b, base, y);
+    uint2 v = make_uint2(0, 0), sum;
+    for (int j = 0; j < 16; ++j) {
+        v.x += x[j];
+        v.y += y[j];
+    }
+    uint2 at = dc_block_scan<4>(v, &sum);
+    at.x += boff[blockIdx.x].x;
+    at.y += boff[blockIdx.x].y;
+    for (int j = 0; j < 16; ++j) {
+        x[j] = at.x += x[j];
+        y[j] = at.y += y[j];
+    }
+    for (int j = 0; j < 4; ++j) {
+        *(uint4*)(a + base + 4 * j) = make_uint4(x[4 * j], x[4 * j + 1], x[4 * j + 2], x[4 * j + 3]);
+        *(uint4*)(b + base + 4 * j) = make_uint4(y[4 * j], y[4 * j + 1], y[4 * j + 2], y[4 * j + 3]);
+    }
+}
+
+// Per chunk: its frame (its root's place), its END word, and the word by which
+// its parent LOADs it, its highest slot; stores is cleared for k_dc_emit_nodes.
+__global__ __launch_bounds__(256) void k_dc_emit_chunks(DcNodes q, DcChunks c, const uint32_t* place, uint32_t* frame)
+{
+    const int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (k >= c.n) return;
+    const int64_t g = c.root[k];
+    const uint32_t at = place[g];
+    frame[k] = at;
+    c.code[c.code_off[k] + q.len[g]] = kEndWord;
+    c.stores[k] = 0;
+    c.max_slot[k] = (q.info[g] & 63) - 1;       // the slots its code uses are its root's stack need
+    const int32_t p = c.parent[k];
+    if (p >= 0) c.code[c.code_off[p] + dc_place_pos(at - place[c.root[p]])] =
+        dc_word(0, M_LOAD, dc_place_slot(at - place[c.root[p]]), (uint32_t)c.load_idx[k]);
+}
+
+// Bound by its loads: about 40 bytes read and one word written per node, the
+// right operand's by its position.
+__global__ __launch_bounds__(256) void k_dc_emit_nodes(DcNodes q, DcChunks c, const uint32_t* place, const uint32_t* id,
+                                                       const uint32_t* frame)
+{
+    const int64_t g = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (g >= q.n) return;
+    const uint32_t k = id[g];
+    const uint32_t at = place[g] - frame[k];
+    int64_t pos;
+    uint32_t word, store;
+    if (!dc_node_word(q, g, dc_place_pos(at), dc_place_slot(at), &pos, &word, &store)) return;
+    uint32_t* code = c.code + c.code_off[k];
+    code[pos] = word;
+    if (store != 0) {
+        code[pos + 1] = store;
+        c.stores[k] = 1;
     }
 }
 
@@ -436,8 +618,9 @@ int device_compile_population(Ctx* c, int vtype, int n_inputs, int64_t n_trees, 
     if (index_min_size > 0) RC(scratch_alloc(c, arena, big, (size_t)n));
     RC(scratch_alloc(c, arena, info, (size_t)n * 4));
     RC(scratch_alloc(c, arena, len, (size_t)n * 4));
-    RC(scratch_alloc(c, arena, open, (size_t)n * 4));
-    RC(scratch_alloc(c, arena, cnt, (size_t)n * 4));
+    const int64_t n_span = (n + kDcSpan - 1) / kDcSpan * kDcSpan;      // the scans read whole blocks
+    RC(scratch_alloc(c, arena, open, (size_t)n_span * 4));
+    RC(scratch_alloc(c, arena, cnt, (size_t)n_span * 4));
     RC(scratch_alloc(c, arena, ncut, (size_t)n));
     RC(scratch_alloc(c, arena, err, 4));
     RC(scratch_alloc(c, arena, counter, 16));
@@ -594,18 +777,27 @@ int device_compile_population(Ctx* c, int vtype, int n_inputs, int64_t n_trees, 
     if (!dc_number_chunks(roots_asc, offsets, n_trees, &root, &tstart, &ctree, &ids, &cbase))
         return set_err(c, GP_EINVAL, "internal error: a tree without its root chunk");
     std::vector<int32_t> rlen(nch), rend(nch);
+    std::vector<int64_t> key;                   // per chunk in ascending root order (k_dc_root_info)
+    const bool per_node = n >= kDcPerNode && C <= kDcPlaceMaxC;
     {
-        DevBuf ids_d, rlen_d, rend_d;
-        RC(up(c, arena, ids_d, ids.data(), (size_t)nch * 4, s));
+        DevBuf ids_d, rlen_d, rend_d, key_d;
+        if (per_node) {
+            key.resize(nch);
+            RC(scratch_alloc(c, arena, key_d, (size_t)nch * 8));
+        } else {
+            RC(up(c, arena, ids_d, ids.data(), (size_t)nch * 4, s));
+        }
         RC(scratch_alloc(c, arena, rlen_d, (size_t)nch * 4));
         RC(scratch_alloc(c, arena, rend_d, (size_t)nch * 4));
         hipLaunchKernelGGL(k_dc_root_info, dim3(blocks_for(nch)), dim3(256), 0, s, q, roots_d.as<int64_t>(),
-                           ids_d.as<int32_t>(), nch, rlen_d.as<int32_t>(), rend_d.as<int32_t>());
+                           per_node ? (const int32_t*)nullptr : ids_d.as<int32_t>(), nch, rlen_d.as<int32_t>(),
+                           rend_d.as<int32_t>(), per_node ? key_d.as<int64_t>() : (int64_t*)nullptr);
         HIPC(c, hipGetLastError());
         // in ascending root order
         std::vector<int32_t> a(nch), b(nch);
         RC(down(c, a.data(), rlen_d, (size_t)nch * 4, s));
         RC(down(c, b.data(), rend_d, (size_t)nch * 4, s));
+        if (per_node) RC(down(c, key.data(), key_d, (size_t)nch * 8, s));
         HIPC(c, hipStreamSynchronize(s));
         for (int64_t j = 0; j < nch; ++j) {
             rlen[ids[j]] = a[j];
@@ -622,22 +814,12 @@ int device_compile_population(Ctx* c, int vtype, int n_inputs, int64_t n_trees, 
     const int64_t n_code = code_off[nch];
     if (out) out->max_code_len = nch ? *std::max_element(code_len.begin(), code_len.end()) : 0;
 
-    // code emission, one pass: each child chunk learns its parent and which of
-    // the parent's LOADs reads it; the LOAD lists are then put together here
+    // code emission; the chunk graph (each chunk's parent and LOAD inputs) and node counts
     DevBuf root_d, ts_d, off_d, nin_d, par_d, lix_d, nodes_d, ms_d, st_d, slot;
     RC(up(c, arena, root_d, root.data(), (size_t)nch * 8, s));
-    RC(up(c, arena, ts_d, tstart.data(), (size_t)nch * 8, s));
     RC(up(c, arena, off_d, code_off.data(), (size_t)nch * 8, s));
-    RC(scratch_alloc(c, arena, nin_d, (size_t)nch * 4));
-    RC(scratch_alloc(c, arena, par_d, (size_t)nch * 4));
-    RC(scratch_alloc(c, arena, lix_d, (size_t)nch * 4));
-    RC(scratch_alloc(c, arena, nodes_d, (size_t)nch * 8));
     RC(scratch_alloc(c, arena, ms_d, (size_t)nch * 4));
     RC(scratch_alloc(c, arena, st_d, (size_t)nch));
-    RC(scratch_alloc(c, arena, slot, (size_t)n));
-    q.slot = slot.as<uint8_t>();
-    HIPC(c, launch_fill_i32(par_d.as<int32_t>(), nch, -1, s));
-    HIPC(c, launch_fill_i32(lix_d.as<int32_t>(), nch, -1, s));
     // the program: the population's own buffer, or a temporary one copied to the host
     DevBuf code_tmp;
     DevBuf& code = out ? out->code : code_tmp;
@@ -647,51 +829,85 @@ int device_compile_population(Ctx* c, int vtype, int n_inputs, int64_t n_trees, 
     DcChunks ck{};
     ck.n = nch;
     ck.root = root_d.as<int64_t>();
-    ck.tree_start = ts_d.as<int64_t>();
     ck.code_off = off_d.as<int64_t>();
     ck.code = code.as<uint32_t>();
-    ck.n_in = nin_d.as<int32_t>();
-    ck.parent = par_d.as<int32_t>();
-    ck.load_idx = lix_d.as<int32_t>();
-    ck.nodes = nodes_d.as<int64_t>();
     ck.max_slot = ms_d.as<int32_t>();
     ck.stores = st_d.as<uint8_t>();
-    HIPC(c, launch_fill_i32(counter.as<int32_t>(), 4, 0, s));
-    hipLaunchKernelGGL(k_dc_emit, dim3(dc_persistent_blocks(c, nch, kDcEmitBatch, max_blocks)), dim3(256), 0, s, q, ck,
-                       counter.as<unsigned long long>());
-    HIPC(c, hipGetLastError());
-    if (tr.on) {
-        HIPC(c, hipStreamSynchronize(s));
-        tr.mark("emission kernel");
-    }
-    std::vector<int32_t> n_in(nch), parent(nch), load_idx(nch), max_slot(nch);
-    std::vector<int64_t> nodes(nch);
+    std::vector<int32_t> n_in(nch, 0), parent(nch, -1), load_idx(nch, -1), max_slot(nch), ins;
+    std::vector<int64_t> nodes(nch), in_off;
     std::vector<uint8_t> stores(nch);
-    RC(down(c, n_in.data(), nin_d, (size_t)nch * 4, s));
-    RC(down(c, parent.data(), par_d, (size_t)nch * 4, s));
-    RC(down(c, load_idx.data(), lix_d, (size_t)nch * 4, s));
-    RC(down(c, nodes.data(), nodes_d, (size_t)nch * 8, s));
-    RC(down(c, max_slot.data(), ms_d, (size_t)nch * 4, s));
-    RC(down(c, stores.data(), st_d, (size_t)nch, s));
-    HIPC(c, hipStreamSynchronize(s));
-    slot.release();
+    if (per_node) {
+        if (!dc_chunk_graph(roots_asc, ids, rend, root, tstart, key, &parent, &load_idx, &nodes, &in_off, &ins))
+            return set_err(c, GP_EINVAL, "internal error: inconsistent chunk graph");
+        std::vector<int64_t> end(nch);
+        for (int64_t k = 0; k < nch; ++k) {
+            end[k] = tstart[k] + rend[k];
+            n_in[k] = (int32_t)(in_off[k + 1] - in_off[k]);
+        }
+        DevBuf end_d, frame_d, bsum_d;
+        const int64_t nb = (n + kDcSpan - 1) / kDcSpan;
+        RC(up(c, arena, end_d, end.data(), (size_t)nch * 8, s));
+        RC(up(c, arena, par_d, parent.data(), (size_t)nch * 4, s));
+        RC(up(c, arena, lix_d, load_idx.data(), (size_t)nch * 4, s));
+        RC(scratch_alloc(c, arena, frame_d, (size_t)nch * 4));
+        RC(scratch_alloc(c, arena, bsum_d, (size_t)nb * 8));
+        ck.parent = par_d.as<int32_t>();
+        ck.load_idx = lix_d.as<int32_t>();
+        // open and cnt are free now: places and chunk ids (whole blocks of both were allocated)
+        uint32_t* place = open.as<uint32_t>();
+        uint32_t* id = cnt.as<uint32_t>();
+        HIPC(c, launch_fill_i32(open.as<int32_t>(), nb * kDcSpan, 0, s));
+        HIPC(c, launch_fill_i32(cnt.as<int32_t>(), nb * kDcSpan, 0, s));
+        hipLaunchKernelGGL(k_dc_steps, dim3(blocks_for(n)), dim3(256), 0, s, q, place);
+        hipLaunchKernelGGL(k_dc_id_steps, dim3(blocks_for(nch)), dim3(256), 0, s, n, ck.root, end_d.as<int64_t>(),
+                           ck.parent, nch, id);
+        hipLaunchKernelGGL(k_dc_scan_sums, dim3((unsigned)nb), dim3(256), 0, s, place, id, bsum_d.as<uint2>());
+        hipLaunchKernelGGL(k_dc_scan_top, dim3(1), dim3(1024), 0, s, bsum_d.as<uint2>(), nb);
+        hipLaunchKernelGGL(k_dc_scan_apply, dim3((unsigned)nb), dim3(256), 0, s, place, id, bsum_d.as<uint2>());
+        hipLaunchKernelGGL(k_dc_emit_chunks, dim3(blocks_for(nch)), dim3(256), 0, s, q, ck, place,
+                           frame_d.as<uint32_t>());
+        hipLaunchKernelGGL(k_dc_emit_nodes, dim3(blocks_for(n)), dim3(256), 0, s, q, ck, place, id,
+                           frame_d.as<uint32_t>());
+        HIPC(c, hipGetLastError());
+        RC(down(c, max_slot.data(), ms_d, (size_t)nch * 4, s));
+        RC(down(c, stores.data(), st_d, (size_t)nch, s));
+        HIPC(c, hipStreamSynchronize(s));
+        tr.mark("emission kernels");
+    } else {
+        // one pass: each child chunk learns its parent and which of the parent's LOADs reads it; the LOAD lists
+        // are then put together here
+        RC(up(c, arena, ts_d, tstart.data(), (size_t)nch * 8, s));
+        RC(scratch_alloc(c, arena, nin_d, (size_t)nch * 4));
+        RC(scratch_alloc(c, arena, par_d, (size_t)nch * 4));
+        RC(scratch_alloc(c, arena, lix_d, (size_t)nch * 4));
+        RC(scratch_alloc(c, arena, nodes_d, (size_t)nch * 8));
+        RC(scratch_alloc(c, arena, slot, (size_t)n));
+        q.slot = slot.as<uint8_t>();
+        HIPC(c, launch_fill_i32(par_d.as<int32_t>(), nch, -1, s));
+        HIPC(c, launch_fill_i32(lix_d.as<int32_t>(), nch, -1, s));
+        ck.tree_start = ts_d.as<int64_t>();
+        ck.n_in = nin_d.as<int32_t>();
+        ck.parent = par_d.as<int32_t>();
+        ck.load_idx = lix_d.as<int32_t>();
+        ck.nodes = nodes_d.as<int64_t>();
+        HIPC(c, launch_fill_i32(counter.as<int32_t>(), 4, 0, s));
+        hipLaunchKernelGGL(k_dc_emit, dim3(dc_persistent_blocks(c, nch, kDcEmitBatch, max_blocks)), dim3(256), 0, s, q,
+                           ck, counter.as<unsigned long long>());
+        HIPC(c, hipGetLastError());
+        RC(down(c, n_in.data(), nin_d, (size_t)nch * 4, s));
+        RC(down(c, parent.data(), par_d, (size_t)nch * 4, s));
+        RC(down(c, load_idx.data(), lix_d, (size_t)nch * 4, s));
+        RC(down(c, nodes.data(), nodes_d, (size_t)nch * 8, s));
+        RC(down(c, max_slot.data(), ms_d, (size_t)nch * 4, s));
+        RC(down(c, stores.data(), st_d, (size_t)nch, s));
+        HIPC(c, hipStreamSynchronize(s));
+        slot.release();
+        if (!dc_scatter_inputs(nch, n_in.data(), parent.data(), load_idx.data(), &in_off, &ins) ||
+            in_off[nch] != nch - n_trees)
+            return set_err(c, GP_EINVAL, "internal error: chunk inputs do not add up");
+    }
     for (int64_t k = 0; k < nch; ++k)
         if ((uint32_t)n_in[k] > kMaxPayload) return set_err(c, GP_EINVAL, "chunk reads too many child chunks");
-    std::vector<int64_t> in_off;
-    std::vector<int32_t> ins;
-    if (!dc_scatter_inputs(nch, n_in.data(), parent.data(), load_idx.data(), &in_off, &ins) ||
-        in_off[nch] != nch - n_trees) {
-        int64_t loads = 0, orphans = 0, first = -1;
-        for (int64_t k = 0; k < nch; ++k) {
-            loads += n_in[k];
-            const bool top = k == cbase[ctree[k] + 1] - 1;
-            if (!top && parent[k] < 0 && orphans++ == 0) first = k;
-        }
-        return set_err(c, GP_EINVAL, "internal error: chunk inputs do not add up (" + std::to_string(loads) +
-                                         " LOADs, " + std::to_string(nch - n_trees) + " child chunks, " +
-                                         std::to_string(orphans) + " without a parent, first " +
-                                         std::to_string(first) + ")");
-    }
     tr.mark("emission");
 
     // subtrees of at least index_min_size nodes (co-evaluation's path search),

@@ -412,6 +412,86 @@ GPE_HD inline bool dc_emit_step(const DcNodes& q, const DcChunks& c, DcEmit& e)
     return true;
 }
 
+// ----- emission of one node at a time (any order)
+// A node's place in its chunk's code, position << kDcSlotBits | stack slot, is
+// the sum of steps over the functions above it (see k_dc_steps): the second
+// operand of a function g starts the first's words later, one slot higher.
+// A place needs 32 - kDcSlotBits bits for the position: a chunk holds at most
+// 2 C nodes and a STORE beside each of their words, so C <= kDcPlaceMaxC is enough.
+constexpr int kDcSlotBits = 5;
+constexpr int64_t kDcPlaceMaxC = int64_t(1) << 24;
+
+GPE_HD inline int64_t dc_place_pos(uint32_t place) { return (int64_t)(place >> kDcSlotBits); }
+GPE_HD inline uint32_t dc_place_slot(uint32_t place) { return place & ((1u << kDcSlotBits) - 1); }
+
+// Start of the tree of function g, from its left operand's tree-local parent.
+GPE_HD inline int64_t dc_tree_start(const DcNodes& q, int64_t g) { return g - q.parl[g + 1]; }
+
+// Function g with two operands to evaluate: the positions [*from, *to) of its
+// second operand, whose places lie *by further.  False for every other node.
+GPE_HD inline bool dc_second_operand(const DcNodes& q, int64_t g, int64_t* from, int64_t* to, uint32_t* by)
+{
+    if (!(q.ops[g] & kFuncBit)) return false;
+    const int32_t iv = q.info[g];
+    const uint32_t m = (uint32_t)(iv >> 8) & 7;
+    if (m != M_SS && m != M_RS) return false;
+    const bool first_r = ((iv >> 8) & 8) != 0;
+    const int64_t s = dc_tree_start(q, g), l = g + 1, r = s + q.endl[l];
+    const int64_t first = first_r ? r : l;
+    *from = first_r ? l : r;
+    *to = first_r ? r : s + q.endl[g];
+    const int32_t w = (q.info[first] & kDcCut) ? 1 : q.len[first];
+    *by = ((uint32_t)w << kDcSlotBits) + 1u;
+    return true;
+}
+
+// The word of node g, whose code starts at pos with its value in slot d:
+// *word at *at, *store after it (0: none).  False when it has none (folded into its parent).
+GPE_HD inline bool dc_node_word(const DcNodes& q, int64_t g, int64_t pos, uint32_t d, int64_t* at, uint32_t* word,
+                                uint32_t* store)
+{
+    const uint8_t op = q.ops[g];
+    *store = 0;
+    if (!(op & kFuncBit)) {
+        if (dc_foldable(q, g) && q.parl[g] >= 0) return false;      // every foldable operand is folded
+        *at = pos;
+        *word = dc_word(0, M_PUSH, d, op);
+        return true;
+    }
+    const int form = (q.info[g] >> 8) & 31;
+    const uint32_t m = (uint32_t)(form & 7);
+    const int64_t s = dc_tree_start(q, g), l = g + 1, r = s + q.endl[l];
+    auto words = [&](int64_t x) { return (q.info[x] & kDcCut) ? 1 : q.len[x]; };
+    uint32_t payload = 0;
+    if (m == M_XX) {
+        if (q.boolean) payload = (uint32_t)q.ops[l] | ((uint32_t)q.ops[r] << 11);
+        *at = pos;
+    } else if (m == M_XS || m == M_SX) {
+        const bool left_folded = (form & 16) != 0;
+        if (q.boolean) payload = q.ops[left_folded ? l : r];
+        *at = pos + words(left_folded ? r : l);
+    } else {
+        *at = pos + words(l) + words(r);
+    }
+    *word = dc_word(op & 3, m, d, payload);
+    if (q.rec && q.rec[g] >= 0) *store = dc_word(0, M_STORE, d, (uint32_t)q.rec[g]);
+    return true;
+}
+
+// Where the LOAD of chunk root g comes among its parent chunk's: by parent in
+// prefix order, the first operand evaluated before the second.  -1 at the root
+// of the tree, which starts at s.
+GPE_HD inline int64_t dc_load_key(const DcNodes& q, int64_t g, int64_t s)
+{
+    const int32_t p = q.parl[g];
+    if (p < 0) return -1;
+    const int64_t pg = s + p;
+    const int form = (q.info[pg] >> 8) & 31;
+    const uint32_t m = (uint32_t)(form & 7);
+    const bool two = m == M_SS || m == M_RS;
+    return pg * 2 + (two && (g == pg + 1) == ((form & 8) != 0) ? 1 : 0);
+}
+
 // ------------------------------------------------------------ host glue
 
 // The LOAD lists of all chunks from each child's parent and LOAD index:
@@ -473,6 +553,49 @@ inline bool dc_number_chunks(const std::vector<int64_t>& roots_asc, const int64_
         j = j1;
     }
     return j == nch;
+}
+
+// The chunk graph from the chunk roots' nesting.  roots_asc, ids, key: per chunk
+// in ascending root order (key: dc_load_key); rend, root, tstart: per chunk
+// id.  Outputs per chunk id: parent (-1: a tree's root chunk), which of its
+// parent's LOADs reads it, its own nodes; the LOAD lists (in_off, inputs).
+inline bool dc_chunk_graph(const std::vector<int64_t>& roots_asc, const std::vector<int32_t>& ids,
+                           const std::vector<int32_t>& rend, const std::vector<int64_t>& root,
+                           const std::vector<int64_t>& tstart, const std::vector<int64_t>& key,
+                           std::vector<int32_t>* parent, std::vector<int32_t>* load_idx, std::vector<int64_t>* nodes,
+                           std::vector<int64_t>* in_off, std::vector<int32_t>* inputs)
+{
+    const int64_t nch = (int64_t)roots_asc.size();
+    std::vector<int32_t> open;                  // the chunks around the current position, outermost first
+    std::vector<int64_t> key_of(nch);
+    in_off->assign(nch + 1, 0);
+    for (int64_t j = 0; j < nch; ++j) {
+        const int32_t k = ids[j];
+        const int64_t end = tstart[k] + rend[k];
+        while (!open.empty() && tstart[open.back()] + rend[open.back()] <= root[k]) open.pop_back();
+        if (root[k] != roots_asc[j] || (key[j] < 0) != open.empty()) return false;
+        (*nodes)[k] = end - root[k];
+        key_of[k] = key[j];
+        (*parent)[k] = open.empty() ? -1 : open.back();
+        if (!open.empty()) {
+            const int32_t p = open.back();
+            if (end > tstart[p] + rend[p]) return false;
+            (*nodes)[p] -= end - root[k];
+            ++(*in_off)[p + 1];
+        }
+        open.push_back(k);
+    }
+    for (int64_t k = 0; k < nch; ++k) (*in_off)[k + 1] += (*in_off)[k];
+    inputs->assign((size_t)(*in_off)[nch], -1);
+    std::vector<int64_t> at(in_off->begin(), in_off->end() - 1);
+    for (int64_t k = 0; k < nch; ++k)
+        if ((*parent)[k] >= 0) (*inputs)[(size_t)at[(*parent)[k]]++] = (int32_t)k;
+    for (int64_t k = 0; k < nch; ++k) {
+        const auto b = inputs->begin() + (*in_off)[k], e = inputs->begin() + (*in_off)[k + 1];
+        std::sort(b, e, [&](int32_t x, int32_t y) { return key_of[x] < key_of[y]; });
+        for (auto i = b; i != e; ++i) (*load_idx)[*i] = (int32_t)(i - b);
+    }
+    return true;
 }
 
 // A recorded function node: global index, record id (local to its tree),
