@@ -22,6 +22,11 @@ struct DevChunk {            // 32 bytes
     int32_t n_in;            // LOAD inputs: chunk_in[in_off .. in_off + n_in)
 };
 
+// Counters that hand out a launch's work items (see next_item): one cache line
+// each, kCursors of them per launch.
+constexpr int kCursors = 16;
+constexpr int kCursorStride = 32;         // in words
+
 // Work item = (chunk << 16) | slice.
 struct EvalParams {
     const uint32_t* code;
@@ -30,13 +35,14 @@ struct EvalParams {
     const int64_t* items;        // leaf work items in priority order
     int64_t n_items;
     int32_t* pending;            // [n_chunks][n_slices] unfinished inputs
-    unsigned int* cursor;        // next item to hand out
+    unsigned int* cursor;        // n_cursors counters, kCursorStride words apart
     const void* inputs;          // [n_inputs][stride]
     void* vecs;                  // [n_slots][stride] chunk and root values
     void* recs;                  // [n_records][stride] parent caches
     int64_t stride;              // padded cases (float) or words (Boolean)
     int32_t n_slices;
     int32_t n_inputs;
+    int32_t n_cursors;           // counters in use, a power of two up to kCursors
 };
 
 // One incremental child.  Pointers refer to the mother's population, so one
@@ -136,7 +142,7 @@ struct Variant {
     int table;                   // runs the generated table-dispatch loop
     int max_inputs;              // input rows held in registers (0: any count, staged in LDS)
     int max_elems;               // > 0: at most this many case words (Boolean) or cases (float)
-    int rows;                    // float: input rows past the first held in registers (others are read from memory)
+    int kind;                    // float table loops: 0 branch table, 1 direct dispatch, 2 direct with input rows in registers
 };
 
 // Whether variant v can run a population of value type vtype whose programs
@@ -161,8 +167,9 @@ inline size_t variant_lds(const Variant& v, int n_inputs)
 int variant_count();
 Variant* variant_table();
 
+// pending = init; counter i at cursor[i * kCursorStride], i < n_cursors, = 0.
 hipError_t launch_init(int32_t* pending, const int32_t* init, int64_t n, unsigned int* cursor,
-                       int n_cursors, hipStream_t s);
+                       int64_t n_cursors, hipStream_t s);
 hipError_t launch_eval(int variant, const EvalParams& p, int grid, hipStream_t s);
 hipError_t launch_fitness(int vtype, const FitParams& p, int64_t n, hipStream_t s);
 hipError_t launch_walk(int vtype, const WalkParams& p, int64_t n_children, hipStream_t s);

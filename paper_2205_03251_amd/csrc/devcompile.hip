@@ -613,7 +613,7 @@ int device_compile_population(Ctx* c, int vtype, int n_inputs, int64_t n_trees, 
 
     // the packed hand-off when every value it carries fits (see devcompile_core.h)
     const int64_t C = std::max<int64_t>(2, chunk_nodes);
-    const bool packed = C <= kDcPackMaxC && compile_stack_slots() <= 32;
+    const bool packed = C <= kDcPackMaxC && compile_stack_slots() <= kDcPackMaxS;
     DevBuf info, len, open, cnt, ncut, slot64, err, flags, big, counter;
     if (index_min_size > 0) RC(scratch_alloc(c, arena, big, (size_t)n));
     RC(scratch_alloc(c, arena, info, (size_t)n * 4));

@@ -31,10 +31,11 @@
 
 namespace gpe {
 
-// info word of a node: stack need (bits 0..5), roots a chunk (bit 6),
-// instruction form (bits 8..12: mode | first operand is the right << 3 |
+// info word of a node: stack need (bits 0..5), roots a chunk (bit 6), its code
+// reads LOADs (bit 7), instruction form (bits 8..12: mode | first operand is the right << 3 |
 // folded operand is the left << 4, as compile_tree's form)
 constexpr int32_t kDcCut = 64;
+constexpr int32_t kDcWaits = 128;
 
 struct DcNodes {
     const uint8_t* ops;
@@ -105,9 +106,10 @@ GPE_HD inline bool dc_foldable(const DcNodes& q, int64_t v)
 GPE_HD inline int dc_max(int a, int b) { return a > b ? a : b; }
 
 // An operand as its parent sees it: roots a chunk of its own (then it is one
-// LOAD word of one slot), or its stack need, code words and open nodes.
+// LOAD word of one slot), or its stack need, code words and open nodes, and
+// whether its code reads LOADs.
 struct DcKid {
-    bool cut;
+    bool cut, waits;
     int need;
     int32_t len;
     int32_t open;
@@ -115,20 +117,33 @@ struct DcKid {
 
 // The function at global index g of the tree starting at s, from its two
 // operands (compile_tree's rules): its stack need, instruction form, code
-// words and open nodes, whether it roots a chunk by size, and which operand
-// (0 none, 1 left, 2 right) it makes root a chunk because both need a full
-// stack.
+// words and open nodes, whether it roots a chunk by size, whether its code
+// reads LOADs, and which operands (1 left | 2 right) it makes root a chunk:
+// beside one that waits for LOADs (side_chunk_nodes), or because both need a
+// full stack.
 struct DcNode {
     int need, form;
     int32_t len;
     int64_t open;
-    bool cut;
-    int cut_kid;
+    bool cut, waits;
+    int cut_kids;
 };
 
 GPE_HD inline DcNode dc_combine(const DcNodes& q, int64_t g, int64_t s, int64_t l, int64_t r, DcKid L, DcKid R)
 {
     const bool fol = dc_foldable(q, l), fo_r = dc_foldable(q, r);
+    const int64_t G = side_chunk_nodes(q.C);
+    const bool wl = L.cut || L.waits, wr = R.cut || R.waits;
+    DcNode o;
+    o.cut_kids = 0;
+    if (wr && !L.cut && L.open >= G) {
+        L.cut = true;
+        o.cut_kids |= 1;
+    }
+    if (wl && !R.cut && R.open >= G) {
+        R.cut = true;
+        o.cut_kids |= 2;
+    }
     auto cost_l = [&]() { return L.cut ? 1 : L.need; };
     auto cost_r = [&]() { return R.cut ? 1 : R.need; };
     auto need_of = [&]() {
@@ -139,17 +154,15 @@ GPE_HD inline DcNode dc_combine(const DcNodes& q, int64_t g, int64_t s, int64_t 
         const int nl = cost_l(), nr = cost_r();
         return nl >= nr ? dc_max(nl, nr + 1) : dc_max(nr, nl + 1);
     };
-    DcNode o;
-    o.cut_kid = 0;
     o.need = need_of();
     if (o.need > q.S) {
         // both operands need a full stack: the bigger one roots a chunk of its own
         if (cost_l() >= cost_r()) {
             L.cut = true;
-            o.cut_kid = 1;
+            o.cut_kids |= 1;
         } else {
             R.cut = true;
-            o.cut_kid = 2;
+            o.cut_kids |= 2;
         }
         o.need = need_of();
     }
@@ -168,18 +181,20 @@ GPE_HD inline DcNode dc_combine(const DcNodes& q, int64_t g, int64_t s, int64_t 
     }
     o.open = 1 + (L.cut ? 1 : (int64_t)L.open) + (R.cut ? 1 : (int64_t)R.open);
     o.cut = o.open >= q.C && g != s;
+    o.waits = L.cut || R.cut || wl || wr;
     return o;
 }
 
 // The outcome of a finished function node: its info and code words for the
-// later passes; an operand cut by the stack rule in the per-node byte array
-// ncut (its own thread has finished it; only this parent decides that).
+// later passes; the operands it cuts in the per-node byte array ncut (their
+// own threads have finished them; only this parent decides that).
 template <class Mem>
 GPE_HD inline void dc_store(const DcNodes& q, int64_t g, int64_t s, int64_t l, int64_t r, const DcNode& o)
 {
     Mem::st(q.len + g, o.len);
-    Mem::st(q.info + g, o.need | (o.cut ? kDcCut : 0) | (o.form << 8));
-    if (o.cut_kid) q.ncut[o.cut_kid == 1 ? l : r] = 1;
+    Mem::st(q.info + g, o.need | (o.cut ? kDcCut : 0) | (o.waits ? kDcWaits : 0) | (o.form << 8));
+    if (o.cut_kids & 1) q.ncut[l] = 1;
+    if (o.cut_kids & 2) q.ncut[r] = 1;
     if (q.big) q.big[g] = s + q.endl[g] - g >= q.big_min ? 1 : 0;
 }
 
@@ -229,6 +244,7 @@ template <class Mem> GPE_HD inline int64_t dc_step(const DcNodes& q, int64_t s, 
         const int32_t i = Mem::ld(q.info + c);
         DcKid k;
         k.cut = (i & kDcCut) != 0;
+        k.waits = (i & kDcWaits) != 0;
         k.need = i & 63;
         k.len = Mem::ld(q.len + c);
         k.open = Mem::ld(q.open + c);
@@ -243,23 +259,26 @@ template <class Mem> GPE_HD inline int64_t dc_step(const DcNodes& q, int64_t s, 
 // ----- hand-off through one 64-bit word per function (chunk targets up to
 // kDcPackMaxC).  A node that does not root a chunk has fewer open nodes than
 // the target (else it would root one) and no more code words than open
-// nodes, so need - 1 (5 bits), words (13) and open nodes (14) fit in 32 bits;
+// nodes, so need - 1 (4 bits, for at most kDcPackMaxS stack slots), whether
+// its code reads LOADs (1), words (13) and open nodes (14) fit in 32 bits;
 // a chunk root is all ones.  Each operand ORs its word into its half of the
 // parent's slot (left operand low, right high); the second to arrive gets the
 // first's word back from the same atomic, so no other value crosses threads.
 constexpr int64_t kDcPackMaxC = 8192;
+constexpr int kDcPackMaxS = 16;
 constexpr uint32_t kDcPackCut = 0xffffffffu;
 
-GPE_HD inline uint32_t dc_pack(int need, int32_t len, int64_t open)
+GPE_HD inline uint32_t dc_pack(int need, bool waits, int32_t len, int64_t open)
 {
-    return (uint32_t)(need - 1) | ((uint32_t)len << 5) | ((uint32_t)open << 18);
+    return (uint32_t)(need - 1) | (waits ? 16u : 0u) | ((uint32_t)len << 5) | ((uint32_t)open << 18);
 }
 
 GPE_HD inline DcKid dc_unpack(uint32_t w)
 {
     DcKid k;
     k.cut = w == kDcPackCut;
-    k.need = (int)(w & 31) + 1;
+    k.waits = (w & 16) != 0;
+    k.need = (int)(w & 15) + 1;
     k.len = (int32_t)((w >> 5) & 8191);
     k.open = (int32_t)(w >> 18);
     return k;
@@ -271,7 +290,7 @@ template <class Mem> GPE_HD inline uint32_t dc_leaf_packed(const DcNodes& q, int
     Mem::st(q.info + g, 1);
     Mem::st(q.len + g, 1);
     if (q.big) q.big[g] = 0;
-    return dc_pack(1, 1, 1);
+    return dc_pack(1, false, 1, 1);
 }
 
 // One arrival of node v (word w) at its parent; returns the parent (and its
@@ -297,7 +316,7 @@ GPE_HD inline int64_t dc_step_packed(const DcNodes& q, int64_t s, int64_t e, int
     }
     const DcNode o = dc_combine(q, pg, s, l, r, dc_unpack(left ? *w : other), dc_unpack(left ? other : *w));
     dc_store<Mem>(q, pg, s, l, r, o);
-    *w = o.cut ? kDcPackCut : dc_pack(o.need, o.len, o.open);
+    *w = o.cut ? kDcPackCut : dc_pack(o.need, o.waits, o.len, o.open);
     return pg;
 }
 

@@ -1017,8 +1017,7 @@ def write_if_changed(path: str, text: str) -> None:
 
 def main(out_path: str) -> None:
     head = "// Generated by gen_dispatch.py; do not edit.\n#pragma once\n"
-    write_if_changed(out_path, head + "".join(f"constexpr int kF32Rows{K} = {n};\n" for K, n in ROWS.items())
-                     + "".join(gen_one(K, S, form) for K, S, form in VARIANTS))
+    write_if_changed(out_path, head + "".join(gen_one(K, S, form) for K, S, form in VARIANTS))
     write_if_changed(os.path.join(os.path.dirname(out_path), "dispatch_bool.inc"),
                      head + f"constexpr int kBoolDispatchInputs = {BOOL_NI};\n"
                      + "".join(gen_bool(K, S) for K, S in BOOL_VARIANTS) + gen_bool_word())

@@ -115,6 +115,38 @@ __device__ __forceinline__ ChunkHdr load_chunk(const GP_CONST DevChunk* c)
     return h;
 }
 
+// The next work item of this wave; false when none is left.  The items are
+// dealt out by p.n_cursors counters, counter c handing out items c, c + n, ...
+// in order; a wave goes round the counters, so they advance together and the
+// items still leave in their priority order but for a few places.  One counter
+// for the launch hands out an item every 9.5 ns at best (one address, all
+// XCDs): 6144 waves took 58 us to get their first item, and launches of small
+// chunks ran at that rate whatever their width (480 000 chunks of 768 nodes
+// with side chunks: 7.9 ms; 6.0 with four).  With a counter per wave group the
+// groups drift apart and long chains start late (5.6 -> 6.3 ms with 16 on the
+// large-tree population).
+__device__ __forceinline__ bool next_item(const EvalParams& p, int lane, uint32_t& turn, int64_t& it)
+{
+    const uint32_t n = (uint32_t)p.n_cursors;              // a power of two
+    for (;;) {
+        const uint32_t c = turn++ & (n - 1);
+        unsigned int k = 0;
+        if (lane == 0)
+            k = __hip_atomic_fetch_add(p.cursor + c * kCursorStride, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        k = __builtin_amdgcn_readfirstlane(k);
+        it = (int64_t)k * n + c;
+        if (it < p.n_items) return true;
+        // that counter is used up: go to the next one that is not (lane l
+        // reads counter l mod n, without a divergent branch), or end
+        const uint32_t own = (uint32_t)lane & (n - 1);
+        const unsigned int u = __hip_atomic_load(p.cursor + own * kCursorStride, __ATOMIC_RELAXED,
+                                                 __HIP_MEMORY_SCOPE_AGENT);
+        const uint64_t mask = __ballot((int64_t)u * n + own < p.n_items) >> (turn & (n - 1));
+        if (mask == 0) return false;                       // the mask repeats every n lanes, n <= 16
+        turn += (uint32_t)__ffsll((unsigned long long)mask) - 1u;
+    }
+}
+
 // --------------------------------------------------- float interpreter
 struct ItemF32 {
     const float* inputs;     // input 0 at this lane's first case
@@ -219,11 +251,9 @@ __global__ __launch_bounds__(64) void k_eval_f32(EvalParams p)
     const int lane = threadIdx.x;
     float st[S][K];
     float x[K];
-    for (;;) {
-        unsigned int it = 0;
-        if (lane == 0) it = atomicAdd(p.cursor, 1u);
-        it = __builtin_amdgcn_readfirstlane(it);
-        if ((int64_t)it >= p.n_items) break;
+    uint32_t turn = blockIdx.x;
+    for (int64_t it;;) {
+        if (!next_item(p, lane, turn, it)) break;
         const int64_t item = cst(p.items)[it];
         int32_t c = (int32_t)(item >> 16);
         const int32_t s = (int32_t)(item & 0xffff);
@@ -303,11 +333,9 @@ __global__ __launch_bounds__(64) void k_eval_f32_tbl(EvalParams p)
     const int lane = threadIdx.x;
     const uint32_t voff = (uint32_t)lane * 4u;
     const uint32_t strideb = (uint32_t)(p.stride * 4);
-    for (;;) {
-        unsigned int it = 0;
-        if (lane == 0) it = atomicAdd(p.cursor, 1u);
-        it = __builtin_amdgcn_readfirstlane(it);
-        if ((int64_t)it >= p.n_items) break;
+    uint32_t turn = blockIdx.x;
+    for (int64_t it;;) {
+        if (!next_item(p, lane, turn, it)) break;
         const int64_t item = cst(p.items)[it];
         int32_t c = (int32_t)(item >> 16);
         const int32_t s = (int32_t)(item & 0xffff);
@@ -430,11 +458,9 @@ __global__ __launch_bounds__(64) void k_eval_bool(EvalParams p)
     const int lane = threadIdx.x;
     uint64_t st[S][K];
     const int32_t row = kWave * K;
-    for (;;) {
-        unsigned int it = 0;
-        if (lane == 0) it = atomicAdd(p.cursor, 1u);
-        it = __builtin_amdgcn_readfirstlane(it);
-        if ((int64_t)it >= p.n_items) break;
+    uint32_t turn = blockIdx.x;
+    for (int64_t it;;) {
+        if (!next_item(p, lane, turn, it)) break;
         const int64_t item = cst(p.items)[it];
         int32_t c = (int32_t)(item >> 16);
         const int32_t s = (int32_t)(item & 0xffff);
@@ -503,11 +529,9 @@ __global__ __launch_bounds__(64) void k_eval_bool_tbl(EvalParams p)
     const uint32_t voff = (uint32_t)lane * 8u;
     const uint32_t strideb = (uint32_t)(p.stride * 8);
     const uint32_t nin = (uint32_t)p.n_inputs;
-    for (;;) {
-        unsigned int it = 0;
-        if (lane == 0) it = atomicAdd(p.cursor, 1u);
-        it = __builtin_amdgcn_readfirstlane(it);
-        if ((int64_t)it >= p.n_items) break;
+    uint32_t turn = blockIdx.x;
+    for (int64_t it;;) {
+        if (!next_item(p, lane, turn, it)) break;
         const int64_t item = cst(p.items)[it];
         int32_t c = (int32_t)(item >> 16);
         const int32_t s = (int32_t)(item & 0xffff);
@@ -545,11 +569,11 @@ __global__ __launch_bounds__(64) void k_eval_bool_tbl(EvalParams p)
 
 // ------------------------------------------------------------- init
 __global__ void k_init(int32_t* pending, const int32_t* init, int64_t n, unsigned int* cursor,
-                       int n_cursors)
+                       int64_t n_cursors)
 {
     const int64_t i0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     for (int64_t i = i0; i < n; i += (int64_t)gridDim.x * blockDim.x) pending[i] = init[i];
-    if (i0 < n_cursors) cursor[i0] = 0u;
+    for (int64_t i = i0; i < n_cursors; i += (int64_t)gridDim.x * blockDim.x) cursor[i * kCursorStride] = 0u;
 }
 
 // ---------------------------------------------------------- fitness
@@ -818,14 +842,14 @@ static Variant g_variants[] = {
     {"f32_k8_s10", 0, 8, 10, (const void*)k_eval_f32<8, 10>, 0},
     {"f32t_k4_s10", 0, 4, 10, (const void*)k_eval_f32_tbl<4, 10, Form::Table>, 0, 1, 0},
     {"f32t_k8_s10", 0, 8, 10, (const void*)k_eval_f32_tbl<8, 10, Form::Table>, 0, 1, 0},
-    {"f32d_k4_s10", 0, 4, 10, (const void*)k_eval_f32_tbl<4, 10, Form::Direct>, 0, 1, 0},
-    {"f32d_k8_s10", 0, 8, 10, (const void*)k_eval_f32_tbl<8, 10, Form::Direct>, 0, 1, 0},
-    {"f32d_k1_s10", 0, 1, 10, (const void*)k_eval_f32_tbl<1, 10, Form::Direct>, 0, 1, 0},
-    {"f32d_k2_s10", 0, 2, 10, (const void*)k_eval_f32_tbl<2, 10, Form::Direct>, 0, 1, 0},
-    {"f32r_k1_s10", 0, 1, 10, (const void*)k_eval_f32_tbl<1, 10, Form::Rows>, 0, 1, 0, 0, kF32Rows1},
-    {"f32r_k2_s10", 0, 2, 10, (const void*)k_eval_f32_tbl<2, 10, Form::Rows>, 0, 1, 0, 0, kF32Rows2},
-    {"f32r_k4_s10", 0, 4, 10, (const void*)k_eval_f32_tbl<4, 10, Form::Rows>, 0, 1, 0, 0, kF32Rows4},
-    {"f32r_k8_s10", 0, 8, 10, (const void*)k_eval_f32_tbl<8, 10, Form::Rows>, 0, 1, 0, 0, kF32Rows8},
+    {"f32d_k4_s10", 0, 4, 10, (const void*)k_eval_f32_tbl<4, 10, Form::Direct>, 0, 1, 0, 0, 1},
+    {"f32d_k8_s10", 0, 8, 10, (const void*)k_eval_f32_tbl<8, 10, Form::Direct>, 0, 1, 0, 0, 1},
+    {"f32d_k1_s10", 0, 1, 10, (const void*)k_eval_f32_tbl<1, 10, Form::Direct>, 0, 1, 0, 0, 1},
+    {"f32d_k2_s10", 0, 2, 10, (const void*)k_eval_f32_tbl<2, 10, Form::Direct>, 0, 1, 0, 0, 1},
+    {"f32r_k1_s10", 0, 1, 10, (const void*)k_eval_f32_tbl<1, 10, Form::Rows>, 0, 1, 0, 0, 2},
+    {"f32r_k2_s10", 0, 2, 10, (const void*)k_eval_f32_tbl<2, 10, Form::Rows>, 0, 1, 0, 0, 2},
+    {"f32r_k4_s10", 0, 4, 10, (const void*)k_eval_f32_tbl<4, 10, Form::Rows>, 0, 1, 0, 0, 2},
+    {"f32r_k8_s10", 0, 8, 10, (const void*)k_eval_f32_tbl<8, 10, Form::Rows>, 0, 1, 0, 0, 2},
     {"bool_k1_s16", 1, 1, 16, (const void*)k_eval_bool<1, 16>, 0},
     {"bool_k2_s16", 1, 2, 16, (const void*)k_eval_bool<2, 16>, 0},
     {"bool_k1_s10", 1, 1, 10, (const void*)k_eval_bool<1, 10>, 0},
@@ -846,7 +870,7 @@ hipError_t launch_eval(int variant, const EvalParams& p, int grid, hipStream_t s
 }
 
 hipError_t launch_init(int32_t* pending, const int32_t* init, int64_t n, unsigned int* cursor,
-                       int n_cursors, hipStream_t s)
+                       int64_t n_cursors, hipStream_t s)
 {
     int64_t need = std::max<int64_t>(n, n_cursors);
     int grid = (int)std::min<int64_t>(4096, std::max<int64_t>(1, (need + 255) / 256));

@@ -20,14 +20,15 @@ inline bool is_func(uint8_t b) { return (b & kFuncBit) != 0; }
 // subtree emits in its own chunk, the nodes not yet assigned to a chunk below
 // it (during emission: where its code starts, -1 when folded into its
 // parent), its stack need, whether it roots a chunk, its instruction form
-// (mode | first operand is the right << 3 | folded operand is the left << 4)
-// and, during emission, the stack slot of its value.
+// (mode | first operand is the right << 3 | folded operand is the left << 4 |
+// kWaits) and, during emission, the stack slot of its value.
 struct NodeRec {
     int32_t end;
     int32_t len;
     int32_t open;
     uint8_t need, cut, form, slot;
 };
+constexpr uint8_t kWaits = 32;          // in form: its code reads LOADs
 static_assert(sizeof(NodeRec) == 16, "one node record is 16 bytes");
 
 // Per-node work arrays of compile_tree, grown to the largest tree seen.
@@ -193,6 +194,7 @@ bool compile_tree(const uint8_t* ops, int64_t n, const CompileOptions& opt, cons
     NodeRec* nd = ws.node.get();
     const bool index = opt.index_min_size > 0;
     out->big_ends.clear();
+    const int64_t G = side_chunk_nodes(C);
     auto words = [&](int64_t c) -> int32_t { return nd[c].cut ? 1 : nd[c].len; };   // LOAD or the code
     std::vector<int64_t> roots;                 // the cut nodes
 
@@ -204,6 +206,7 @@ bool compile_tree(const uint8_t* ops, int64_t n, const CompileOptions& opt, cons
         x.end = (int32_t)(i + 1);
         x.cut = opaque(i) ? 1 : 0;            // a compiled chunk: one LOAD
         x.need = 1;
+        x.form = 0;
         x.open = 1;
         x.len = 1;                            // PUSH, when not folded into its parent
     };
@@ -216,6 +219,16 @@ bool compile_tree(const uint8_t* ops, int64_t n, const CompileOptions& opt, cons
             bigs.push_back({(int32_t)full(i), (int32_t)full(x.end)});
         x.cut = 0;
         const bool fol = foldable(l), fo_r = foldable(r);
+        // an operand beside one that waits for LOADs (see side_chunk_nodes)
+        const bool wl = L.cut || (L.form & kWaits), wr = R.cut || (R.form & kWaits);
+        if (wr && !L.cut && L.open >= G) {
+            L.cut = 1;
+            cuts.push_back(l);
+        }
+        if (wl && !R.cut && R.open >= G) {
+            R.cut = 1;
+            cuts.push_back(r);
+        }
         auto cost = [](const NodeRec& c) { return c.cut ? 1 : (int)c.need; };
         auto need_of = [&]() {
             bool fl = !L.cut && fol, fr = !R.cut && fo_r;
@@ -248,6 +261,7 @@ bool compile_tree(const uint8_t* ops, int64_t n, const CompileOptions& opt, cons
             x.form = (uint8_t)((!first_r || boolean ? M_SS : M_RS) | (first_r ? 8 : 0));
             x.len = words(l) + words(r) + 1;
         }
+        if (L.cut || R.cut || wl || wr) x.form |= kWaits;
         int64_t o = 1 + (L.cut ? 1 : L.open) + (R.cut ? 1 : R.open);
         x.open = (int32_t)std::min<int64_t>(o, INT32_MAX);
         if ((o >= C || forced(i)) && i != 0) {

@@ -50,6 +50,20 @@ constexpr int kMaxStackSlots = 32;
 // compiled as a chunk of its own (see compose_child).
 constexpr int64_t kPathSiblingChunk = 64;
 
+// A subtree of at least this many nodes beside an operand that waits for a
+// chunk below (it reads LOADs) roots a chunk of its own, for chunk target C.
+// A chunk runs only once its inputs are done, so whatever shares a chunk with
+// a LOAD waits for it; moved out, it runs beside the chunk waited for, and
+// the chain of dependent chunks up a tree holds the path and small pieces
+// only.  Longest chain of a random 10^6-node tree (1.6 us a chunk, 46 ns a
+// word): 1024-node chunks 2253 -> 439 us, 4096-node chunks 5.2 -> 0.73 ms.
+// Smaller pieces shorten the chains further but add chunks: 32 nodes is where
+// a piece takes as long as its hand-off, C / 32 keeps the number of chunks
+// (one per 270 nodes at C = 1024, one per 1100 at 4096) falling with C, so
+// that the choice of C still trades chain length against chunk count.
+constexpr int64_t kSideChunkMin = 32;
+constexpr int64_t side_chunk_nodes(int64_t C) { return C / 32 > kSideChunkMin ? C / 32 : kSideChunkMin; }
+
 inline uint32_t ins_word(uint32_t f, uint32_t mode, uint32_t d, uint32_t payload)
 {
     return f | (mode << 2) | (d << 5) | (payload << kPayloadShift);

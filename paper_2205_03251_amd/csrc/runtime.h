@@ -88,7 +88,7 @@ struct Plan {
     DevBuf items;                // int64 work items
     DevBuf pending_init;         // int32 [n_chunks * n_slices]
     DevBuf pending;
-    DevBuf cursor;               // one per tree in per-tree mode
+    DevBuf cursor;               // kCursors counters per launch (per tree in per-tree mode)
     std::vector<int64_t> tree_item_begin, tree_item_count;
     hipGraphExec_t graph = nullptr;
     gp_handle graph_cases = 0;

@@ -128,9 +128,17 @@ int64_t auto_chunk_nodes(int vtype, int64_t total_nodes, int64_t n_trees, int64_
     (void)n_trees;
     (void)T;
     // Small chunks keep the chain of dependent chunks in the largest trees
-    // short; very small ones spend more on chunk hand-off than on work.
-    if (total_nodes < 200000) return 256;
-    return 1024;
+    // short, larger ones cost fewer hand-offs: the more nodes there are, the
+    // more the hand-offs count.  Measured (float, K = 4 or 8, with the side
+    // chunks of side_chunk_nodes): 1.4e5 nodes on 1024 cases 84, 106, 119 us
+    // at 512, 1024, 2048; 4e6 nodes 0.74, 0.61, 0.69 ms; 4e7 nodes on 256
+    // cases 1.08, 0.87, 0.87 ms; 6e7 nodes 1.95, 1.89, 1.82 ms at 1024, 2048,
+    // 4096; 2e8 nodes 6.1, 5.9, 5.6, 5.5 ms at 1024 ... 8192.
+    if (total_nodes < 500000) return 512;
+    if (total_nodes < 15000000) return 1024;
+    if (total_nodes < 50000000) return 2048;
+    if (total_nodes < 1000000000) return 4096;
+    return 8192;
 }
 
 static int64_t elems_of(int vtype, int64_t T) { return vtype == GP_BOOL ? (T + 63) / 64 : T; }
@@ -159,13 +167,22 @@ static int default_variant(int vtype, const CaseSet* cs, const Pop* p, int force
     };
     if (ok(forced)) return forced;
     int wantK = 1;
-    if (vtype == GP_F32) wantK = cs->n_elems <= 64 ? 1 : cs->n_elems <= 128 ? 2 : 4;
-    else wantK = cs->n_elems <= 64 ? 1 : 2;
-    // prefer a table-dispatch interpreter when one fits, the kind that holds input rows in registers for
-    // populations of several inputs (for one input its registers would only cost resident waves)
-    for (int kind : {vtype == GP_F32 && p->n_inputs > 1 ? 1 : 0, 0})
+    if (vtype == GP_F32) {
+        wantK = cs->n_elems <= 64 ? 1 : cs->n_elems <= 128 ? 2 : 4;
+        // eight cases per lane halve the dispatch work per case and leave half as many slices to run side by side:
+        // better once there is work for every wave, unless they pad the cases much further.  Nodes x slices of 512:
+        // 8.6e6 0.61 ms with 4, 0.67 with 8; 1.9e7 (three inputs) 0.85 and 0.73; 1.3e8 2.54 and 1.82 ms.
+        const int64_t s8 = (cs->n_elems + 511) / 512, s4 = (cs->n_elems + 255) / 256;
+        if (cs->n_elems > 256 && p->total_nodes * s8 >= 15000000 && s8 * 2 * 8 <= s4 * 9) wantK = 8;
+    } else {
+        wantK = cs->n_elems <= 64 ? 1 : 2;
+    }
+    // prefer a table-dispatch interpreter when one fits: the kind that holds input rows in registers for
+    // populations of several inputs (for one input its registers would only cost resident waves), else the one
+    // that dispatches directly (2e8 nodes at K = 8 5.59 against 5.80 ms through the branch table)
+    for (int kind : {vtype == GP_F32 && p->n_inputs > 1 ? 2 : 1, 1, 0})
         for (int v = 0; v < variant_count(); ++v)
-            if (ok(v) && vt[v].K == wantK && vt[v].table && (vt[v].rows > 0) == (kind == 1)) return v;
+            if (ok(v) && vt[v].K == wantK && vt[v].table && (vtype == GP_BOOL || vt[v].kind == kind)) return v;
     for (int v = 0; v < variant_count(); ++v)
         if (ok(v) && vt[v].K == wantK) return v;
     for (int v = 0; v < variant_count(); ++v)
@@ -601,7 +618,7 @@ static int make_plan(Ctx* c, Pop* p, const CaseSet* cs, Launch L, bool per_tree,
     RC(upload(c, pl->items, items.data(), items.size() * sizeof(int64_t), stream));
     RC(upload(c, pl->pending_init, pend.data(), pend.size() * sizeof(int32_t), stream));
     RC(dev_alloc(c, pl->pending, pend.size() * sizeof(int32_t)));
-    RC(dev_alloc(c, pl->cursor, (size_t)(per_tree ? p->n_trees : 1) * sizeof(unsigned int)));
+    RC(dev_alloc(c, pl->cursor, (size_t)(per_tree ? p->n_trees : 1) * kCursors * kCursorStride * sizeof(unsigned int)));
     pl->grid = (int)std::max<int64_t>(1, std::min<int64_t>(resident_grid(c, v, pl->waves_per_cu), pl->n_items));
     HIPC(c, hipStreamSynchronize(stream));
     p->plans[key] = std::move(pl);
@@ -625,6 +642,11 @@ static EvalParams eval_params(Pop* p, const CaseSet* cs, Plan* pl)
     e.stride = cs->stride;
     e.n_slices = pl->n_slices;
     e.n_inputs = cs->n_inputs;
+    // Boolean items are short (a chunk of 256 words takes about 10 us), so their counters are asked more often:
+    // 400 trees on 4096 cases 0.32 ms with 4, 0.25 with 16; float launches keep their order better with 4
+    // (1000 large trees 5.57 ms, 5.87 with 16)
+    e.n_cursors = p->vtype == GP_BOOL ? 16 : 4;
+    static_assert(kCursors == 16, "counters allocated per launch");
     return e;
 }
 
@@ -648,7 +670,7 @@ static int enqueue_body(Ctx* c, Pop* p, const CaseSet* cs, Plan* pl, hipStream_t
 {
     const int64_t n_pend = p->n_chunks * pl->n_slices;
     HIPC(c, launch_init(pl->pending.as<int32_t>(), pl->pending_init.as<int32_t>(), n_pend,
-                        pl->cursor.as<unsigned int>(), pl->per_tree ? (int)p->n_trees : 1, s));
+                        pl->cursor.as<unsigned int>(), (pl->per_tree ? p->n_trees : 1) * kCursors, s));
     EvalParams e = eval_params(p, cs, pl);
     int64_t nl = 1;
     if (time_kernel) HIPC(c, hipEventRecord(c->kev0, s));
@@ -661,7 +683,7 @@ static int enqueue_body(Ctx* c, Pop* p, const CaseSet* cs, Plan* pl, hipStream_t
             EvalParams et = e;
             et.items = e.items + pl->tree_item_begin[t];
             et.n_items = pl->tree_item_count[t];
-            et.cursor = e.cursor + t;
+            et.cursor = e.cursor + t * kCursors * kCursorStride;
             const int grid = (int)std::max<int64_t>(1, std::min<int64_t>(full, et.n_items));
             HIPC(c, launch_eval(pl->variant, et, grid, s));
             ++nl;
@@ -761,7 +783,7 @@ int enqueue_promoted(Ctx* c, Pop* p, const Pop* src, gp_handle cases_h, const Ca
         RC(upload(c, pl.items, items.data(), items.size() * sizeof(int64_t), s));
         RC(upload(c, pl.pending_init, pend.data(), pend.size() * sizeof(int32_t), s));
         RC(dev_alloc(c, pl.pending, pend.size() * sizeof(int32_t)));
-        RC(dev_alloc(c, pl.cursor, sizeof(unsigned int)));
+        RC(dev_alloc(c, pl.cursor, kCursors * kCursorStride * sizeof(unsigned int)));
         pl.grid = (int)std::max<int64_t>(1, std::min<int64_t>(resident_grid(c, v, pl.waves_per_cu), pl.n_items));
         RC(enqueue_body(c, p, cs, &pl, s, nullptr, false));
     } else {
@@ -2461,11 +2483,11 @@ int gp_autotune(gp_ctx* ctx, gp_handle pop, gp_handle cases, int* best_variant, 
     std::vector<int64_t> chunk_sizes{p->chunk_nodes};
     if (p->auto_chunk && !p->host_ops.empty()) {
         const int64_t mean = p->total_nodes / std::max<int64_t>(1, p->n_trees);
-        // large populations of large trees keep large chunks; mid-size ones (10^8..10^9 nodes) are bound by
-        // chains of chunk hand-offs and do best at 512..1024-node chunks; small ones, down to 128
-        std::vector<int64_t> cand = p->total_nodes > 1000000000  ? std::vector<int64_t>{1024, 2048, 4096, 8192}
-                                    : p->total_nodes > 200000000 ? std::vector<int64_t>{512, 768, 1024, 2048}
-                                                                 : std::vector<int64_t>{128, 192, 256, 512, 1024, 2048, 4096};
+        // large populations do best at large chunks (see auto_chunk_nodes); small ones are bound by chains of
+        // chunk hand-offs, down to 128 nodes
+        std::vector<int64_t> cand = p->total_nodes > 200000000
+                                        ? std::vector<int64_t>{1024, 2048, 4096, 8192}
+                                        : std::vector<int64_t>{128, 192, 256, 512, 1024, 2048, 4096};
         chunk_sizes.clear();
         for (int64_t c : cand)
             if (c <= std::max<int64_t>(256, 4 * mean)) chunk_sizes.push_back(c);
@@ -2511,7 +2533,7 @@ int gp_autotune(gp_ctx* ctx, gp_handle pop, gp_handle cases, int* best_variant, 
             if (!variant_fits(vt, qp->vtype, qp->max_stack, qp->n_inputs, cs->n_elems, cs->stride,
                               qp->vtype == GP_BOOL ? 8 : 4))
                 continue;
-            if (vt.rows > 0 && qp->n_inputs == 1) continue;     // registers for rows that are never read
+            if (vt.kind == 2 && qp->n_inputs == 1) continue;     // registers for rows that are never read
             float t = 0.f;
             RC(time_variant(qp, Launch{v, 0}, &t));
             full.emplace_back(t, v);
