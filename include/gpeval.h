@@ -127,7 +127,10 @@ int gp_create(int device, uint64_t hbm_budget_bytes, void* hip_stream, gp_ctx** 
 void gp_destroy(gp_ctx* ctx);
 /* Reason for the last failed call on this context (static text if ctx is NULL). */
 const char* gp_last_error(const gp_ctx* ctx);
-/* Device memory currently held by the context, in bytes. */
+/* Device memory currently held by the context's populations, cases and calls,
+ * in bytes.  Freed blocks of at most 1/16 of the budget and 8 GiB in all are
+ * kept for the next calls and not counted; they are given back when the budget
+ * or the device runs short, by gp_server_start and by gp_destroy. */
 uint64_t gp_memory_used(const gp_ctx* ctx);
 
 /* ------------------------------------------------------------------- data */

@@ -31,7 +31,9 @@ struct DevBuf {
     Ctx* ctx = nullptr;
     void* p = nullptr;
     size_t bytes = 0;
+    size_t block = 0;            // size of the block behind it (a reused one may be larger)
     bool borrowed = false;       // memory of a DevArena: not freed by release()
+    bool pooled = false;         // allocated inside a PoolScope: may go back to the context's pool
     DevBuf() = default;
     DevBuf(const DevBuf&) = delete;
     DevBuf& operator=(const DevBuf&) = delete;
@@ -42,7 +44,9 @@ struct DevBuf {
         std::swap(ctx, o.ctx);
         std::swap(p, o.p);
         std::swap(bytes, o.bytes);
+        std::swap(block, o.block);
         std::swap(borrowed, o.borrowed);
+        std::swap(pooled, o.pooled);
     }
     template <class T> T* as() const { return (T*)p; }
 };
@@ -55,6 +59,25 @@ struct DevArena {
     DevBuf buf;
     size_t used = 0;             // bytes handed out since the last reset
     size_t high = 0;             // most ever asked for between two resets
+};
+
+// Device blocks a context keeps for its next calls instead of freeing them: an
+// index or a load otherwise spends more time in hipMalloc and hipFree (which
+// waits for the device) than in its kernels.  Calls with host time, before and
+// after: the index of 2.15e8 nodes 24.3 -> 2.2 ms, load, evaluation and release
+// of 4.3e7 nodes 34.2 -> 28.5 ms, two generations of 200 trees 14.5 -> 11.6 ms.
+// Used only by the
+// thread that holds Ctx::mu inside a PoolScope, whose work all goes to the
+// context stream: a block handed out again is overwritten after everything
+// that used it before.  Holds at most `limit` bytes; trimmed when the budget
+// or the device runs short, when a server starts, and by gp_destroy.
+struct DevPool {
+    std::multimap<size_t, void*> blocks;     // by size
+    size_t bytes = 0;
+    size_t limit = 0;
+    void* take(size_t need, size_t* got);
+    bool give(void* p, size_t n);
+    void trim();
 };
 
 struct CaseSet {
@@ -228,6 +251,17 @@ struct Ctx {
     // pinned host memory that results for the host are packed into (used by
     // the thread that holds mu; allocated on first use, kept to gp_destroy)
     uint8_t* stage = nullptr;
+    DevPool pool;
+};
+
+// Allocations and releases of this thread on c use the pool while it lives (c's
+// lock held; not while a server runs, whose threads allocate for themselves).
+struct PoolScope {
+    explicit PoolScope(Ctx* c);
+    ~PoolScope();
+    PoolScope(const PoolScope&) = delete;
+    PoolScope& operator=(const PoolScope&) = delete;
+    Ctx* before;
 };
 constexpr size_t kStageBytes = size_t(4) << 20;
 
@@ -331,6 +365,8 @@ Launch choose_launch(Ctx* c, int vtype, const CaseSet* cs, const Pop* p);
 // Workgroups of one launch of variant v: the resident ones, at most
 // waves_per_cu per compute unit when that is positive.
 int64_t resident_grid(const Ctx* c, const Variant& v, int waves_per_cu);
+// The interpreter for p on cs: the forced one if it fits, else the default.
+int default_variant(int vtype, const CaseSet* cs, const Pop* p, int forced);
 int64_t auto_chunk_nodes(int vtype, int64_t total_nodes, int64_t n_trees, int64_t T);
 int compile_stack_slots();
 

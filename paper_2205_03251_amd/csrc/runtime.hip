@@ -44,17 +44,50 @@ int hip_check(Ctx* c, hipError_t e, const char* what)
     } while (0)
 
 // ------------------------------------------------------------ memory
+static thread_local Ctx* t_pool = nullptr;     // the context whose PoolScope this thread is in
+
+PoolScope::PoolScope(Ctx* c) : before(t_pool) { t_pool = c->server ? nullptr : c; }
+PoolScope::~PoolScope() { t_pool = before; }
+
+// The smallest kept block that holds `need` without wasting more than an eighth (and 64 KiB).
+void* DevPool::take(size_t need, size_t* got)
+{
+    auto it = blocks.lower_bound(need);
+    if (it == blocks.end() || it->first > need + need / 8 + 65536) return nullptr;
+    void* p = it->second;
+    *got = it->first;
+    bytes -= it->first;
+    blocks.erase(it);
+    return p;
+}
+
+bool DevPool::give(void* p, size_t n)
+{
+    if (n > limit || bytes > limit - n) return false;
+    blocks.emplace(n, p);
+    bytes += n;
+    return true;
+}
+
+void DevPool::trim()
+{
+    for (auto& b : blocks) (void)hipFree(b.second);
+    blocks.clear();
+    bytes = 0;
+}
+
 DevBuf::~DevBuf() { release(); }
 
 void DevBuf::release()
 {
     if (p && !borrowed) {
-        (void)hipFree(p);
+        if (!(pooled && ctx && t_pool == ctx && ctx->pool.give(p, block))) (void)hipFree(p);
         if (ctx) ctx->used -= bytes;
     }
     p = nullptr;
     bytes = 0;
     borrowed = false;
+    pooled = false;
 }
 
 int scratch_alloc(Ctx* c, DevArena* a, DevBuf& b, size_t bytes)
@@ -87,19 +120,34 @@ int dev_alloc(Ctx* c, DevBuf& b, size_t bytes)
     b.release();
     if (bytes == 0) bytes = 256;
     bytes = (bytes + 255) & ~(size_t)255;
-    if (c->used + bytes > c->budget)
+    const bool pooled = t_pool == c;
+    void* p = nullptr;
+    size_t block = bytes;
+    if (pooled) {
+        if (c->used + bytes <= c->budget) p = c->pool.take(bytes, &block);
+        if (!p && c->used + bytes + c->pool.bytes > c->budget) c->pool.trim();
+    }
+    if (!p && c->used + bytes > c->budget)
         return set_err(c, GP_EBUDGET,
                        "device memory budget exceeded: need " + std::to_string(bytes) + " more bytes, " +
                            std::to_string(c->budget - std::min<uint64_t>(c->budget, c->used)) + " left");
-    void* p = nullptr;
-    hipError_t e = hipMalloc(&p, bytes);
-    if (e != hipSuccess) {
-        (void)hipGetLastError();
-        return set_err(c, GP_ENOMEM, std::string("hipMalloc failed: ") + hipGetErrorString(e));
+    if (!p) {
+        hipError_t e = hipMalloc(&p, bytes);
+        if (e != hipSuccess && pooled && c->pool.bytes > 0) {
+            (void)hipGetLastError();
+            c->pool.trim();
+            e = hipMalloc(&p, bytes);
+        }
+        if (e != hipSuccess) {
+            (void)hipGetLastError();
+            return set_err(c, GP_ENOMEM, std::string("hipMalloc failed: ") + hipGetErrorString(e));
+        }
     }
     b.ctx = c;
     b.p = p;
     b.bytes = bytes;
+    b.block = block;
+    b.pooled = pooled;
     c->used += bytes;
     return GP_OK;
 }
@@ -157,7 +205,7 @@ static TuneKey tune_key(int vtype, const CaseSet* cs, const Pop* p)
     return TuneKey{vtype, ilog2_ceil(cs->T), ilog2_ceil(std::max<int64_t>(1, p->total_nodes / std::max<int64_t>(1, p->n_trees)))};
 }
 
-static int default_variant(int vtype, const CaseSet* cs, const Pop* p, int forced)
+int default_variant(int vtype, const CaseSet* cs, const Pop* p, int forced)
 {
     Variant* vt = variant_table();
     auto ok = [&](int v) {
@@ -1195,6 +1243,7 @@ int gp_create(int device, uint64_t hbm_budget_bytes, void* hip_stream, gp_ctx** 
     size_t free_b = 0, total_b = 0;
     if ((e = hipMemGetInfo(&free_b, &total_b)) != hipSuccess) return fail(e, "hipMemGetInfo");
     c->budget = hbm_budget_bytes ? hbm_budget_bytes : (uint64_t)(0.9 * (double)free_b);
+    c->pool.limit = (size_t)std::min<uint64_t>(uint64_t(8) << 30, c->budget / 16);
     if (hip_stream) {
         c->stream = (hipStream_t)hip_stream;
         c->own_stream = false;
@@ -1233,6 +1282,7 @@ void gp_destroy(gp_ctx* ctx)
     (void)hipStreamSynchronize(ctx->stream);
     ctx->pops.clear();
     ctx->cases.clear();
+    ctx->pool.trim();
     if (ctx->stage) (void)hipHostFree(ctx->stage);
     if (ctx->ev0) (void)hipEventDestroy(ctx->ev0);
     if (ctx->ev1) (void)hipEventDestroy(ctx->ev1);
@@ -1255,6 +1305,7 @@ int gp_set_cases(gp_ctx* ctx, int vtype, int n_inputs, int64_t n_cases, const vo
 {
     if (!ctx || !cases_out) return GP_EINVAL;
     std::lock_guard<std::mutex> lk(ctx->mu);
+    PoolScope pool(ctx);
     HIPC(ctx, hipSetDevice(ctx->device));
     if (vtype != GP_F32 && vtype != GP_BOOL) return set_err(ctx, GP_EINVAL, "unknown value type");
     if (n_inputs < 1 || n_inputs > kMaxInputs) return set_err(ctx, GP_EINVAL, "n_inputs must be 1..64");
@@ -1316,6 +1367,7 @@ int gp_load_population(gp_ctx* ctx, int vtype, int layout, int n_inputs, int64_t
 {
     if (!ctx || !pop_out) return GP_EINVAL;
     std::lock_guard<std::mutex> lk(ctx->mu);
+    PoolScope pool(ctx);
     HIPC(ctx, hipSetDevice(ctx->device));
     auto p = std::make_shared<Pop>();
     if (flags & (GP_DEVICE_PTR | GP_DEVICE_COMPILE)) {
@@ -1516,6 +1568,7 @@ int gp_free(gp_ctx* ctx, gp_handle h)
 {
     if (!ctx) return GP_EINVAL;
     std::lock_guard<std::mutex> lk(ctx->mu);
+    PoolScope pool(ctx);
     (void)hipSetDevice(ctx->device);
     (void)hipStreamSynchronize(ctx->stream);
     if (ctx->pops.erase(h)) return GP_OK;
@@ -1660,6 +1713,7 @@ int gp_evaluate_full(gp_ctx* ctx, gp_handle pop, gp_handle cases, uint32_t flags
     if (!ctx) return GP_EINVAL;
     const double t0 = now_ms();
     std::lock_guard<std::mutex> lk(ctx->mu);
+    PoolScope pool(ctx);
     HIPC(ctx, hipSetDevice(ctx->device));
     Pop* p;
     CaseSet* cs;
@@ -1704,6 +1758,7 @@ int gp_fitness(gp_ctx* ctx, gp_handle cases, const void* outputs, int64_t n, uin
 {
     if (!ctx) return GP_EINVAL;
     std::lock_guard<std::mutex> lk(ctx->mu);
+    PoolScope pool(ctx);
     HIPC(ctx, hipSetDevice(ctx->device));
     auto ic = ctx->cases.find(cases);
     if (ic == ctx->cases.end()) return set_err(ctx, GP_EINVAL, "unknown case-set handle");
@@ -1740,6 +1795,7 @@ int gp_evaluate_incremental_batch(gp_ctx* ctx, gp_handle pop, gp_handle cases, i
     if (!ctx) return GP_EINVAL;
     const double t0 = now_ms();
     std::lock_guard<std::mutex> lk(ctx->mu);
+    PoolScope pool(ctx);
     HIPC(ctx, hipSetDevice(ctx->device));
     Pop* p;
     CaseSet* cs;
@@ -1820,6 +1876,7 @@ int gp_splice_children(gp_ctx* ctx, gp_handle pop, int64_t n_children, const int
     if (!ctx) return GP_EINVAL;
     const double t0 = now_ms();
     std::lock_guard<std::mutex> lk(ctx->mu);
+    PoolScope pool(ctx);
     HIPC(ctx, hipSetDevice(ctx->device));
     auto ip = ctx->pops.find(pop);
     if (ip == ctx->pops.end()) return set_err(ctx, GP_EINVAL, "unknown population handle");
@@ -1958,6 +2015,7 @@ int gp_evolve(gp_ctx* ctx, gp_handle pop, gp_handle cases, const gp_evolve_cfg* 
 {
     if (!ctx || !cfg || !out_pop) return GP_EINVAL;
     std::lock_guard<std::mutex> lk(ctx->mu);
+    PoolScope pool(ctx);
     HIPC(ctx, hipSetDevice(ctx->device));
     Pop* p0;
     CaseSet* cs;
@@ -2451,6 +2509,7 @@ int gp_autotune(gp_ctx* ctx, gp_handle pop, gp_handle cases, int* best_variant, 
 {
     if (!ctx) return GP_EINVAL;
     std::lock_guard<std::mutex> lk(ctx->mu);
+    PoolScope pool(ctx);
     HIPC(ctx, hipSetDevice(ctx->device));
     Pop* p;
     CaseSet* cs;
@@ -2685,7 +2744,7 @@ int gpe::index_trees(Ctx* ctx, int n_inputs, int64_t n_trees, const uint8_t* ops
     const int64_t seg_total = ix_levels(n_nodes, q, len);
     const int64_t nb = (n_nodes + kIxBlock - 1) / kIxBlock;
     DevBuf el, boff, bsum, seg, flag, bempty;
-    RC(scratch_alloc(ctx, arena, el, (size_t)(nb * kIxBlock + kIxFan) * 4));
+    RC(scratch_alloc(ctx, arena, el, (size_t)(nb * kIxBlock + kIxFan) * 2));
     RC(scratch_alloc(ctx, arena, boff, (size_t)(nb + 1) * 4));
     RC(scratch_alloc(ctx, arena, bsum, (size_t)nb * 4));
     RC(scratch_alloc(ctx, arena, seg, (size_t)(seg_total + kIxFan) * 4));
@@ -2706,6 +2765,7 @@ int gp_index_trees(gp_ctx* ctx, int n_inputs, int64_t n_trees, const uint8_t* op
 {
     if (!ctx) return GP_EINVAL;
     std::lock_guard<std::mutex> lk(ctx->mu);
+    PoolScope pool(ctx);
     HIPC(ctx, hipSetDevice(ctx->device));
     return index_trees(ctx, n_inputs, n_trees, ops, offsets, n_nodes, valid, end, parent, strahler, device_ms,
                        ctx->stream);

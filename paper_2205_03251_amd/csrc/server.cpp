@@ -120,25 +120,6 @@ struct Server {
 
 namespace {
 
-int variant_for(Server* S, int vtype, const CaseSet* cs, const Pop* p)
-{
-    Variant* vt = variant_table();
-    auto ok = [&](int v) {
-        return v >= 0 && v < variant_count() &&
-               variant_fits(vt[v], vtype, p->max_stack, p->n_inputs, cs->n_elems, cs->stride,
-                            vtype == GP_BOOL ? 8 : 4);
-    };
-    if (ok(S->forced_variant)) return S->forced_variant;
-    int wantK = vtype == GP_F32 ? (cs->n_elems <= 64 ? 1 : cs->n_elems <= 128 ? 2 : 4) : (cs->n_elems <= 64 ? 1 : 2);
-    for (int v = 0; v < variant_count(); ++v)
-        if (ok(v) && vt[v].K == wantK && vt[v].table) return v;
-    for (int v = 0; v < variant_count(); ++v)
-        if (ok(v) && vt[v].K == wantK) return v;
-    for (int v = 0; v < variant_count(); ++v)
-        if (ok(v)) return v;
-    return -1;
-}
-
 uint64_t estimate_full(const TreeProg& pg, const CaseSet* cs)
 {
     const uint64_t esz = cs->vtype == GP_BOOL ? 8 : 4;
@@ -325,7 +306,7 @@ int launch_batch(Server* S, SBatch* b)
         b->pop = std::make_shared<Pop>();
         int rc0 = assemble_population(c, cs->vtype, cs->n_inputs, progs, nodes, 0, b->pop.get(), s);
         if (rc0 != GP_OK) return rc0;
-        const Launch L{variant_for(S, cs->vtype, cs, b->pop.get()), std::max(0, S->forced_waves)};
+        const Launch L{default_variant(cs->vtype, cs, b->pop.get(), S->forced_variant), std::max(0, S->forced_waves)};
         if (L.variant < 0) return GP_EINVAL;
         const int rc = enqueue_full(c, b->pop.get(), ch, cs, L, false, false, s, nullptr);
         if (rc != GP_OK) return rc;
@@ -545,6 +526,7 @@ int gp_server_start(gp_ctx* ctxp, const gp_server_cfg* cfg)
     S->budget = S->cfg.budget_bytes ? std::min<uint64_t>(S->cfg.budget_bytes, ctx->budget) : ctx->budget;
     {
         std::lock_guard<std::mutex> lk(ctx->mu);
+        ctx->pool.trim();                        // its threads allocate for themselves
         S->tuned = ctx->tuned;
         S->forced_variant = ctx->forced_variant;
         S->forced_waves = ctx->forced_waves;
