@@ -3,8 +3,8 @@
 // assemble_population build on the host, byte for byte, built from the trees'
 // bytes in device memory.  The per-thread steps are in devcompile_core.h.
 //
-// Passes: the device tree index (validity, subtree ends, parents); one thread
-// per terminal finishes nodes bottom-up (stack need, cuts, instruction form,
+// Passes: the device tree index (validity, subtree ends, parents); walks from
+// the terminals up finish nodes bottom-up (stack need, cuts, instruction form,
 // code length); the crossover points' paths are read up the parent index and
 // their records assigned on the host; chunk roots are compacted, numbered and
 // given code offsets (host prefix sums over per-chunk lengths); one thread per
@@ -70,11 +70,6 @@ struct DevMemPacked : DevMem {
     __device__ static void st(int32_t* p, int32_t v) { *p = v; }
 };
 
-// Persistent waves: a wave takes kDcBatch positions at a time from a shared
-// cursor, and each lane whose walk has ended takes the next terminal of the
-// wave's batch, so no lane idles while the longest walk of its wave goes on.
-constexpr int kDcBatch = 1024;
-
 __device__ __forceinline__ int64_t dc_uniform(int64_t x)
 {
     const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)x);
@@ -82,7 +77,8 @@ __device__ __forceinline__ int64_t dc_uniform(int64_t x)
     return (int64_t)(((uint64_t)hi << 32) | lo);
 }
 
-// The next batch [*pb, *pe) of [0, n) for this wave; false once none is left.
+// The next batch [*pb, *pe) of [0, n) for this wave of a persistent kernel;
+// false once none is left.
 __device__ __forceinline__ bool dc_take_batch(unsigned long long* cursor, int64_t n, int64_t batch, int64_t* pb,
                                               int64_t* pe)
 {
@@ -94,32 +90,209 @@ __device__ __forceinline__ bool dc_take_batch(unsigned long long* cursor, int64_
     return b < n;
 }
 
-__global__ __launch_bounds__(256) void k_dc_up_packed(DcNodes q, unsigned long long* cursor)
+// Bottom-up pass, packed hand-off (chunk targets up to kDcPackMaxC).  First a
+// workgroup finishes the functions whose whole subtree lies in its kDcSpan
+// positions, in LDS: the first operand to arrive leaves its word at the
+// function, the second takes it back by an exchange, combines, and leaves the
+// function's result in its place.  A wave's lanes share out the terminals of
+// its quarter, each lane taking the next as its walk ends.  The functions
+// whose subtree runs on past the block (about 150 of 4096 on random trees: the
+// depth gained over the block) get their left operand's word when that one is
+// finished, and every finished node whose parent lies before the block is
+// listed.  Results leave in whole lines.  Then a lane for each listed node
+// walks up from it (k_dc_up_walk).
+//
+// For 4.3e7 nodes (200 trees of up to 10^6) the block kernel takes 1.7 ms, bound
+// by the chains of LDS steps of its four waves, and the walks 2.6 ms, bound by
+// the deepest tree: about 2500 steps of one memory round trip.  With every
+// arrival a global 64-bit atomic and four dependent trips a step the pass took
+// 6.3 ms; walking on from the block with those steps, 9.9 ms.
+constexpr int kDcSpan = 4096;
+constexpr int kDcList = 256;                    // listed arrivals of one wave
+constexpr uint16_t kDcOutside = 0xffff;         // a parent before the block; a function not finished in it
+constexpr uint16_t kDcTop = 0xfffe;             // no parent: a tree's root
+
+__global__ __launch_bounds__(256) void k_dc_up_block(DcNodes q, uint32_t* n_walks, uint32_t* walk_v, uint32_t* walk_w)
 {
-    const uint64_t below = (1ull << (threadIdx.x & 63)) - 1;
-    int64_t v = -1, s = 0, e = 0, ts = 0, te = 0, pb = 0, pe = 0;
+    __shared__ uint32_t word[kDcSpan];          // 0, then the first operand's word, then info | len << 13
+    __shared__ uint16_t par[kDcSpan], rgt[kDcSpan];
+    __shared__ uint8_t op[kDcSpan];
+    __shared__ uint32_t lw[4][kDcList];
+    __shared__ uint16_t lv[4][kDcList];
+    __shared__ int64_t trees[2];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int64_t base = (int64_t)blockIdx.x * kDcSpan;
+    const int64_t end = base + kDcSpan < q.n ? base + kDcSpan : q.n;
+    if (tid < 2) trees[tid] = dc_tree_of(q, tid == 0 ? base : end - 1);
+    __syncthreads();
+    const int64_t t_lo = trees[0], t_hi = trees[1];
+    auto tree_of = [&](int64_t g) {
+        int64_t lo = t_lo, hi = t_hi + 1;
+        while (hi - lo > 1) {
+            const int64_t mid = (lo + hi) >> 1;
+            if (q.offsets[mid] <= g) lo = mid;
+            else hi = mid;
+        }
+        return lo;
+    };
+    const int64_t v0 = base + 16 * tid;
+    uint32_t big = 0;
+    if (v0 < end) {
+        int64_t t = tree_of(v0), s = q.offsets[t], e = q.offsets[t + 1];
+        for (int j = 0; j < 16; ++j) {
+            const int64_t v = v0 + j;
+            if (v >= end) break;
+            if (v >= e) {
+                ++t;
+                s = e;
+                e = q.offsets[t + 1];
+            }
+            const int i = 16 * tid + j;
+            const uint8_t o = q.ops[v];
+            const int32_t pl = q.parl[v];
+            const int64_t last = s + q.endl[v];
+            uint16_t r = kDcOutside;
+            if ((o & kFuncBit) && last <= end) r = (uint16_t)(s + q.endl[v + 1] - base);
+            op[i] = o;
+            par[i] = pl < 0 ? kDcTop : s + pl >= base ? (uint16_t)(s + pl - base) : kDcOutside;
+            rgt[i] = r;
+            word[i] = 0;
+            if ((o & kFuncBit) && last - v >= q.big_min) big |= 1u << j;
+        }
+    }
+    __syncthreads();
+
+    uint32_t n_list = 0;                        // the wave's listed nodes
+    auto flush = [&]() {
+        uint32_t at = 0;
+        if (lane == 0 && n_list > 0) at = atomicAdd(n_walks, n_list);
+        at = __builtin_amdgcn_readfirstlane(at);
+        for (uint32_t i = lane; i < n_list; i += 64) {
+            walk_v[at + i] = (uint32_t)(base + lv[wave][i]);
+            walk_w[at + i] = lw[wave][i];
+        }
+        n_list = 0;
+    };
+    const uint64_t below = (1ull << lane) - 1;
+    int pb = wave * (kDcSpan / 4);
+    const int pe = (int)(end - base) < pb + kDcSpan / 4 ? (int)(end - base) : pb + kDcSpan / 4;
+    int v = -1;
     uint32_t w = 0;
-    bool more = true;
     for (;;) {
-        if (pb >= pe && more) more = dc_take_batch(cursor, q.n, kDcBatch, &pb, &pe);
         const uint64_t idle = __ballot(v < 0);
-        if (v < 0 && pb < pe) {
-            const int64_t g = pb + __popcll(idle & below);
-            if (g < pe && !(q.ops[g] & kFuncBit)) {
-                if (g < ts || g >= te) {
-                    const int64_t t = dc_tree_of(q, g);
-                    ts = q.offsets[t];
-                    te = q.offsets[t + 1];
-                }
-                s = ts;
-                e = te;
-                w = dc_leaf_packed<DevMemPacked>(q, g);
+        if (v < 0) {
+            const int g = pb + __popcll(idle & below);
+            if (g < pe && !(op[g] & kFuncBit)) {
+                word[g] = 1u | (1u << 13);
+                w = dc_leaf_word(dc_foldable_op(q, op[g]));
                 v = g;
             }
         }
         if (pb < pe) pb += __popcll(idle);
-        if (v >= 0) v = dc_step_packed<DevMemPacked>(q, s, e, v, &w);
-        if (!more && pb >= pe && __ballot(v >= 0) == 0) break;
+        int list = 0;                           // integers across the branches, not lane-mask booleans
+        if (v >= 0) {
+            const int p = par[v];
+            if (p == kDcTop) {
+                v = -1;
+            } else if (p == kDcOutside) {
+                list = 1;
+            } else if (rgt[p] == kDcOutside) {
+                // v is p's left operand (the right one ends with p, past the block)
+                ((uint32_t*)q.slot64)[2 * (base + p)] = w;
+                v = -1;
+            } else {
+                const uint32_t other =
+                    __hip_atomic_exchange(&word[p], w, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_WORKGROUP);
+                if (other == 0) {
+                    v = -1;                     // the other operand is not done yet
+                } else {
+                    const int l = p + 1, r = rgt[p];
+                    const int left = v == l;
+                    const DcNode o = dc_combine(q, par[p] == kDcTop, dc_unpack(left ? w : other),
+                                                dc_unpack(left ? other : w));
+                    word[p] = (uint32_t)dc_info(o) | ((uint32_t)o.len << 13);
+                    if (o.cut_kids & 1) atomicOr(&word[l], (uint32_t)kDcCut);
+                    if (o.cut_kids & 2) atomicOr(&word[r], (uint32_t)kDcCut);
+                    w = o.cut ? kDcPackCut : dc_pack(o.need, o.waits, o.len, o.open);
+                    v = p;
+                }
+            }
+        }
+        const uint64_t listed = __ballot(list);
+        if (list) {
+            const uint32_t at = n_list + __popcll(listed & below);
+            lv[wave][at] = (uint16_t)v;
+            lw[wave][at] = w;
+            v = -1;
+        }
+        n_list += __popcll(listed);
+        if (n_list + 64 > kDcList) flush();
+        if (pb >= pe && __ballot(v >= 0) == 0) break;
+    }
+    flush();
+    __syncthreads();
+    // the results of terminals and of the functions finished here (the others' are stored by their walks)
+    if (v0 >= end) return;
+    bool all = v0 + 16 <= end;
+    for (int j = 0; j < 16 && all; ++j) all = !(op[16 * tid + j] & kFuncBit) || rgt[16 * tid + j] != kDcOutside;
+    if (all) {
+        for (int j = 0; j < 16; j += 4) {
+            const uint4 x = *(const uint4*)(word + 16 * tid + j);
+            *(int4*)(q.info + v0 + j) = make_int4(x.x & 8191, x.y & 8191, x.z & 8191, x.w & 8191);
+            *(int4*)(q.len + v0 + j) = make_int4(x.x >> 13, x.y >> 13, x.z >> 13, x.w >> 13);
+        }
+        if (q.big) {
+            uint32_t b[4];
+            for (int j = 0; j < 4; ++j)
+                b[j] = (big >> (4 * j) & 1u) | (big >> (4 * j + 1) & 1u) << 8 | (big >> (4 * j + 2) & 1u) << 16 |
+                       (big >> (4 * j + 3) & 1u) << 24;
+            *(uint4*)(q.big + v0) = make_uint4(b[0], b[1], b[2], b[3]);
+        }
+        return;
+    }
+    for (int j = 0; j < 16; ++j) {
+        const int i = 16 * tid + j;
+        if (v0 + j >= end || ((op[i] & kFuncBit) && rgt[i] == kDcOutside)) continue;
+        q.info[v0 + j] = word[i] & 8191;
+        q.len[v0 + j] = word[i] >> 13;
+        if (q.big) q.big[v0 + j] = big >> j & 1;
+    }
+}
+
+// Lane i walks up from listed node i.  At each parent, if the other operand's
+// word is there already (stored by the block kernel, or by an earlier arrival),
+// the lane combines without an atomic; else it leaves its own word by one and
+// ends, unless the other came in between.  The parent's slot, its own parent
+// and its end are loaded together, so a step of the chain costs one trip.
+__global__ __launch_bounds__(256) void k_dc_up_walk(DcNodes q, const uint32_t* n_walks, const uint32_t* walk_v,
+                                                    const uint32_t* walk_w)
+{
+    const uint32_t n = *n_walks;
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
+        int64_t v = walk_v[i];
+        uint32_t w = walk_w[i];
+        const int64_t s = q.offsets[dc_tree_of(q, v)];
+        int32_t p = q.parl[v];
+        while (p >= 0) {
+            const int64_t pg = s + p;
+            if (pg >= v) {
+                DevMem::err(q.err, 2);
+                break;
+            }
+            const bool left = v == pg + 1;
+            const int64_t end = s + q.endl[pg];
+            const int32_t pp = q.parl[pg];
+            uint32_t* half = (uint32_t*)(q.slot64 + pg);
+            uint32_t other = __hip_atomic_load(half + (left ? 1 : 0), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (other == 0) {
+                const uint64_t old = DevMem::fetch_or64(q.slot64 + pg, left ? (uint64_t)w : (uint64_t)w << 32);
+                other = left ? (uint32_t)(old >> 32) : (uint32_t)old;
+                if (other == 0) break;          // the other operand is not done yet
+            }
+            w = dc_finish_packed<DevMemPacked>(q, s, pg, left ? w : other, left ? other : w, end);
+            v = pg;
+            p = pp;
+        }
     }
 }
 
@@ -207,8 +380,6 @@ __global__ __launch_bounds__(256) void k_dc_store(DcNodes q, const int64_t* node
 // Compaction of a flag array, in order: a block takes kDcSpan positions, 16
 // per thread.  Count pass: the block's set flags.  Write pass: each set
 // position to out[boff[block] + its rank in the block].
-constexpr int kDcSpan = 4096;
-
 __device__ __forceinline__ uint32_t dc_flags16(const uint8_t* flags, int64_t base, int64_t n)
 {
     uint32_t m = 0;
@@ -652,9 +823,14 @@ int device_compile_population(Ctx* c, int vtype, int n_inputs, int64_t n_trees, 
     q.S = compile_stack_slots();
     q.C = C;
     if (packed) {
+        // open and cnt are not in use yet: the listed nodes and their words
+        uint32_t* n_walks = counter.as<uint32_t>();
         HIPC(c, launch_fill_i32(counter.as<int32_t>(), 4, 0, s));
-        hipLaunchKernelGGL(k_dc_up_packed, dim3(dc_persistent_blocks(c, n, kDcBatch, max_blocks)), dim3(256), 0, s, q,
-                           counter.as<unsigned long long>());
+        hipLaunchKernelGGL(k_dc_up_block, dim3((unsigned)(n_span / kDcSpan)), dim3(256), 0, s, q, n_walks,
+                           open.as<uint32_t>(), cnt.as<uint32_t>());
+        // about 100 nodes are listed per block, at most every terminal; a lane takes a second one only beyond n / 16
+        hipLaunchKernelGGL(k_dc_up_walk, dim3(blocks_for((n + 15) / 16)), dim3(256), 0, s, q, n_walks,
+                           open.as<uint32_t>(), cnt.as<uint32_t>());
     } else {
         hipLaunchKernelGGL(k_dc_up, dim3(blocks_for(n)), dim3(256), 0, s, q);
     }

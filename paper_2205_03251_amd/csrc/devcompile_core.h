@@ -97,25 +97,23 @@ GPE_HD inline int64_t dc_tree_of(const DcNodes& q, int64_t g)
     return lo;
 }
 
-GPE_HD inline bool dc_foldable(const DcNodes& q, int64_t v)
-{
-    const uint8_t b = q.ops[v];
-    return !(b & kFuncBit) && (q.boolean || b == 0);
-}
+GPE_HD inline bool dc_foldable_op(const DcNodes& q, uint8_t b) { return !(b & kFuncBit) && (q.boolean || b == 0); }
+GPE_HD inline bool dc_foldable(const DcNodes& q, int64_t v) { return dc_foldable_op(q, q.ops[v]); }
 
 GPE_HD inline int dc_max(int a, int b) { return a > b ? a : b; }
 
 // An operand as its parent sees it: roots a chunk of its own (then it is one
-// LOAD word of one slot), or its stack need, code words and open nodes, and
-// whether its code reads LOADs.
+// LOAD word of one slot), or its stack need, code words and open nodes,
+// whether its code reads LOADs, and whether it is a terminal that folds into
+// its parent's instruction.
 struct DcKid {
-    bool cut, waits;
+    bool cut, waits, fold;
     int need;
     int32_t len;
     int32_t open;
 };
 
-// The function at global index g of the tree starting at s, from its two
+// A function from its two
 // operands (compile_tree's rules): its stack need, instruction form, code
 // words and open nodes, whether it roots a chunk by size, whether its code
 // reads LOADs, and which operands (1 left | 2 right) it makes root a chunk:
@@ -129,9 +127,9 @@ struct DcNode {
     int cut_kids;
 };
 
-GPE_HD inline DcNode dc_combine(const DcNodes& q, int64_t g, int64_t s, int64_t l, int64_t r, DcKid L, DcKid R)
+// root: the function is its tree's root.
+GPE_HD inline DcNode dc_combine(const DcNodes& q, bool root, DcKid L, DcKid R)
 {
-    const bool fol = dc_foldable(q, l), fo_r = dc_foldable(q, r);
     const int64_t G = side_chunk_nodes(q.C);
     const bool wl = L.cut || L.waits, wr = R.cut || R.waits;
     DcNode o;
@@ -147,7 +145,7 @@ GPE_HD inline DcNode dc_combine(const DcNodes& q, int64_t g, int64_t s, int64_t 
     auto cost_l = [&]() { return L.cut ? 1 : L.need; };
     auto cost_r = [&]() { return R.cut ? 1 : R.need; };
     auto need_of = [&]() {
-        const bool fl = !L.cut && fol, fr = !R.cut && fo_r;
+        const bool fl = !L.cut && L.fold, fr = !R.cut && R.fold;
         if (fl && fr) return 1;
         if (fl) return cost_r();
         if (fr) return cost_l();
@@ -166,7 +164,7 @@ GPE_HD inline DcNode dc_combine(const DcNodes& q, int64_t g, int64_t s, int64_t 
         }
         o.need = need_of();
     }
-    const bool fl = !L.cut && fol, fr = !R.cut && fo_r;
+    const bool fl = !L.cut && L.fold, fr = !R.cut && R.fold;
     if (fl && fr) {
         o.form = M_XX;
         o.len = 1;
@@ -180,9 +178,14 @@ GPE_HD inline DcNode dc_combine(const DcNodes& q, int64_t g, int64_t s, int64_t 
         o.len = (L.cut ? 1 : L.len) + (R.cut ? 1 : R.len) + 1;
     }
     o.open = 1 + (L.cut ? 1 : (int64_t)L.open) + (R.cut ? 1 : (int64_t)R.open);
-    o.cut = o.open >= q.C && g != s;
+    o.cut = o.open >= q.C && !root;
     o.waits = L.cut || R.cut || wl || wr;
     return o;
+}
+
+GPE_HD inline int32_t dc_info(const DcNode& o)
+{
+    return o.need | (o.cut ? kDcCut : 0) | (o.waits ? kDcWaits : 0) | (o.form << 8);
 }
 
 // The outcome of a finished function node: its info and code words for the
@@ -192,7 +195,7 @@ template <class Mem>
 GPE_HD inline void dc_store(const DcNodes& q, int64_t g, int64_t s, int64_t l, int64_t r, const DcNode& o)
 {
     Mem::st(q.len + g, o.len);
-    Mem::st(q.info + g, o.need | (o.cut ? kDcCut : 0) | (o.waits ? kDcWaits : 0) | (o.form << 8));
+    Mem::st(q.info + g, dc_info(o));
     if (o.cut_kids & 1) q.ncut[l] = 1;
     if (o.cut_kids & 2) q.ncut[r] = 1;
     if (q.big) q.big[g] = s + q.endl[g] - g >= q.big_min ? 1 : 0;
@@ -245,12 +248,13 @@ template <class Mem> GPE_HD inline int64_t dc_step(const DcNodes& q, int64_t s, 
         DcKid k;
         k.cut = (i & kDcCut) != 0;
         k.waits = (i & kDcWaits) != 0;
+        k.fold = dc_foldable(q, c);
         k.need = i & 63;
         k.len = Mem::ld(q.len + c);
         k.open = Mem::ld(q.open + c);
         return k;
     };
-    const DcNode o = dc_combine(q, pg, s, l, r, kid(l), kid(r));
+    const DcNode o = dc_combine(q, pg == s, kid(l), kid(r));
     dc_store<Mem>(q, pg, s, l, r, o);
     Mem::st(q.open + pg, (int32_t)(o.open < 0x7fffffff ? o.open : 0x7fffffff));
     return pg;
@@ -260,7 +264,7 @@ template <class Mem> GPE_HD inline int64_t dc_step(const DcNodes& q, int64_t s, 
 // kDcPackMaxC).  A node that does not root a chunk has fewer open nodes than
 // the target (else it would root one) and no more code words than open
 // nodes, so need - 1 (4 bits, for at most kDcPackMaxS stack slots), whether
-// its code reads LOADs (1), words (13) and open nodes (14) fit in 32 bits;
+// its code reads LOADs (1), words (13; 0: a terminal that its parent folds) and open nodes (14) fit in 32 bits;
 // a chunk root is all ones.  Each operand ORs its word into its half of the
 // parent's slot (left operand low, right high); the second to arrive gets the
 // first's word back from the same atomic, so no other value crosses threads.
@@ -278,19 +282,35 @@ GPE_HD inline DcKid dc_unpack(uint32_t w)
     DcKid k;
     k.cut = w == kDcPackCut;
     k.waits = (w & 16) != 0;
+    k.fold = w >> 5 == 1u << 13;                // no words, one open node
     k.need = (int)(w & 15) + 1;
     k.len = (int32_t)((w >> 5) & 8191);
     k.open = (int32_t)(w >> 18);
     return k;
 }
 
-// A terminal's stores, and its word for its parent.
+// A terminal's word for its parent, and its stores.
+GPE_HD inline uint32_t dc_leaf_word(bool fold) { return dc_pack(1, false, fold ? 0 : 1, 1); }
 template <class Mem> GPE_HD inline uint32_t dc_leaf_packed(const DcNodes& q, int64_t g)
 {
     Mem::st(q.info + g, 1);
     Mem::st(q.len + g, 1);
     if (q.big) q.big[g] = 0;
-    return dc_pack(1, false, 1, 1);
+    return dc_leaf_word(dc_foldable(q, g));
+}
+
+// Function pg of the tree starting at s, its subtree's end, from its operands'
+// words: its outcome stored, its own word returned.
+template <class Mem>
+GPE_HD inline uint32_t dc_finish_packed(const DcNodes& q, int64_t s, int64_t pg, uint32_t wl, uint32_t wr, int64_t end)
+{
+    const DcNode o = dc_combine(q, pg == s, dc_unpack(wl), dc_unpack(wr));
+    Mem::st(q.len + pg, o.len);
+    Mem::st(q.info + pg, dc_info(o));
+    if (o.cut_kids & 1) q.ncut[pg + 1] = 1;
+    if (o.cut_kids & 2) q.ncut[s + q.endl[pg + 1]] = 1;
+    if (q.big) q.big[pg] = end - pg >= q.big_min ? 1 : 0;
+    return o.cut ? kDcPackCut : dc_pack(o.need, o.waits, o.len, o.open);
 }
 
 // One arrival of node v (word w) at its parent; returns the parent (and its
@@ -309,14 +329,7 @@ GPE_HD inline int64_t dc_step_packed(const DcNodes& q, int64_t s, int64_t e, int
     const uint64_t old = Mem::fetch_or64(q.slot64 + pg, left ? (uint64_t)*w : (uint64_t)*w << 32);
     if (old == 0) return -1;                        // the other operand is not done yet
     const uint32_t other = left ? (uint32_t)(old >> 32) : (uint32_t)old;
-    const int64_t l = pg + 1, r = s + q.endl[pg + 1];
-    if (r <= l || r >= e || (!left && r != v)) {
-        Mem::err(q.err, 1);
-        return -1;
-    }
-    const DcNode o = dc_combine(q, pg, s, l, r, dc_unpack(left ? *w : other), dc_unpack(left ? other : *w));
-    dc_store<Mem>(q, pg, s, l, r, o);
-    *w = o.cut ? kDcPackCut : dc_pack(o.need, o.waits, o.len, o.open);
+    *w = dc_finish_packed<Mem>(q, s, pg, left ? *w : other, left ? other : *w, s + q.endl[pg]);
     return pg;
 }
 
