@@ -54,16 +54,6 @@ __device__ __forceinline__ float fop(float a, float b)
     }
 }
 
-__device__ __forceinline__ float fop_rt(int f, float a, float b)
-{
-    switch (f) {
-    case 0: return fop<0>(a, b);
-    case 1: return fop<1>(a, b);
-    case 2: return fop<2>(a, b);
-    default: return fop<3>(a, b);
-    }
-}
-
 template <int F>
 __device__ __forceinline__ uint64_t bop(uint64_t a, uint64_t b)
 {
@@ -71,16 +61,6 @@ __device__ __forceinline__ uint64_t bop(uint64_t a, uint64_t b)
     else if constexpr (F == 1) return a | b;
     else if constexpr (F == 2) return ~(a & b);
     else return ~(a | b);
-}
-
-__device__ __forceinline__ uint64_t bop_rt(int f, uint64_t a, uint64_t b)
-{
-    switch (f) {
-    case 0: return bop<0>(a, b);
-    case 1: return bop<1>(a, b);
-    case 2: return bop<2>(a, b);
-    default: return bop<3>(a, b);
-    }
 }
 
 // Bit-equal, or both NaN.
@@ -649,6 +629,65 @@ __global__ __launch_bounds__(256) void k_fit_bool(FitParams p)
 }
 
 // ------------------------------------------------------ incremental walk
+// Levels are taken in groups: the vectors of a whole group are loaded before
+// its first level is computed (their addresses do not depend on the walk), and
+// the group's levels are compared by one exchange between the waves instead of
+// one a level.  Levels past the stop within its group are computed for
+// nothing; what they leave is not used (on a stop the child's values are the
+// mother's).  The chain is bound by memory latency: a trip and two barriers
+// per group instead of per level.  300 children of trees of 10^4..10^6 nodes
+// on 1024 cases (up to 1000 levels): 0.55 -> 0.10 ms.
+template <int R> constexpr int walk_group() { return R <= 2 ? 16 : R <= 4 ? 8 : R <= 8 ? 4 : R <= 16 ? 2 : 1; }
+
+// v = f(v, s), the walked operand v on the right when `right`.
+template <int R>
+__device__ __forceinline__ void walk_apply(int f, bool right, float (&v)[R], const float (&s)[R])
+{
+    switch (f) {
+#define GP_WALK(F)                                                                            \
+    case F:                                                                                   \
+        UNROLL for (int m = 0; m < R; ++m) v[m] = right ? fop<F>(s[m], v[m]) : fop<F>(v[m], s[m]); \
+        break;
+        GP_WALK(0)
+        GP_WALK(1)
+        GP_WALK(2)
+    default:
+        GP_WALK(3)
+#undef GP_WALK
+    }
+}
+
+template <int R>
+__device__ __forceinline__ void walk_apply(int f, uint64_t (&v)[R], const uint64_t (&s)[R])
+{
+    switch (f) {
+#define GP_WALK(F)                                                                            \
+    case F:                                                                                   \
+        UNROLL for (int m = 0; m < R; ++m) v[m] = bop<F>(v[m], s[m]);                         \
+        break;
+        GP_WALK(0)
+        GP_WALK(1)
+        GP_WALK(2)
+    default:
+        GP_WALK(3)
+#undef GP_WALK
+    }
+}
+
+// The first level of a group (0 .. G - 1) at which every thread's bit of eq is
+// set, or -1; levels past n read as unequal.  turn: the group's number (the
+// exchange buffer alternates, so one barrier a group is enough).
+__device__ __forceinline__ int walk_first_equal(uint32_t eq, int G, int n, int turn, uint32_t (*ex)[4])
+{
+    uint32_t all = 0;
+    for (int g = 0; g < G; ++g) all |= (__ballot(eq >> g & 1u) == ~0ull ? 1u : 0u) << g;
+    if (n < G) all &= (1u << n) - 1u;
+    if ((threadIdx.x & 63) == 0) ex[turn & 1][threadIdx.x >> 6] = all;
+    __syncthreads();
+    const uint32_t m = ex[turn & 1][0] & ex[turn & 1][1] & ex[turn & 1][2] & ex[turn & 1][3];
+    return __ffs((int)m) - 1;
+}
+
 // One workgroup of 256 threads per child.  Level 0 compares the donor's
 // vector with the mother's vector at the crossover point; level k applies
 // the k-th ancestor's function with the path operand replaced by the
@@ -659,6 +698,7 @@ template <int R>
 __global__ __launch_bounds__(256) void k_walk_f32(WalkParams p)
 {
     __shared__ double red[256];
+    __shared__ uint32_t ex[2][4];
     const int64_t ci = blockIdx.x;
     const GP_CONST WalkChild* wcp = cst(p.children) + ci;
     const SpineLvl* levels = wcp->levels;
@@ -690,28 +730,33 @@ __global__ __launch_bounds__(256) void k_walk_f32(WalkParams p)
     if (__syncthreads_and(eq)) {
         stop = 0;
     } else {
-        for (int k = 0; k < n_levels; ++k) {
-            const GP_CONST SpineLvl* lp = cst(levels) + k;
-            const SpineLvl lv{lp->fside, lp->sib, lp->par, 0};
-            const float* sb = lv.sib >= 0 ? recs + (int64_t)lv.sib * p.stride
-                                          : in + (int64_t)(-lv.sib - 1) * p.stride;
-            const float* pr = recs + (int64_t)lv.par * p.stride;
-            const int f = lv.fside & 3;
-            const bool right = (lv.fside & 4) != 0;
-            eq = true;
-            UNROLL for (int m = 0; m < R; ++m) {
-                const int64_t i = tid + 256 * m;
-                if (i < T) {
-                    const float s = sb[i];
-                    const float r = right ? fop_rt(f, s, v[m]) : fop_rt(f, v[m], s);
-                    v[m] = r;
-                    eq = eq && same_f32(r, pr[i]);
+        constexpr int G = walk_group<R>();
+        uint32_t at[R];                         // threads past the last case read it again
+        UNROLL for (int m = 0; m < R; ++m) at[m] = (uint32_t)min((int64_t)(tid + 256 * m), T - 1);
+        for (int k = 0; k < n_levels && stop < 0; k += G) {
+            float sv[G][R], pv[G][R];
+            int fs[G];
+            UNROLL for (int g = 0; g < G; ++g) {
+                const GP_CONST SpineLvl* lp = cst(levels) + min(k + g, n_levels - 1);
+                const int32_t sib = lp->sib, par = lp->par;
+                fs[g] = lp->fside;
+                const float* sb = sib >= 0 ? recs + (int64_t)sib * p.stride : in + (int64_t)(-sib - 1) * p.stride;
+                const float* pr = recs + (int64_t)par * p.stride;
+                UNROLL for (int m = 0; m < R; ++m) {
+                    sv[g][m] = sb[at[m]];
+                    pv[g][m] = pr[at[m]];
                 }
             }
-            if (__syncthreads_and(eq)) {
-                stop = k + 1;
-                break;
+            uint32_t same = 0;
+            UNROLL for (int g = 0; g < G; ++g) {
+                if (k + g >= n_levels) break;
+                walk_apply<R>(fs[g] & 3, (fs[g] & 4) != 0, v, sv[g]);
+                uint32_t e = 1;
+                UNROLL for (int m = 0; m < R; ++m) e &= tid + 256 * m >= T || same_f32(v[m], pv[g][m]) ? 1u : 0u;
+                same |= e << g;
             }
+            const int first = walk_first_equal(same, G, n_levels - k, k / G, ex);
+            if (first >= 0) stop = k + first + 1;
         }
     }
     if (tid == 0) {
@@ -748,6 +793,7 @@ template <int R>
 __global__ __launch_bounds__(256) void k_walk_bool(WalkParams p)
 {
     __shared__ int64_t red[256];
+    __shared__ uint32_t ex[2][4];
     const int64_t ci = blockIdx.x;
     const GP_CONST WalkChild* wcp = cst(p.children) + ci;
     const SpineLvl* levels = wcp->levels;
@@ -780,28 +826,36 @@ __global__ __launch_bounds__(256) void k_walk_bool(WalkParams p)
     if (__syncthreads_and(eq)) {
         stop = 0;
     } else {
-        for (int k = 0; k < n_levels; ++k) {
-            const GP_CONST SpineLvl* lp = cst(levels) + k;
-            const SpineLvl lv{lp->fside, lp->sib, lp->par, 0};
-            const uint64_t* sb = lv.sib >= 0 ? recs + (int64_t)lv.sib * p.stride
-                                             : in + (int64_t)(-lv.sib - 1) * p.stride;
-            const uint64_t* pr = recs + (int64_t)lv.par * p.stride;
-            const int f = lv.fside & 3;
-            const bool right = (lv.fside & 4) != 0;
-            eq = true;
-            UNROLL for (int m = 0; m < R; ++m) {
-                const int64_t i = tid + 256 * m;
-                if (i < W) {
-                    const uint64_t s = sb[i];
-                    const uint64_t r = right ? bop_rt(f, s, v[m]) : bop_rt(f, v[m], s);
-                    v[m] = r;
-                    eq = eq && (((r ^ pr[i]) & valid_bits(i, T)) == 0);
+        constexpr int G = walk_group<2 * R>();
+        uint32_t at[R];                         // threads past the last word read it again
+        UNROLL for (int m = 0; m < R; ++m) at[m] = (uint32_t)min((int64_t)(tid + 256 * m), W - 1);
+        for (int k = 0; k < n_levels && stop < 0; k += G) {
+            uint64_t sv[G][R], pv[G][R];
+            int fs[G];
+            UNROLL for (int g = 0; g < G; ++g) {
+                const GP_CONST SpineLvl* lp = cst(levels) + min(k + g, n_levels - 1);
+                const int32_t sib = lp->sib, par = lp->par;
+                fs[g] = lp->fside;
+                const uint64_t* sb = sib >= 0 ? recs + (int64_t)sib * p.stride : in + (int64_t)(-sib - 1) * p.stride;
+                const uint64_t* pr = recs + (int64_t)par * p.stride;
+                UNROLL for (int m = 0; m < R; ++m) {
+                    sv[g][m] = sb[at[m]];
+                    pv[g][m] = pr[at[m]];
                 }
             }
-            if (__syncthreads_and(eq)) {
-                stop = k + 1;
-                break;
+            uint32_t same = 0;
+            UNROLL for (int g = 0; g < G; ++g) {
+                if (k + g >= n_levels) break;
+                walk_apply<R>(fs[g] & 3, v, sv[g]);
+                uint32_t e = 1;
+                UNROLL for (int m = 0; m < R; ++m) {
+                    const int64_t i = tid + 256 * m;
+                    e &= i >= W || ((v[m] ^ pv[g][m]) & valid_bits(i, T)) == 0 ? 1u : 0u;
+                }
+                same |= e << g;
             }
+            const int first = walk_first_equal(same, G, n_levels - k, k / G, ex);
+            if (first >= 0) stop = k + first + 1;
         }
     }
     if (tid == 0) {
@@ -912,6 +966,7 @@ template <int R>
 __global__ __launch_bounds__(256) void k_coeval_f32(CoParams p)
 {
     __shared__ double red[256];
+    __shared__ uint32_t ex[2][4];
     const GP_CONST CoChild* cp = cst(p.children) + blockIdx.x;
     const float* vin = (const float*)cp->v_in;
     const float* min_ = (const float*)cp->m_in;
@@ -937,23 +992,29 @@ __global__ __launch_bounds__(256) void k_coeval_f32(CoParams p)
             if (tid + 256 * k < T) eq = eq && same_f32(v[k], m[k]);
         if (__syncthreads_and(eq)) stop = 0;
     }
-    for (int l = 0; stop == -2 && l < n_levels; ++l) {
-        const GP_CONST CoLevel* lp = cst(levels) + l;
-        const float* sb = (const float*)lp->sib;
-        const int fs = lp->fside;
-        const int f = fs & 3;
-        const bool right = (fs & 4) != 0;
-        bool eq = true;
-        UNROLL for (int k = 0; k < R; ++k) {
-            const int64_t i = tid + 256 * k;
-            if (i < T) {
-                const float s = sb[i];
-                v[k] = right ? fop_rt(f, s, v[k]) : fop_rt(f, v[k], s);
-                m[k] = right ? fop_rt(f, s, m[k]) : fop_rt(f, m[k], s);
-                eq = eq && same_f32(v[k], m[k]);
-            }
+    constexpr int G = walk_group<R>();
+    uint32_t at[R];                             // threads past the last case read it again
+    UNROLL for (int k = 0; k < R; ++k) at[k] = (uint32_t)min((int64_t)(tid + 256 * k), T - 1);
+    for (int l = 0; stop == -2 && l < n_levels; l += G) {
+        float sv[G][R];
+        int fs[G];
+        UNROLL for (int g = 0; g < G; ++g) {
+            const GP_CONST CoLevel* lp = cst(levels) + min(l + g, n_levels - 1);
+            const float* sb = (const float*)lp->sib;
+            fs[g] = lp->fside;
+            UNROLL for (int k = 0; k < R; ++k) sv[g][k] = sb[at[k]];
         }
-        if (__syncthreads_and(eq)) stop = level_base + l + 1;
+        uint32_t same = 0;
+        UNROLL for (int g = 0; g < G; ++g) {
+            if (l + g >= n_levels) break;
+            walk_apply<R>(fs[g] & 3, (fs[g] & 4) != 0, v, sv[g]);
+            walk_apply<R>(fs[g] & 3, (fs[g] & 4) != 0, m, sv[g]);
+            uint32_t e = 1;
+            UNROLL for (int k = 0; k < R; ++k) e &= tid + 256 * k >= T || same_f32(v[k], m[k]) ? 1u : 0u;
+            same |= e << g;
+        }
+        const int first = walk_first_equal(same, G, n_levels - l, l / G, ex);
+        if (first >= 0) stop = level_base + l + first + 1;
     }
     if (stop == -2 && last) stop = -1;
     if (tid == 0) p.stop_out[slot] = stop;
@@ -992,6 +1053,7 @@ template <int R>
 __global__ __launch_bounds__(256) void k_coeval_bool(CoParams p)
 {
     __shared__ int64_t red[256];
+    __shared__ uint32_t ex[2][4];
     const GP_CONST CoChild* cp = cst(p.children) + blockIdx.x;
     const uint64_t* vin = (const uint64_t*)cp->v_in;
     const uint64_t* min_ = (const uint64_t*)cp->m_in;
@@ -1020,23 +1082,32 @@ __global__ __launch_bounds__(256) void k_coeval_bool(CoParams p)
         }
         if (__syncthreads_and(eq)) stop = 0;
     }
-    for (int l = 0; stop == -2 && l < n_levels; ++l) {
-        const GP_CONST CoLevel* lp = cst(levels) + l;
-        const uint64_t* sb = (const uint64_t*)lp->sib;
-        const int fs = lp->fside;
-        const int f = fs & 3;
-        const bool right = (fs & 4) != 0;
-        bool eq = true;
-        UNROLL for (int k = 0; k < R; ++k) {
-            const int64_t i = tid + 256 * k;
-            if (i < W) {
-                const uint64_t s = sb[i];
-                v[k] = right ? bop_rt(f, s, v[k]) : bop_rt(f, v[k], s);
-                m[k] = right ? bop_rt(f, s, m[k]) : bop_rt(f, m[k], s);
-                eq = eq && (((v[k] ^ m[k]) & valid_bits(i, T)) == 0);
-            }
+    constexpr int G = walk_group<2 * R>();
+    uint32_t at[R];                             // threads past the last word read it again
+    UNROLL for (int k = 0; k < R; ++k) at[k] = (uint32_t)min((int64_t)(tid + 256 * k), W - 1);
+    for (int l = 0; stop == -2 && l < n_levels; l += G) {
+        uint64_t sv[G][R];
+        int fs[G];
+        UNROLL for (int g = 0; g < G; ++g) {
+            const GP_CONST CoLevel* lp = cst(levels) + min(l + g, n_levels - 1);
+            const uint64_t* sb = (const uint64_t*)lp->sib;
+            fs[g] = lp->fside;
+            UNROLL for (int k = 0; k < R; ++k) sv[g][k] = sb[at[k]];
         }
-        if (__syncthreads_and(eq)) stop = level_base + l + 1;
+        uint32_t same = 0;
+        UNROLL for (int g = 0; g < G; ++g) {
+            if (l + g >= n_levels) break;
+            walk_apply<R>(fs[g] & 3, v, sv[g]);
+            walk_apply<R>(fs[g] & 3, m, sv[g]);
+            uint32_t e = 1;
+            UNROLL for (int k = 0; k < R; ++k) {
+                const int64_t i = tid + 256 * k;
+                e &= i >= W || ((v[k] ^ m[k]) & valid_bits(i, T)) == 0 ? 1u : 0u;
+            }
+            same |= e << g;
+        }
+        const int first = walk_first_equal(same, G, n_levels - l, l / G, ex);
+        if (first >= 0) stop = level_base + l + first + 1;
     }
     if (stop == -2 && last) stop = -1;
     if (tid == 0) p.stop_out[slot] = stop;
