@@ -690,10 +690,11 @@ static EvalParams eval_params(Pop* p, const CaseSet* cs, Plan* pl)
     e.stride = cs->stride;
     e.n_slices = pl->n_slices;
     e.n_inputs = cs->n_inputs;
-    // Boolean items are short (a chunk of 256 words takes about 10 us), so their counters are asked more often:
-    // 400 trees on 4096 cases 0.32 ms with 4, 0.25 with 16; float launches keep their order better with 4
-    // (1000 large trees 5.57 ms, 5.87 with 16)
-    e.n_cursors = p->vtype == GP_BOOL ? 16 : 4;
+    // Sixteen counters when a wave takes few items, since all ask for their first at once: 300 trees of 10..10^4
+    // nodes (1.2 items a wave) 0.21 ms with 4, 0.13 with 16; 1000 of 10^3..10^4 (1.7) 0.22 and 0.14; 20 of up to
+    // 10^6 (9) 0.63 and 0.53; Boolean, 400 trees on 4096 cases (4) 0.32 and 0.25.  Four when it takes many, which
+    // keep the order better: three inputs, 1500 cases (18) 0.71 and 0.94 ms; 1000 large trees (77) 5.57 and 5.89.
+    e.n_cursors = pl->n_items <= 12 * (int64_t)pl->grid ? 16 : 4;
     static_assert(kCursors == 16, "counters allocated per launch");
     return e;
 }
