@@ -76,7 +76,8 @@ enum { GP_PREFIX = 0, GP_POSTFIX = 1 };    /* load layout */
 #define GP_DEVICE_PTR 0x1u   /* pointer arguments are device pointers */
 #define GP_ASYNC      0x2u   /* return once enqueued (needs GP_DEVICE_PTR outputs) */
 #define GP_PER_TREE   0x4u   /* one launch per tree instead of one batched launch */
-#define GP_NO_GRAPH   0x8u   /* launch kernels directly, no captured graph replay */
+#define GP_NO_GRAPH   0x8u   /* launch kernels directly (and time the interpreter's), no captured
+                                graph replay of the launches of GP_PER_TREE */
 #define GP_KEEP_TREES 0x10u  /* gp_load_population: keep the trees' bytes in device
                                 memory (charged to the budget) for gp_splice_children */
 #define GP_COEVAL     0x20u  /* gp_evaluate_incremental_batch: re-evaluate the mother

@@ -121,6 +121,16 @@ struct FitParams {
     int64_t stride;
     int64_t n_valid;             // T
     int64_t P;
+    // the caller's arrays, written as well when not null: rows (dense) and scores
+    void* rows_dst = nullptr;
+    void* fit_dst = nullptr;
+    // an interpreter launch's counters, set back for its next run when not null
+    int32_t* pending = nullptr;
+    const int32_t* pending_init = nullptr;
+    int64_t n_pending = 0;
+    unsigned int* cursor = nullptr;
+    int64_t n_cursors = 0;
+    int64_t n_rows = 0;          // set by the launcher
 };
 
 // ----------------------------------------------------------- launchers

@@ -567,44 +567,70 @@ __global__ void k_init(int32_t* pending, const int32_t* init, int64_t n, unsigne
 // Sum of |out - y| in double over P = max(64, 2^ceil(log2 T)) zero-padded
 // slots by the halving tree s[i] += s[i + h], h = P/2 ... 1.  Thread t holds
 // slots t + 256 m (m < R = max(1, P/256)); the levels h >= 256 pair slots of
-// the same thread, the rest go through LDS.
+// the same thread, the two above a wave go through LDS and the rest are lane
+// shuffles.  The sum is valid in thread 0.
 template <int R>
 __device__ double halving_sum(double (&e)[R], int64_t P, double* red)
 {
     const int tid = threadIdx.x;
     UNROLL for (int r = R / 2; r >= 1; r /= 2)
         UNROLL for (int m = 0; m < r; ++m) e[m] = e[m] + e[m + r];
-    const int Pp = P < 256 ? (int)P : 256;
-    red[tid] = e[0];
-    __syncthreads();
-    for (int h = Pp / 2; h >= 1; h >>= 1) {
-        if (tid < h) red[tid] = red[tid] + red[tid + h];
+    double v = e[0];
+    for (int h = 128; h >= 64; h >>= 1) {
+        if (P < 2 * h) continue;               // P is a power of two, at least 64
+        red[tid] = v;
+        __syncthreads();
+        if (tid < h) v = v + red[tid + h];
         __syncthreads();
     }
-    const double r = red[0];
-    __syncthreads();
-    return r;
+    for (int h = 32; h >= 1; h >>= 1) {
+        const double o = __shfl_down(v, h, 64);
+        v = v + o;                             // lanes at and past h add what the tree never reads
+    }
+    return v;
+}
+
+// The counters of the interpreter launch before this one, set back for the
+// next run of its plan by all blocks of the scoring launch.  Small evaluations
+// are bound by launches and the gaps between them: with the scoring launch also
+// writing the caller's arrays, 100 trees of at most 15 nodes on 20 cases take
+// 26 us a call in two launches, against 51 us in four (counters, interpreter,
+// scores, copies out), replayed as a graph or not.
+__device__ void reset_counters(const FitParams& p)
+{
+    if (!p.pending) return;
+    const int64_t i0 = (int64_t)blockIdx.x * 256 + threadIdx.x, step = (int64_t)gridDim.x * 256;
+    for (int64_t i = i0; i < p.n_pending; i += step) p.pending[i] = p.pending_init[i];
+    for (int64_t i = i0; i < p.n_cursors; i += step) p.cursor[i * kCursorStride] = 0u;
 }
 
 template <int R>
 __global__ __launch_bounds__(256) void k_fit_f32(FitParams p)
 {
     __shared__ double red[256];
+    reset_counters(p);
     const int64_t row = blockIdx.x;
+    if (row >= p.n_rows) return;
     const float* v = (const float*)p.vecs + (p.first_slot + row) * p.stride;
+    float* out = p.rows_dst ? (float*)p.rows_dst + row * p.n_valid : nullptr;
     const float* y = (const float*)p.target;
     double e[R];
     UNROLL for (int m = 0; m < R; ++m) {
         const int64_t i = threadIdx.x + 256 * m;
         double val = 0.0;
         if (i < p.n_valid) {
-            const float d = v[i] - y[i];
+            const float x = v[i];
+            if (out) out[i] = x;
+            const float d = x - y[i];
             val = (double)fabsf(d);
         }
         e[m] = val;
     }
     const double f = halving_sum<R>(e, p.P, red);
-    if (threadIdx.x == 0) ((double*)p.fit_out)[row] = f;
+    if (threadIdx.x == 0) {
+        ((double*)p.fit_out)[row] = f;
+        if (p.fit_dst) ((double*)p.fit_dst)[row] = f;
+    }
 }
 
 __device__ int64_t block_sum_i64(int64_t v, int64_t* red)
@@ -624,15 +650,24 @@ __device__ int64_t block_sum_i64(int64_t v, int64_t* red)
 __global__ __launch_bounds__(256) void k_fit_bool(FitParams p)
 {
     __shared__ int64_t red[256];
+    reset_counters(p);
     const int64_t row = blockIdx.x;
+    if (row >= p.n_rows) return;
     const uint64_t* v = (const uint64_t*)p.vecs + (p.first_slot + row) * p.stride;
     const uint64_t* t = (const uint64_t*)p.target;
     const int64_t W = (p.n_valid + 63) / 64;
     int64_t hits = 0;
-    for (int64_t w = threadIdx.x; w < W; w += 256)
-        hits += __popcll(~(v[w] ^ t[w]) & valid_bits(w, p.n_valid));
+    uint64_t* out = p.rows_dst ? (uint64_t*)p.rows_dst + row * W : nullptr;
+    for (int64_t w = threadIdx.x; w < W; w += 256) {
+        const uint64_t x = v[w];
+        if (out) out[w] = x;
+        hits += __popcll(~(x ^ t[w]) & valid_bits(w, p.n_valid));
+    }
     const int64_t h = block_sum_i64(hits, red);
-    if (threadIdx.x == 0) ((int64_t*)p.fit_out)[row] = h;
+    if (threadIdx.x == 0) {
+        ((int64_t*)p.fit_out)[row] = h;
+        if (p.fit_dst) ((int64_t*)p.fit_dst)[row] = h;
+    }
 }
 
 // ------------------------------------------------------ incremental walk
@@ -941,21 +976,28 @@ hipError_t launch_init(int32_t* pending, const int32_t* init, int64_t n, unsigne
 
 static int halving_rows(int64_t P) { return P <= 256 ? 1 : (int)(P / 256); }
 
-hipError_t launch_fitness(int vtype, const FitParams& p, int64_t n, hipStream_t s)
+hipError_t launch_fitness(int vtype, const FitParams& q, int64_t n, hipStream_t s)
 {
     if (n <= 0) return hipSuccess;
+    FitParams p = q;
+    p.n_rows = n;
+    // a block per row; more where there are many counters to set back
+    int64_t blocks = n;
+    if (p.pending) blocks = std::max(blocks, std::min<int64_t>(2048, (p.n_pending + 2047) / 2048));
+    if (blocks > 0x7fffffff) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)blocks);
     if (vtype == 1) {
-        hipLaunchKernelGGL(k_fit_bool, dim3((unsigned)n), dim3(256), 0, s, p);
+        hipLaunchKernelGGL(k_fit_bool, grid, dim3(256), 0, s, p);
         return hipGetLastError();
     }
     switch (halving_rows(p.P)) {
-    case 1: hipLaunchKernelGGL(k_fit_f32<1>, dim3((unsigned)n), dim3(256), 0, s, p); break;
-    case 2: hipLaunchKernelGGL(k_fit_f32<2>, dim3((unsigned)n), dim3(256), 0, s, p); break;
-    case 4: hipLaunchKernelGGL(k_fit_f32<4>, dim3((unsigned)n), dim3(256), 0, s, p); break;
-    case 8: hipLaunchKernelGGL(k_fit_f32<8>, dim3((unsigned)n), dim3(256), 0, s, p); break;
-    case 16: hipLaunchKernelGGL(k_fit_f32<16>, dim3((unsigned)n), dim3(256), 0, s, p); break;
-    case 32: hipLaunchKernelGGL(k_fit_f32<32>, dim3((unsigned)n), dim3(256), 0, s, p); break;
-    case 64: hipLaunchKernelGGL(k_fit_f32<64>, dim3((unsigned)n), dim3(256), 0, s, p); break;
+    case 1: hipLaunchKernelGGL(k_fit_f32<1>, grid, dim3(256), 0, s, p); break;
+    case 2: hipLaunchKernelGGL(k_fit_f32<2>, grid, dim3(256), 0, s, p); break;
+    case 4: hipLaunchKernelGGL(k_fit_f32<4>, grid, dim3(256), 0, s, p); break;
+    case 8: hipLaunchKernelGGL(k_fit_f32<8>, grid, dim3(256), 0, s, p); break;
+    case 16: hipLaunchKernelGGL(k_fit_f32<16>, grid, dim3(256), 0, s, p); break;
+    case 32: hipLaunchKernelGGL(k_fit_f32<32>, grid, dim3(256), 0, s, p); break;
+    case 64: hipLaunchKernelGGL(k_fit_f32<64>, grid, dim3(256), 0, s, p); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();

@@ -105,6 +105,7 @@ struct Plan {
     int variant = -1;
     int waves_per_cu = 0;
     bool per_tree = false;
+    bool counters_set = false;   // pending and the cursors hold their initial values (each run sets them back)
     int32_t n_slices = 0;
     int64_t n_items = 0;
     int grid = 0;
@@ -300,10 +301,19 @@ int ensure_eval_buffers(Ctx* c, Pop* p, const CaseSet* cs);
 // Synchronises s.  n_evaluated (may be null) receives their number.
 int enqueue_promoted(Ctx* c, Pop* p, const Pop* src, gp_handle cases_h, const CaseSet* cs, Launch L,
                      hipStream_t s, int64_t* n_evaluated);
-// Enqueue a full evaluation on stream s (no copies out, no synchronisation).
-// time_kernel: record c->kev0/kev1 around the interpreter launch.
+// Where the scoring launch of a batched full evaluation also writes its rows
+// (dense) and scores: device or mapped host memory, or null.
+struct FullOut {
+    void* rows = nullptr;
+    void* fit = nullptr;
+};
+// Enqueue a full evaluation on stream s (no copies out but `out`'s, no
+// synchronisation).  time_kernel: record c->kev0/kev1 around the interpreter
+// launch.  use_graph: one launch per tree is replayed from a captured graph (a
+// batched evaluation is two launches, which take less time than a replay).
 int enqueue_full(Ctx* c, Pop* p, gp_handle cases_h, const CaseSet* cs, Launch L, bool per_tree,
-                 bool use_graph, hipStream_t s, int64_t* launches, bool time_kernel = false);
+                 bool use_graph, hipStream_t s, int64_t* launches, bool time_kernel = false,
+                 const FullOut* out = nullptr);
 // Build the walk descriptors of an incremental batch and enqueue donor
 // evaluation + walk on s.  Outputs are device buffers owned by the caller.
 struct IncJob {

@@ -624,6 +624,16 @@ int ensure_eval_buffers(Ctx* c, Pop* p, const CaseSet* cs)
     return GP_OK;
 }
 
+// Counters of a plan to their initial values, in front of a run that no
+// completed run left them set for.
+static int set_counters(Ctx* c, Pop* p, Plan* pl, hipStream_t s)
+{
+    HIPC(c, launch_init(pl->pending.as<int32_t>(), pl->pending_init.as<int32_t>(), p->n_chunks * pl->n_slices,
+                        pl->cursor.as<unsigned int>(), (pl->per_tree ? p->n_trees : 1) * kCursors, s));
+    pl->counters_set = true;
+    return GP_OK;
+}
+
 static int make_plan(Ctx* c, Pop* p, const CaseSet* cs, Launch L, bool per_tree, Plan** out,
                      hipStream_t stream)
 {
@@ -668,6 +678,7 @@ static int make_plan(Ctx* c, Pop* p, const CaseSet* cs, Launch L, bool per_tree,
     RC(dev_alloc(c, pl->pending, pend.size() * sizeof(int32_t)));
     RC(dev_alloc(c, pl->cursor, (size_t)(per_tree ? p->n_trees : 1) * kCursors * kCursorStride * sizeof(unsigned int)));
     pl->grid = (int)std::max<int64_t>(1, std::min<int64_t>(resident_grid(c, v, pl->waves_per_cu), pl->n_items));
+    RC(set_counters(c, p, pl.get(), stream));
     HIPC(c, hipStreamSynchronize(stream));
     p->plans[key] = std::move(pl);
     *out = p->plans[key].get();
@@ -712,16 +723,19 @@ static FitParams fit_params(Pop* p, const CaseSet* cs)
     return f;
 }
 
-// Everything one full evaluation enqueues: reset counters and cursors,
-// evaluate, score.
+// Everything one full evaluation enqueues: set counters and cursors when the
+// run before did not leave them so, evaluate, score (and set them back).
 static int enqueue_body(Ctx* c, Pop* p, const CaseSet* cs, Plan* pl, hipStream_t s, int64_t* launches,
-                        bool time_kernel)
+                        bool time_kernel, const FullOut* out)
 {
-    const int64_t n_pend = p->n_chunks * pl->n_slices;
-    HIPC(c, launch_init(pl->pending.as<int32_t>(), pl->pending_init.as<int32_t>(), n_pend,
-                        pl->cursor.as<unsigned int>(), (pl->per_tree ? p->n_trees : 1) * kCursors, s));
+    const int64_t n_pend = p->n_chunks * pl->n_slices, n_cur = (pl->per_tree ? p->n_trees : 1) * kCursors;
+    int64_t nl = 0;
+    if (!pl->counters_set) {
+        RC(set_counters(c, p, pl, s));
+        ++nl;
+    }
+    pl->counters_set = false;                   // until the scoring launch below is enqueued
     EvalParams e = eval_params(p, cs, pl);
-    int64_t nl = 1;
     if (time_kernel) HIPC(c, hipEventRecord(c->kev0, s));
     if (!pl->per_tree) {
         HIPC(c, launch_eval(pl->variant, e, pl->grid, s));
@@ -739,20 +753,31 @@ static int enqueue_body(Ctx* c, Pop* p, const CaseSet* cs, Plan* pl, hipStream_t
         }
     }
     if (time_kernel) HIPC(c, hipEventRecord(c->kev1, s));
-    HIPC(c, launch_fitness(p->vtype, fit_params(p, cs), p->n_trees, s));
+    FitParams f = fit_params(p, cs);
+    f.pending = pl->pending.as<int32_t>();
+    f.pending_init = pl->pending_init.as<int32_t>();
+    f.n_pending = n_pend;
+    f.cursor = pl->cursor.as<unsigned int>();
+    f.n_cursors = n_cur;
+    if (out) {
+        f.rows_dst = out->rows;
+        f.fit_dst = out->fit;
+    }
+    HIPC(c, launch_fitness(p->vtype, f, p->n_trees, s));
+    pl->counters_set = true;
     ++nl;
     if (launches) *launches += nl;
     return GP_OK;
 }
 
 int enqueue_full(Ctx* c, Pop* p, gp_handle cases_h, const CaseSet* cs, Launch L, bool per_tree,
-                 bool use_graph, hipStream_t s, int64_t* launches, bool time_kernel)
+                 bool use_graph, hipStream_t s, int64_t* launches, bool time_kernel, const FullOut* out)
 {
     RC(ensure_eval_buffers(c, p, cs));
     Plan* pl = nullptr;
     RC(make_plan(c, p, cs, L, per_tree, &pl, s));
-    if (!use_graph) {
-        RC(enqueue_body(c, p, cs, pl, s, launches, time_kernel));
+    if (!use_graph || !per_tree) {
+        RC(enqueue_body(c, p, cs, pl, s, launches, time_kernel, out));
     } else {
         if (!pl->graph || pl->graph_cases != cases_h) {
             if (pl->graph) {
@@ -760,13 +785,16 @@ int enqueue_full(Ctx* c, Pop* p, gp_handle cases_h, const CaseSet* cs, Launch L,
                 pl->graph = nullptr;
             }
             hipGraph_t g = nullptr;
+            // every replay sets the counters back for the next: none is captured setting them first
+            if (!pl->counters_set) RC(set_counters(c, p, pl, s));
             HIPC(c, hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
             int64_t dummy = 0;
-            int rc = enqueue_body(c, p, cs, pl, s, &dummy, false);
+            int rc = enqueue_body(c, p, cs, pl, s, &dummy, false, nullptr);
             hipError_t e2 = hipStreamEndCapture(s, &g);
-            if (rc != GP_OK) {
+            if (rc != GP_OK || e2 != hipSuccess) {
+                pl->counters_set = false;
                 if (g) (void)hipGraphDestroy(g);
-                return rc;
+                RC(rc);
             }
             HIPC(c, e2);
             hipError_t e3 = hipGraphInstantiate(&pl->graph, g, nullptr, nullptr, 0);
@@ -774,6 +802,7 @@ int enqueue_full(Ctx* c, Pop* p, gp_handle cases_h, const CaseSet* cs, Launch L,
             HIPC(c, e3);
             pl->graph_cases = cases_h;
         }
+        if (!pl->counters_set) RC(set_counters(c, p, pl, s));
         HIPC(c, hipGraphLaunch(pl->graph, s));
         if (launches) *launches += 1;
     }
@@ -834,7 +863,7 @@ int enqueue_promoted(Ctx* c, Pop* p, const Pop* src, gp_handle cases_h, const Ca
         RC(dev_alloc(c, pl.pending, pend.size() * sizeof(int32_t)));
         RC(dev_alloc(c, pl.cursor, kCursors * kCursorStride * sizeof(unsigned int)));
         pl.grid = (int)std::max<int64_t>(1, std::min<int64_t>(resident_grid(c, v, pl.waves_per_cu), pl.n_items));
-        RC(enqueue_body(c, p, cs, &pl, s, nullptr, false));
+        RC(enqueue_body(c, p, cs, &pl, s, nullptr, false, nullptr));
     } else {
         // every child is one reused chunk (a whole subtree of a parent): nothing runs but the fitness
         HIPC(c, launch_fitness(p->vtype, fit_params(p, cs), p->n_trees, s));
@@ -1615,24 +1644,40 @@ static int lookup(gp_ctx* ctx, gp_handle pop, gp_handle cases, Pop** p, CaseSet*
 class ResultCopies {
 public:
     explicit ResultCopies(Ctx* c) : c_(c) {}
-    void add(void* dst, const void* src, int64_t rows, int64_t row_bytes, int64_t src_row_bytes, bool to_host)
+    // The array's index for target(), -1 when there is nothing to copy.
+    int add(void* dst, const void* src, int64_t rows, int64_t row_bytes, int64_t src_row_bytes, bool to_host)
     {
-        if (dst && rows > 0 && row_bytes > 0) a_[n_++] = Arr{dst, src, rows, row_bytes, src_row_bytes, to_host, -1};
+        if (!dst || rows <= 0 || row_bytes <= 0) return -1;
+        a_[n_] = Arr{dst, src, rows, row_bytes, src_row_bytes, to_host, -1, nullptr, false};
+        Arr& a = a_[n_];
+        const int64_t bytes = rows * row_bytes;
+        a.cpu = to_host && host_writes(dst);
+        if (a.cpu && used_ + bytes <= (int64_t)kStageBytes && stage()) {
+            a.at = used_;
+            used_ += (bytes + 15) & ~int64_t(15);
+            a.kernel_dst = c_->stage + a.at;
+        } else if (!to_host && on_device(dst, bytes)) {
+            a.kernel_dst = dst;
+        }
+        return n_++;
+    }
+    // Where a kernel of the caller's may write array i itself, in units of
+    // `align` bytes (enqueue() then leaves it out); null if it may not.
+    void* target(int i, size_t align)
+    {
+        if (i < 0 || ((uintptr_t)a_[i].kernel_dst & (align - 1)) != 0) return nullptr;
+        a_[i].written = a_[i].kernel_dst != nullptr;
+        return a_[i].kernel_dst;
     }
     int enqueue()
     {
         PackParams p{};
         for (int i = 0; i < n_; ++i) {
             Arr& a = a_[i];
-            const int64_t bytes = a.rows * a.row_bytes;
-            const bool cpu = a.to_host && host_writes(a.dst);
-            if (cpu && used_ + bytes <= (int64_t)kStageBytes && stage()) {
-                a.at = used_;
-                used_ += (bytes + 15) & ~int64_t(15);
-                pack_part(p, a.src, c_->stage + a.at, a.rows, a.row_bytes, a.src_row_bytes);
-            } else if (!a.to_host && on_device(a.dst, bytes)) {
-                pack_part(p, a.src, a.dst, a.rows, a.row_bytes, a.src_row_bytes);
-            } else if (cpu && a.row_bytes != a.src_row_bytes && stage()) {
+            if (a.written) continue;
+            if (a.kernel_dst) {
+                pack_part(p, a.src, a.kernel_dst, a.rows, a.row_bytes, a.src_row_bytes);
+            } else if (a.cpu && a.row_bytes != a.src_row_bytes && stage()) {
                 a.at = -2;                     // packed in finish()
             } else {
                 HIPC(c_, hipMemcpy2DAsync(a.dst, a.row_bytes, a.src, a.src_row_bytes, a.row_bytes, a.rows,
@@ -1669,6 +1714,9 @@ private:
         int64_t rows, row_bytes, src_row_bytes;
         bool to_host;
         int64_t at;                            // offset in the stage; -1 copied already, -2 packed in finish()
+        void* kernel_dst;                      // where a kernel writes it, or null
+        bool written;                          // by a kernel of the caller's
+        bool cpu = false;                      // for the host, in memory this thread may write
     };
     bool stage()
     {
@@ -1726,14 +1774,20 @@ int gp_evaluate_full(gp_ctx* ctx, gp_handle pop, gp_handle cases, uint32_t flags
     const bool per_tree = (flags & GP_PER_TREE) != 0;
     const bool graph = !(flags & GP_NO_GRAPH);
     int64_t launches = 0;
-    HIPC(ctx, hipEventRecord(ctx->ev0, ctx->stream));
-    RC(enqueue_full(ctx, p, cases, cs, L, per_tree, graph, ctx->stream, &launches, !graph));
-    HIPC(ctx, hipEventRecord(ctx->ev1, ctx->stream));
     const size_t esz = p->vtype == GP_BOOL ? 8 : 4;
-    ResultCopies rc(ctx);
     const bool host = !(flags & GP_DEVICE_PTR);
-    rc.add(root_out, p->vecs.p, p->n_trees, cs->n_elems * esz, cs->stride * esz, host);
-    rc.add(fitness_out, p->fit.p, 1, p->n_trees * 8, p->n_trees * 8, host);
+    HIPC(ctx, hipEventRecord(ctx->ev0, ctx->stream));
+    RC(ensure_eval_buffers(ctx, p, cs));
+    ResultCopies rc(ctx);
+    const int rows = rc.add(root_out, p->vecs.p, p->n_trees, cs->n_elems * esz, cs->stride * esz, host);
+    const int fits = rc.add(fitness_out, p->fit.p, 1, p->n_trees * 8, p->n_trees * 8, host);
+    FullOut out;
+    if (!per_tree) {
+        out.rows = rc.target(rows, esz);
+        out.fit = rc.target(fits, 8);
+    }
+    RC(enqueue_full(ctx, p, cases, cs, L, per_tree, graph, ctx->stream, &launches, !graph, &out));
+    HIPC(ctx, hipEventRecord(ctx->ev1, ctx->stream));
     RC(rc.enqueue());
     float ms = 0.f, kms = 0.f;
     if (!(flags & GP_ASYNC)) {
@@ -2528,7 +2582,7 @@ int gp_autotune(gp_ctx* ctx, gp_handle pop, gp_handle cases, int* best_variant, 
                 RC(rechunk(ctx, p, cn, &q));
                 p = replace_population(ctx, pop, p, q);
             }
-            RC(enqueue_full(ctx, p, cases, cs, L, false, true, ctx->stream, nullptr));   // warm-up + capture
+            RC(enqueue_full(ctx, p, cases, cs, L, false, true, ctx->stream, nullptr));   // warm-up
             HIPC(ctx, hipEventRecord(ctx->ev0, ctx->stream));
             RC(enqueue_full(ctx, p, cases, cs, L, false, true, ctx->stream, nullptr));
             HIPC(ctx, hipEventRecord(ctx->ev1, ctx->stream));
@@ -2553,7 +2607,7 @@ int gp_autotune(gp_ctx* ctx, gp_handle pop, gp_handle cases, int* best_variant, 
             if (c <= std::max<int64_t>(256, 4 * mean)) chunk_sizes.push_back(c);
     }
     auto time_variant = [&](Pop* q, Launch L, float* out) -> int {
-        RC(enqueue_full(ctx, q, cases, cs, L, false, true, ctx->stream, nullptr));   // warm-up + capture
+        RC(enqueue_full(ctx, q, cases, cs, L, false, true, ctx->stream, nullptr));   // warm-up
         float tmin = 1e30f;
         for (int r = 0; r < 3; ++r) {
             HIPC(ctx, hipEventRecord(ctx->ev0, ctx->stream));

@@ -71,3 +71,35 @@ def test_boolean_results_to_host_and_device(ctx, n_trees, k):
     assert np.array_equal(ctx.fitness(ch, g.GP_BOOL, want_r), want_f)
     ctx.free(ph)
     ctx.free(ch)
+
+
+# one tree of many chunks: more counters to set back than a block per row covers; 300 trees: a block per tree
+@pytest.mark.parametrize("vt", ["f32", "bool"])
+@pytest.mark.parametrize("n_trees,n_nodes", [(1, 200001), (300, 301)])
+def test_every_run_sets_its_counters_back(ctx, vt, n_trees, n_nodes):
+    from paper_2205_03251_amd import gpeval as g
+    if vt == "f32":
+        t, cases = g.GP_F32, gen.float_cases(22, 97)
+        pop = gen.sized_population(21, n_trees, n_nodes, n_nodes)
+        with np.errstate(all="ignore"):
+            want_r, want_f = oracle.eval_population_f32(pop, cases.x, cases.y)
+        ch, T = ctx.set_cases(t, cases.x, cases.y), 97
+        ph = ctx.load_population(t, pop.ops, pop.offsets, chunk_nodes=64)
+    else:
+        t, cases = g.GP_BOOL, gen.bool_cases(8)
+        pop = gen.sized_population(21, n_trees, n_nodes, n_nodes, n_terms=8, vtype=gen.VT_BOOL)
+        want_r, want_f = oracle.eval_population_bool(pop, cases.inputs, cases.target, cases.T)
+        ch, T = ctx.set_cases(t, cases.inputs, cases.target, n_cases=cases.T), cases.T
+        ph = ctx.load_population(t, pop.ops, pop.offsets, n_inputs=8, chunk_nodes=64)
+    for kw in ({}, {}, {"per_tree": True}, {"graph": False}, {"per_tree": True}, {"per_tree": True, "graph": False},
+               {"device": True}, {}):
+        r, f, _ = ctx.evaluate_full(ph, ch, t, n_trees, T, **kw)
+        if kw.get("device"):
+            r, f = r.cpu().numpy().view(want_r.dtype), f.cpu().numpy()
+        if vt == "f32":
+            assert same(r, want_r), kw
+            assert ((f == want_f) | (np.isnan(f) & np.isnan(want_f))).all(), kw
+        else:
+            assert np.array_equal(r, want_r) and np.array_equal(f, want_f), kw
+    ctx.free(ph)
+    ctx.free(ch)
