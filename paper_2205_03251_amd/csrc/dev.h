@@ -225,7 +225,7 @@ struct IxParams {
     int32_t* parent;                    // [n], tree-local, -1 at a root
     uint8_t* sn;                        // [n] Strahler numbers (0 in invalid trees), or null
     uint8_t* bempty;                    // [n_blocks + 1]: the Strahler pass marked nothing in the block
-    int32_t* bad_offsets;               // set to 1 when offsets are not 0..n, non-decreasing
+    int32_t* bad_offsets;               // two words: 1 when offsets are not 0..n, non-decreasing; a Strahler pass's count
 };
 
 hipError_t launch_index(const IxParams& q, int32_t* bsum, int64_t n_blocks, const int64_t* host_len,
@@ -260,12 +260,13 @@ constexpr int64_t kIxStaticWords = kIxStaticBempty + ix_round64((kIxStaticBlocks
 // must be current), looked up once per device; hipSuccess or the lookup's
 // error.
 hipError_t ix_static_scratch(int device, int32_t** out);
-// 1 at a terminal and 2 at a function of a valid tree (every function has two children of at least 1), 0 else.
-hipError_t launch_strahler_init(const IxParams& q, hipStream_t s);
-// One level: raises to level + 1 every node with a function below it whose children are both at level or
-// more; sets *any when there is such a function.  Reuses el and boff.
-// Pass `level` of the Strahler numbers; afterwards boff[n_blocks] holds the
-// number of functions it marked (none: the numbers are final).
+// The Strahler numbers of the nodes whose subtrees end in their block of
+// kIxBlock positions (0 in invalid trees), and lower bounds of the others';
+// with one block that is all.
+hipError_t launch_strahler_init(const IxParams& q, int64_t n_blocks, hipStream_t s);
+// Pass `level` over the nodes that are left (n_blocks > 1).  Reuses el and
+// boff; afterwards bad_offsets[1] holds what it counted (none: the numbers are
+// final).
 hipError_t launch_strahler_level(const IxParams& q, int level, int32_t* bsum, int64_t n_blocks, hipStream_t s);
 hipError_t launch_coeval(int vtype, const CoParams& p, int64_t n_children, hipStream_t s);
 // One generation's random choices (Section 6.3): per slot i, the winners of

@@ -15,7 +15,8 @@
 // LDS; the few that leave the block continue in a min-tree of E (level 0 is
 // E, each entry of level l the minimum of a group of kIxFan entries of level
 // l - 1, so a search step reads one 64-byte group).  On request the Strahler
-// number of every node follows, one level per pass over the subtree ranges.
+// number of every node follows, one level per pass over the subtree ranges,
+// first within each block and then for the subtrees that leave theirs.
 #include <algorithm>
 #include <mutex>
 
@@ -255,10 +256,10 @@ __global__ __launch_bounds__(256) void k_ix_scan(IxParams q, int32_t* bsum)
 // Exclusive prefix of the block totals bsum[0 .. nb) into boff, boff[nb] =
 // their sum (E(n) after the position scan), and el[nb * kIxBlock] = 0 so that
 // E(n) = el[n] + boff[n / kIxBlock] also when n is a multiple of the block.
-// Three launches: the prefix within each group of kIxBlock totals (a
-// workgroup per group, 16 a thread), whose sum then replaces the group's
-// first total (read by then); the group sums scanned in place by one
-// workgroup; each group's offset added.  bsum is left clobbered.
+// One launch for a single group of kIxBlock totals, three for more: the prefix
+// within each group (a workgroup per group, 16 a thread), whose sum then
+// replaces the group's first total (read by then); the group sums scanned in
+// place by one workgroup; each group's offset added.  bsum is left clobbered.
 __global__ __launch_bounds__(256) void k_ix_top_local(IxParams q, int32_t* bsum, int64_t nb)
 {
     __shared__ int32_t wtot[4];
@@ -284,6 +285,13 @@ __global__ __launch_bounds__(256) void k_ix_top_local(IxParams q, int32_t* bsum,
 #pragma unroll
     for (int j = 0; j < 16; ++j)
         if (i0 + j < nb) q.boff[i0 + j] = excl + pre[j];
+    if (gridDim.x == 1) {
+        if (tid == 255) {
+            q.boff[nb] = excl + run;
+            q.el[nb * kIxBlock] = 0;
+        }
+        return;
+    }
     __syncthreads();                          // every total of the group read
     if (tid == 255) bsum[g0] = excl + run;
 }
@@ -323,8 +331,8 @@ static hipError_t launch_top(const IxParams& q, int32_t* bsum, int64_t nb, hipSt
     const int64_t ng = (nb + kIxBlock - 1) / kIxBlock;
     if (ng > kIxTopGroups) return hipErrorInvalidValue;
     hipLaunchKernelGGL(k_ix_top_local, dim3((unsigned)ng), dim3(256), 0, s, q, bsum, nb);
-    hipLaunchKernelGGL(k_ix_top_groups, dim3(1), dim3(kIxTopGroups), 0, s, q, bsum, nb);
     if (ng > 1) {
+        hipLaunchKernelGGL(k_ix_top_groups, dim3(1), dim3(kIxTopGroups), 0, s, q, bsum, nb);
         const int64_t grid = std::min<int64_t>(65536, (nb - kIxBlock + 255) / 256);
         hipLaunchKernelGGL(k_ix_top_add, dim3((unsigned)grid), dim3(256), 0, s, q, (const int32_t*)bsum, nb);
     }
@@ -371,37 +379,6 @@ __device__ __forceinline__ void ix_bytes16(const uint8_t* p, int64_t k0, int64_t
         w[0] = w[1] = w[2] = w[3] = 0;
         for (int j = 0; j < 16; ++j)
             if (k0 + j < n) w[j >> 2] |= (uint32_t)p[k0 + j] << (8 * (j & 3));
-    }
-}
-
-// The positions of one thread: 16 consecutive ones, walking the trees they
-// fall in.  body(k, t, s, e, op, ek) runs for each position k inside a
-// well-formed tree t = [s, e), with k's opcode byte op and E(k); other(k) for
-// the rest.  The opcodes come in one 16-byte load and E is carried along from
-// E(k0) by the steps, so the walk itself reads nothing per position.
-template <class Body, class Other>
-__device__ __forceinline__ void ix_positions(const IxParams& q, Body body, Other other)
-{
-    const int64_t k0 = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 16;
-    if (k0 >= q.n) return;
-    uint32_t w[4];
-    ix_bytes16(q.ops, k0, q.n, w);
-    int32_t ek = ix_e(q, k0);
-    int64_t t = ix_tree_of(q, k0);
-    int64_t s = q.offsets[t], e = q.offsets[t + 1];
-    for (int j = 0; j < 16; ++j) {
-        const int64_t k = k0 + j;
-        if (k >= q.n) break;
-        const uint32_t wj = j < 8 ? (j < 4 ? w[0] : w[1]) : (j < 12 ? w[2] : w[3]);
-        const uint8_t op = (uint8_t)(wj >> (8 * (j & 3)));
-        while (k >= e && t + 1 < q.n_trees) {
-            ++t;
-            s = q.offsets[t];
-            e = q.offsets[t + 1];
-        }
-        if (0 <= s && s <= k && k < e && e <= q.n) body(k, t, s, e, op, ek);
-        else other(k);
-        ek += (op & 0x80) ? 1 : -1;
     }
 }
 
@@ -730,55 +707,53 @@ __device__ __forceinline__ void ix_block_trees(const IxParams& q, int64_t b, int
 // iff its subtree holds a function whose two children both have at least k
 // (numbers never decrease towards the root, and a node whose children differ
 // takes the larger).  Pass k marks those functions, counts them with a prefix
-// sum over positions (kept in el/boff, whose E values the ends and parents no
-// longer need), and raises every function whose subtree range holds one.
-__global__ __launch_bounds__(256) void k_ix_sinit(IxParams q)
+// sum over positions, and raises every function whose subtree range holds one.
+//
+// k_ix_sblock runs the passes of one block of positions in LDS, all levels in
+// one launch.  That settles every node whose subtree ends inside the block;
+// the open ones (about 2 in a hundred of a random tree's functions) hold the
+// largest number among their descendants in the block.  k_ix_sopen adds the
+// descendants in the block where the subtree ends, and the passes over the
+// whole population (k_ix_sflag, k_ix_supd) are left with the open nodes and
+// with a count of one, in front of a whole block's, for a block that holds a
+// number above the pass's level.  At 200 trees of 1000 to 300000 nodes (10
+// million) a pass over all nodes took 30 to 95 us, the reading of all numbers
+// and the prefix of marks being most of it, and 40 more for the host's look at
+// its count; now k_ix_sblock takes 62 us, k_ix_sopen 21 and a pass 20 to 25, all
+// latency.  The whole index with numbers: 958 -> 635 us.
+
+// The open nodes (a bit for each position of a group of 16), the largest
+// number in a block before each of its groups and in each block: after the
+// blocks' first trees in the min-tree's storage, which has a word for each
+// group (n > kIxBlock).
+struct IxOpen {
+    uint16_t* open;
+    uint8_t* before;
+    uint8_t* bmax;
+};
+
+__device__ __forceinline__ IxOpen ix_open(const IxParams& q)
 {
-    const int64_t k0 = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 16;
-    if (k0 + 16 <= q.n && (((uintptr_t)(q.sn + k0)) & 15) == 0) {
-        // 16 positions in one tree: the numbers from the opcode bytes at once
-        int64_t lo, hi;
-        ix_block_trees(q, k0 / kIxBlock, lo, hi);
-        const int64_t t = ix_tree_in(q, lo, hi, k0);
-        const int64_t s = q.offsets[t], e = q.offsets[t + 1];
-        if (0 <= s && s <= k0 && k0 + 16 <= e && e <= q.n) {
-            uint32_t w[4];
-            ix_bytes16(q.ops, k0, q.n, w);
-            const bool ok = q.valid[t] != 0;
-            uint32_t v[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) v[i] = ok ? ((w[i] & 0x80808080u) >> 7) + 0x01010101u : 0u;
-            *(uint4*)(q.sn + k0) = make_uint4(v[0], v[1], v[2], v[3]);
-            return;
-        }
-    }
-    ix_positions(
-        q,
-        [&](int64_t k, int64_t t, int64_t, int64_t, uint8_t op, int32_t) {
-            q.sn[k] = q.valid[t] ? ((op & 0x80) ? 2 : 1) : 0;               // a function is at least 2
-        },
-        [&](int64_t k) { q.sn[k] = 0; });
+    const int64_t nb = (q.n + kIxBlock - 1) / kIxBlock, ng = (q.n + 15) / 16;
+    IxOpen o;
+    o.open = (uint16_t*)(q.seg + nb);
+    o.before = (uint8_t*)(o.open + ng);
+    o.bmax = o.before + ng;
+    return o;
 }
 
-// Positions of this thread's 16 that hold a function still at level: only
-// they can be marked or raised, and a thread with none skips the tree lookup.
-__device__ __forceinline__ uint32_t ix_at_level(const IxParams& q, int64_t k0, int level, uint32_t (&sn)[4])
+// The larger of each byte pair (values below 128).
+__device__ __forceinline__ uint32_t ix_max8(uint32_t a, uint32_t b)
 {
-    uint32_t ops[4];
-    ix_bytes16(q.ops, k0, q.n, ops);
-    ix_bytes16(q.sn, k0, q.n, sn);
-    uint32_t m = 0;
-    for (int j = 0; j < 16; ++j) {
-        const uint32_t o = (ops[j >> 2] >> (8 * (j & 3))) & 0xffu, v = (sn[j >> 2] >> (8 * (j & 3))) & 0xffu;
-        if (k0 + j < q.n && (o & 0x80u) && v == (uint32_t)level) m |= 1u << j;
-    }
-    return m;
+    const uint32_t ge = ((a | 0x80808080u) - b) & 0x80808080u;
+    const uint32_t m = ge - (ge >> 7);
+    return (a & m) | (b & ~m);
 }
 
-__device__ __forceinline__ uint32_t ix_at_level(const IxParams& q, int64_t k0, int level)
+__device__ __forceinline__ uint32_t ix_max_of(uint32_t a)
 {
-    uint32_t sn[4];
-    return ix_at_level(q, k0, level, sn);
+    a = ix_max8(a, a >> 16);
+    return ix_max8(a, a >> 8) & 0xffu;
 }
 
 // end[k0 .. k0 + 16), with four 16-byte loads where aligned (k0 + 16 <= n).
@@ -819,54 +794,263 @@ __device__ __forceinline__ void ix_each_from(const IxParams& q, int64_t k0, uint
     }
 }
 
+// The passes of one block in LDS.  Bound by the chain of a tree's lookup, the
+// loads and four barriers a level, not by its 6 bytes a node (0.8 TB/s):
+// eight blocks of 256 threads on a compute unit hide part of it, so the dense
+// level 2 stands apart (inside the loop its unpacked ends are kept for all
+// levels: 123 registers against 50, half the blocks, 78 us against 62).
+__global__ __launch_bounds__(256) void k_ix_sblock(IxParams q)
+{
+    __shared__ uint4 s_num[kIxBlock / 16];       // the numbers, a byte each
+    __shared__ uint4 s_endv[kIxBlock / 8];       // subtree ends in the block, 16 bits each (kIxBlock: there or beyond)
+    __shared__ int32_t s_pre[257];               // marked before a group of 16
+    __shared__ uint32_t s_bits[257];             // marked in it
+    __shared__ int32_t wtot[4];
+    uint8_t* num = (uint8_t*)s_num;
+    uint16_t* ends = (uint16_t*)s_endv;
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, p0 = tid * 16;
+    const int64_t B = (int64_t)blockIdx.x * kIxBlock, k0 = B + p0;
+    uint32_t sn[4] = {0u, 0u, 0u, 0u}, xs[8];
+    uint32_t at = 0, open = 0;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) xs[j] = (uint32_t)(p0 + 2 * j + 1) | ((uint32_t)(p0 + 2 * j + 2) << 16);
+    if (k0 < q.n) {
+        int64_t lo, hi;
+        ix_block_trees(q, blockIdx.x, lo, hi);
+        int64_t t = ix_tree_in(q, lo, hi, k0);
+        int64_t s = q.offsets[t], e = q.offsets[t + 1];
+        bool ok = q.valid[t] != 0;
+        if (0 <= s && s <= k0 && k0 + kIxFan <= e && e <= q.n) {         // all 16 in one tree
+            if (ok) {
+                uint32_t ops[4];
+                ix_bytes16(q.ops, k0, q.n, ops);
+                const int32_t sb = (int32_t)max<int64_t>(s - B, -INT32_MAX), eb = (int32_t)min<int64_t>(e - B, INT32_MAX);
+                int32_t en[kIxFan];
+                ix_ends16(q, k0, en);
+#pragma unroll
+                for (int j = 0; j < kIxFan; ++j) {
+                    const int32_t x = sb + min(en[j], INT32_MAX - kIxBlock);
+                    if (x > p0 + j && x <= eb) {
+                        const uint32_t f = (ops[j >> 2] >> (8 * (j & 3) + 7)) & 1u;
+                        sn[j >> 2] |= (f + 1u) << (8 * (j & 3));         // a function is at least 2
+                        at |= f << j;
+                        if (x > kIxBlock) open |= 1u << j;
+                        const uint32_t xl = (uint32_t)min(x, kIxBlock);
+                        xs[j >> 1] = (j & 1) ? (xs[j >> 1] & 0xffffu) | (xl << 16) : (xs[j >> 1] & 0xffff0000u) | xl;
+                    }
+                }
+            }
+        } else {
+            // through LDS, one position at a time
+            s_num[tid] = make_uint4(0u, 0u, 0u, 0u);
+            s_endv[2 * tid] = make_uint4(xs[0], xs[1], xs[2], xs[3]);
+            s_endv[2 * tid + 1] = make_uint4(xs[4], xs[5], xs[6], xs[7]);
+#pragma unroll 1
+            for (int j = 0; j < kIxFan && k0 + j < q.n; ++j) {
+                const int64_t k = k0 + j;
+                while (k >= e && t + 1 < q.n_trees) {
+                    ++t;
+                    s = q.offsets[t];
+                    e = q.offsets[t + 1];
+                    ok = q.valid[t] != 0;
+                }
+                if (ok && 0 <= s && s <= k && k < e && e <= q.n) {
+                    const int64_t x = s - B + q.end[k];
+                    if (x > p0 + j && x <= e - B) {
+                        const uint32_t f = q.ops[k] >> 7;
+                        num[p0 + j] = (uint8_t)(f + 1u);
+                        ends[p0 + j] = (uint16_t)min<int64_t>(x, kIxBlock);
+                        at |= f << j;
+                        if (x > kIxBlock) open |= 1u << j;
+                    }
+                }
+            }
+            const uint4 v = s_num[tid], x0 = s_endv[2 * tid], x1 = s_endv[2 * tid + 1];
+            sn[0] = v.x, sn[1] = v.y, sn[2] = v.z, sn[3] = v.w;
+            xs[0] = x0.x, xs[1] = x0.y, xs[2] = x0.z, xs[3] = x0.w;
+            xs[4] = x1.x, xs[5] = x1.y, xs[6] = x1.z, xs[7] = x1.w;
+        }
+    }
+    s_num[tid] = make_uint4(sn[0], sn[1], sn[2], sn[3]);
+    s_endv[2 * tid] = make_uint4(xs[0], xs[1], xs[2], xs[3]);
+    s_endv[2 * tid + 1] = make_uint4(xs[4], xs[5], xs[6], xs[7]);
+    if (tid == 0) s_bits[256] = 0;
+    __syncthreads();
+    // `at`: this thread's functions at the level, the only ones that can be marked or raised
+    uint32_t bits = 0;
+    int32_t excl = 0;                                                    // marked in the block before p0
+    // the prefix of the marks; false when the block has none
+    const auto count = [&]() -> bool {
+        if (!__syncthreads_or(bits != 0)) return false;
+        const int32_t run = __popc(bits);
+        int32_t incl = run;
+        for (int o = 1; o < 64; o <<= 1) {
+            const int32_t y = __shfl_up(incl, o, 64);
+            if (lane >= o) incl += y;
+        }
+        if (lane == 63) wtot[w] = incl;
+        __syncthreads();
+        excl = incl - run;
+        for (int i = 0; i < w; ++i) excl += wtot[i];
+        s_pre[tid] = excl;
+        s_bits[tid] = bits;
+        if (tid == 255) s_pre[256] = excl + run;
+        __syncthreads();
+        return true;
+    };
+    // marks in [p0 + j, x)
+    const auto marked = [&](int j, uint32_t x) -> bool {
+        return s_pre[x >> 4] + __popc(s_bits[x >> 4] & ((1u << (x & 15)) - 1u)) > excl + __popc(bits & ((1u << j) - 1u));
+    };
+    const auto raise = [&](uint32_t raised) {
+        if (raised) {
+#pragma unroll
+            for (int j = 0; j < kIxFan; ++j) sn[j >> 2] += ((raised >> j) & 1u) << (8 * (j & 3));
+            s_num[tid] = make_uint4(sn[0], sn[1], sn[2], sn[3]);
+        }
+        at = raised;
+        __syncthreads();
+    };
+    // level 2, where every function is: all 16 positions at once
+    {
+        const uint32_t x16 = tid < 255 ? ends[p0 + 16] : (uint32_t)kIxBlock, n16 = tid < 255 ? num[p0 + 16] : 0u;
+        uint32_t nr[kIxFan];                                             // the right children's numbers
+#pragma unroll
+        for (int j = 0; j < kIxFan; ++j) {
+            const uint32_t r = j + 1 < kIxFan ? (xs[(j + 1) >> 1] >> (16 * ((j + 1) & 1))) & 0xffffu : x16;
+            nr[j] = r < kIxBlock ? num[r] : 0u;
+        }
+#pragma unroll
+        for (int j = 0; j < kIxFan; ++j) {
+            const uint32_t nl = j + 1 < kIxFan ? (sn[(j + 1) >> 2] >> (8 * ((j + 1) & 3))) & 0xffu : n16;
+            if (nl >= 2 && nr[j] >= 2) bits |= 1u << j;
+        }
+        bits &= at;
+        if (count()) {
+            uint32_t raised = 0;
+#pragma unroll
+            for (int j = 0; j < kIxFan; ++j)
+                if (marked(j, (xs[j >> 1] >> (16 * (j & 1))) & 0xffffu)) raised |= 1u << j;
+            raise(raised & at);
+        } else {
+            at = 0;
+        }
+    }
+    for (uint32_t level = 3; level < 64; ++level) {
+        bits = 0;
+        for (uint32_t m = at; m; m &= m - 1) {
+            const int j = __ffs(m) - 1, l = p0 + j + 1;
+            const int r = l < kIxBlock ? ends[l] : kIxBlock;             // the right child
+            if (r < kIxBlock && num[l] >= level && num[r] >= level) bits |= 1u << j;
+        }
+        if (!count()) break;
+        uint32_t raised = 0;
+        for (uint32_t m = at; m; m &= m - 1) {
+            const int j = __ffs(m) - 1;
+            if (marked(j, ends[p0 + j])) raised |= 1u << j;
+        }
+        raise(raised);
+    }
+    if (k0 < q.n) {
+        if (k0 + 16 <= q.n && (((uintptr_t)(q.sn + k0)) & 15) == 0) {
+            *(uint4*)(q.sn + k0) = make_uint4(sn[0], sn[1], sn[2], sn[3]);
+        } else {
+#pragma unroll
+            for (int j = 0; j < kIxFan; ++j)
+                if (k0 + j < q.n) q.sn[k0 + j] = (uint8_t)(sn[j >> 2] >> (8 * (j & 3)));
+        }
+    }
+    if (gridDim.x == 1) return;                                          // nothing is open
+    const IxOpen o = ix_open(q);
+    // the largest number up to each group
+    int32_t mx = (int32_t)ix_max_of(ix_max8(ix_max8(sn[0], sn[1]), ix_max8(sn[2], sn[3])));
+    for (int d = 1; d < 64; d <<= 1) {
+        const int32_t y = __shfl_up(mx, d, 64);
+        if (lane >= d) mx = max(mx, y);
+    }
+    __syncthreads();
+    if (lane == 63) wtot[w] = mx;
+    __syncthreads();
+    int32_t before = __shfl_up(mx, 1, 64);
+    if (lane == 0) before = 0;
+    for (int i = 0; i < w; ++i) before = max(before, wtot[i]);
+    if (k0 < q.n) {
+        o.open[k0 / 16] = (uint16_t)open;
+        o.before[k0 / 16] = (uint8_t)before;
+    }
+    if (tid == 255) o.bmax[blockIdx.x] = (uint8_t)max(before, mx);
+}
+
+// The open nodes of this thread's group at `level` (at any, 0).
+__device__ __forceinline__ uint32_t ix_open_at(const IxParams& q, const IxOpen& o, int64_t k0, uint32_t level)
+{
+    const uint32_t open = k0 < q.n ? o.open[k0 / 16] : 0u;
+    if (!open || level == 0) return open;
+    uint32_t sn[4], m = 0;
+    ix_bytes16(q.sn, k0, q.n, sn);
+#pragma unroll
+    for (int j = 0; j < kIxFan; ++j)
+        if (((sn[j >> 2] >> (8 * (j & 3))) & 0xffu) == level) m |= 1u << j;
+    return m & open;
+}
+
+// Open nodes take the largest number in the block where their subtree ends,
+// up to the end: all of it is theirs.  Numbers that other threads raise in
+// the same launch count as they are read: each is some descendant's or less.
+__global__ __launch_bounds__(256) void k_ix_sopen(IxParams q)
+{
+    const int64_t k0 = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 16;
+    const IxOpen o = ix_open(q);
+    const uint32_t m = ix_open_at(q, o, k0, 0);
+    if (!m) return;
+    int64_t lo, hi;
+    ix_block_trees(q, blockIdx.x, lo, hi);
+    const int64_t t = ix_tree_in(q, lo, hi, k0);
+    ix_each_from(q, k0, m, t, q.offsets[t], q.offsets[t + 1], [&](int64_t k, int64_t s, int64_t e) {
+        const int64_t x = s + q.end[k];
+        if (x <= k || x > e || x % kIxBlock == 0) return;
+        const int64_t g = (x - 1) / 16;                                  // the last group with positions before x
+        uint32_t v[4];
+        ix_bytes16(q.sn, g * 16, q.n, v);
+        const int in = (int)(x - g * 16);
+        uint32_t a = 0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int b = in - 4 * i;                                    // bytes of this word before x
+            a = ix_max8(a, b <= 0 ? 0u : b >= 4 ? v[i] : v[i] & ((1u << (8 * b)) - 1u));
+        }
+        const uint32_t most = max(ix_max_of(a), (uint32_t)o.before[g]);
+        if (most > q.sn[k]) q.sn[k] = (uint8_t)most;
+    });
+}
+
+// A pass over the open nodes: marks those with two children at level or
+// more, with their prefix in el (its E values are not needed any more).
 __global__ __launch_bounds__(256) void k_ix_sflag(IxParams q, int level, int32_t* bsum)
 {
     __shared__ int32_t wtot[4];
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int64_t base = ((int64_t)blockIdx.x * 256 + tid) * 16;
+    const IxOpen o = ix_open(q);
     uint32_t bits = 0;
     // a function with both children at level or more is itself at level already
-    uint32_t snw[4];
-    const uint32_t m = base < q.n ? ix_at_level(q, base, level, snw) : 0u;
-    int64_t t = 0, s = 0, e = 0;
+    const uint32_t m = ix_open_at(q, o, base, (uint32_t)level);
     if (m) {
         int64_t lo, hi;
         ix_block_trees(q, blockIdx.x, lo, hi);
-        t = ix_tree_in(q, lo, hi, base);
-        s = q.offsets[t];
-        e = q.offsets[t + 1];
-    }
-    if (m && 0 <= s && s <= base && base + kIxFan < e && e <= q.n) {
-        // every position and its first child in one tree: the ends and the
-        // right children's numbers are loaded all at once
-        int32_t en[kIxFan];
-        ix_ends16(q, base, en);                                          // end[base .. base + 15]
-        const int32_t en16 = q.end[base + kIxFan];
-        const uint32_t sn16 = q.sn[base + kIxFan];
-        uint32_t snr[kIxFan];
-#pragma unroll
-        for (int j = 0; j < kIxFan; ++j) {
-            const int64_t r = s + (j + 1 < kIxFan ? en[j + 1] : en16);  // the right child of base + j
-            snr[j] = ((m >> j) & 1u) && r > base + j + 1 && r < e ? q.sn[r] : 0u;
-        }
-#pragma unroll
-        for (int j = 0; j < kIxFan; ++j) {
-            const uint32_t sl = j + 1 < kIxFan ? (snw[(j + 1) >> 2] >> (8 * ((j + 1) & 3))) & 0xffu : sn16;
-            if (((m >> j) & 1u) && sl >= (uint32_t)level && snr[j] >= (uint32_t)level) bits |= 1u << j;
-        }
-    } else {
-        ix_each_from(q, base, m, t, s, e, [&](int64_t k, int64_t s, int64_t e) {
+        const int64_t t = ix_tree_in(q, lo, hi, base);
+        ix_each_from(q, base, m, t, q.offsets[t], q.offsets[t + 1], [&](int64_t k, int64_t s, int64_t e) {
             if (k + 1 < e) {
                 const int64_t r = s + q.end[k + 1];                  // the right child
                 if (r > k + 1 && r < e && q.sn[k + 1] >= level && q.sn[r] >= level) bits |= 1u << (int)(k - base);
             }
         });
     }
-    // past the first levels most blocks mark nothing: their prefix is left
-    // unwritten and read as zero
+    const int32_t above = o.bmax[blockIdx.x] > level ? 1 : 0;
+    // most blocks mark nothing: their prefix is left unwritten and read as zero
     if (!__syncthreads_or(bits != 0)) {
         if (tid == 0) {
-            bsum[blockIdx.x] = 0;
+            bsum[blockIdx.x] = above;
             q.bempty[blockIdx.x] = 1;
         }
         return;
@@ -889,7 +1073,7 @@ __global__ __launch_bounds__(256) void k_ix_sflag(IxParams q, int level, int32_t
     for (int j = 0; j < 2; ++j)
         dst[j] = make_int4(ix_pack16(pre[8 * j], pre[8 * j + 1]), ix_pack16(pre[8 * j + 2], pre[8 * j + 3]),
                            ix_pack16(pre[8 * j + 4], pre[8 * j + 5]), ix_pack16(pre[8 * j + 6], pre[8 * j + 7]));
-    if (tid == 255) bsum[blockIdx.x] = excl + run;
+    if (tid == 255) bsum[blockIdx.x] = excl + run + above;
 }
 
 // Marked functions before position x (x <= n): a block that marked none
@@ -900,79 +1084,44 @@ __device__ __forceinline__ int32_t ix_count_before(const IxParams& q, int64_t x)
     return q.bempty[b] ? q.boff[b] : ix_e(q, x);
 }
 
-// DENSE: the first pass, where every function starts at the level, so each
-// thread has several nodes to test; later passes test few nodes per thread
-// and run the plain walk (the batched loads' registers would cost them
-// resident waves).
-template <bool DENSE>
+// Raises the open nodes at level whose range holds a mark, or a whole block
+// with a number above level (the count in front of the node's own block is
+// left out: its part from the node on is in the node's number already).
 __global__ __launch_bounds__(256) void k_ix_supd(IxParams q, int level)
 {
     const int64_t k0 = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 16;
-    if (k0 >= q.n) return;
-    // only a node at level can rise
-    uint32_t snw[4];
-    const uint32_t m = ix_at_level(q, k0, level, snw);
+    const IxOpen o = ix_open(q);
+    if (blockIdx.x == 0 && threadIdx.x == 0) q.bad_offsets[1] = q.boff[gridDim.x];
+    const uint32_t m = ix_open_at(q, o, k0, (uint32_t)level);
     if (!m) return;
     int64_t lo, hi;
-    ix_block_trees(q, k0 / kIxBlock, lo, hi);
+    ix_block_trees(q, blockIdx.x, lo, hi);
     const int64_t t = ix_tree_in(q, lo, hi, k0);
-    const int64_t s = q.offsets[t], e = q.offsets[t + 1];
-    if (DENSE && 0 <= s && s <= k0 && k0 + kIxFan <= e && e <= q.n) {
-        // all 16 positions in one tree: their ends, then the counts at the
-        // subtree ends, loaded all at once; the numbers written back together
-        int32_t en[kIxFan];
-        ix_ends16(q, k0, en);
-        int32_t cx[kIxFan];
-#pragma unroll
-        for (int j = 0; j < kIxFan; ++j) {
-            const int64_t x = s + en[j];                                 // the subtree is [k0 + j, x)
-            cx[j] = ((m >> j) & 1u) && x > k0 + j && x <= e ? ix_count_before(q, x) : INT32_MIN;
-        }
-        uint32_t raised = 0;
-#pragma unroll
-        for (int j = 0; j < kIxFan; ++j)
-            if (cx[j] != INT32_MIN && cx[j] > ix_count_before(q, k0 + j)) raised |= 1u << j;
-        if (!raised) return;
-#pragma unroll
-        for (int j = 0; j < kIxFan; ++j)
-            if ((raised >> j) & 1u)
-                snw[j >> 2] = (snw[j >> 2] & ~(0xffu << (8 * (j & 3)))) | ((uint32_t)(level + 1) << (8 * (j & 3)));
-        if ((((uintptr_t)(q.sn + k0)) & 15) == 0) {
-            *(uint4*)(q.sn + k0) = make_uint4(snw[0], snw[1], snw[2], snw[3]);
-        } else {
-#pragma unroll
-            for (int j = 0; j < kIxFan; ++j)
-                if ((raised >> j) & 1u) q.sn[k0 + j] = (uint8_t)(level + 1);
-        }
-        return;
-    }
-    ix_each_from(q, k0, m, t, s, e, [&](int64_t k, int64_t s, int64_t e) {
+    const int32_t above = o.bmax[blockIdx.x] > level ? 1 : 0;
+    ix_each_from(q, k0, m, t, q.offsets[t], q.offsets[t + 1], [&](int64_t k, int64_t s, int64_t e) {
         const int64_t x = s + q.end[k];                              // the subtree is [k, x)
-        if (x > k && x <= e && ix_count_before(q, x) > ix_count_before(q, k)) q.sn[k] = (uint8_t)(level + 1);
+        if (x > k && x <= e && ix_count_before(q, x) > ix_count_before(q, k) + above) q.sn[k] = (uint8_t)(level + 1);
     });
 }
 
-hipError_t launch_strahler_init(const IxParams& q, hipStream_t s)
+hipError_t launch_strahler_init(const IxParams& q, int64_t nb, hipStream_t s)
 {
     if (q.top > 0) {
-        const int64_t nb = (q.n + kIxBlock - 1) / kIxBlock;
         const int64_t bg = std::min<int64_t>(65536, std::max<int64_t>(1, (nb + 255) / 256));
         hipLaunchKernelGGL(k_ix_tfirst, dim3((unsigned)bg), dim3(256), 0, s, q, q.seg, nb);
     }
-    const int64_t pg = (q.n + 16 * 256 - 1) / (16 * 256);
-    hipLaunchKernelGGL(k_ix_sinit, dim3((unsigned)pg), dim3(256), 0, s, q);
+    hipLaunchKernelGGL(k_ix_sblock, dim3((unsigned)nb), dim3(256), 0, s, q);
+    if (nb > 1) hipLaunchKernelGGL(k_ix_sopen, dim3((unsigned)nb), dim3(256), 0, s, q);
     return hipGetLastError();
 }
 
 hipError_t launch_strahler_level(const IxParams& q, int level, int32_t* bsum, int64_t nb,
                                  hipStream_t s)
 {
-    const int64_t pg = (q.n + 16 * 256 - 1) / (16 * 256);
     hipLaunchKernelGGL(k_ix_sflag, dim3((unsigned)nb), dim3(256), 0, s, q, level, bsum);
     const hipError_t et = launch_top(q, bsum, nb, s);
     if (et != hipSuccess) return et;
-    if (level == 2) hipLaunchKernelGGL(k_ix_supd<true>, dim3((unsigned)pg), dim3(256), 0, s, q, level);
-    else hipLaunchKernelGGL(k_ix_supd<false>, dim3((unsigned)pg), dim3(256), 0, s, q, level);
+    hipLaunchKernelGGL(k_ix_supd, dim3((unsigned)nb), dim3(256), 0, s, q, level);
     return hipGetLastError();
 }
 

@@ -2735,7 +2735,7 @@ static int64_t ix_levels(int64_t n, IxParams& q, int64_t (&len)[kIxMaxLevels])
 
 // The index kernels on ctx's stream with the given scratch (el, boff, bsum,
 // seg sized for q.n; flag 2 words; bempty n_blocks + 1 bytes), then the host
-// waits for the offsets flag (and, per Strahler level, for the level's count).
+// waits for the offsets flag (and, every few Strahler levels, for a level's count).
 // Flags are cleared by a fill kernel.  Allocates nothing.
 static int ix_run(Ctx* ctx, IxParams& q, int32_t* bsum, int32_t* flag, int64_t nb, const int64_t* len,
                   double* device_ms, hipStream_t st)
@@ -2746,22 +2746,24 @@ static int ix_run(Ctx* ctx, IxParams& q, int32_t* bsum, int32_t* flag, int64_t n
     HIPC(ctx, launch_fill_i32(flag, 2, 0, st));
     if (q.sn) HIPC(ctx, launch_fill_u8(q.bempty, nb + 1, 1, st));      // block nb holds only E(n)
     HIPC(ctx, launch_index(q, bsum, nb, len, st));
-    if (q.sn) {
-        // one pass per level, while some function has two children at the
-        // current level (the pass leaves their number in boff[nb])
-        HIPC(ctx, launch_strahler_init(q, st));
-        for (int level = 2; level < 64; ++level) {          // the initial numbers settle level 1
-            HIPC(ctx, launch_strahler_level(q, level, bsum, nb, st));
-            int32_t more = 0;
-            HIPC(ctx, hipMemcpyAsync(&more, q.boff + nb, 4, hipMemcpyDeviceToHost, st));
-            HIPC(ctx, hipStreamSynchronize(st));
-            if (!more) break;
-        }
-    }
-    int32_t bad = 0;
-    if (device_ms) HIPC(ctx, hipEventRecord(ctx->ev1, st));
-    HIPC(ctx, hipMemcpyAsync(&bad, flag, 4, hipMemcpyDeviceToHost, st));
-    HIPC(ctx, hipStreamSynchronize(st));
+    if (q.sn) HIPC(ctx, launch_strahler_init(q, nb, st));
+    // one pass per level over the subtrees that leave their block, while it
+    // counts something.  A pass too many takes 15 to 20 us, the host's look at
+    // the count 30 to 40: two passes before the first look (combs are done after
+    // one), then three, then four (the numbers of 10 million nodes in 200 random
+    // trees reach 10, nine passes).
+    int32_t state[2] = {0, 0};                              // bad offsets, the last pass's count
+    int level = 2, ahead = 2;                               // the blocks settle level 1
+    do {
+        if (q.sn && nb > 1)
+            for (int i = 0; i < ahead && level < 64; ++i, ++level)
+                HIPC(ctx, launch_strahler_level(q, level, bsum, nb, st));
+        ++ahead;
+        if (device_ms) HIPC(ctx, hipEventRecord(ctx->ev1, st));
+        HIPC(ctx, hipMemcpyAsync(state, flag, 8, hipMemcpyDeviceToHost, st));
+        HIPC(ctx, hipStreamSynchronize(st));
+    } while (state[1] && level < 64);
+    const int32_t bad = state[0];
     if (device_ms) {
         float ms = 0.f;
         HIPC(ctx, hipEventElapsedTime(&ms, ctx->ev0, ctx->ev1));
