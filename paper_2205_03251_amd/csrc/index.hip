@@ -10,11 +10,12 @@
 // E(k) >= E(s) for s < k < e, and E(e) = E(s) - 1 (the count of open child
 // positions never runs out early and ends exhausted).  The subtree of node k
 // ends (exclusively) at the first j > k with E(j) < E(k): k + 1 for a
-// terminal.  Its parent is the last i < k with E(i) <= E(k).  Both searches
-// run per 4096-position block, in registers and in the block's minima in
-// LDS; the few that leave the block continue in a min-tree of E (level 0 is
-// E, each entry of level l the minimum of a group of kIxFan entries of level
-// l - 1, so a search step reads one 64-byte group).  On request the Strahler
+// terminal.  A function's first child follows it, the second starts where the
+// first one's subtree ends.  The searches for the ends run per 4096-position
+// block, in registers and in the block's minima in LDS; the few that leave the
+// block continue in a min-tree of E (level 0 is E, each entry of level l the
+// minimum of a group of kIxFan entries of level l - 1, so a search step reads
+// one 64-byte group).  On request the Strahler
 // number of every node follows, one level per pass over the subtree ranges,
 // first within each block and then for the subtrees that leave theirs.
 #include <algorithm>
@@ -174,37 +175,6 @@ __device__ __forceinline__ int64_t ix_first_below_at(const IxParams& q, int l, i
     while (l > 0 && hit >= 0) {
         --l;
         hit = ix_scan_group(q, l, hit * kIxFan, v);
-    }
-    return hit;
-}
-
-// Last position at or before the end of entry p of level l whose E is at
-// most v, or -1: the mirror image of ix_first_below_at.
-__device__ __forceinline__ int64_t ix_last_at_most_at(const IxParams& q, int l, int64_t p, int32_t v)
-{
-    int64_t hit = -1;
-    int32_t x[kIxFan];
-    for (;;) {
-        if (p < 0) return -1;
-        const int64_t g = p & ~(int64_t)(kIxFan - 1);
-        ix_load_group(q, l, g, x);
-#pragma unroll
-        for (int i = 0; i < kIxFan; ++i)
-            if (g + i <= p && x[i] <= v) hit = g + i;
-        if (hit >= 0) break;
-        if (l == q.top) return -1;
-        p = g / kIxFan - 1;
-        ++l;
-    }
-    while (l > 0) {
-        --l;
-        const int64_t g = hit * kIxFan, len = q.lvl[2 * l + 1];
-        ix_load_group(q, l, g, x);
-        hit = -1;
-#pragma unroll
-        for (int i = 0; i < kIxFan; ++i)
-            if (g + i < len && x[i] <= v) hit = g + i;
-        if (hit < 0) return -1;
     }
     return hit;
 }
@@ -458,16 +428,6 @@ __device__ __forceinline__ int ix_first_lt(const int32_t (&x)[kIxFan], int g, in
     return hit < kIxFan ? g + hit : -1;
 }
 
-// Last index in [g, g + upto] whose entry is at most v, or -1.
-__device__ __forceinline__ int ix_last_le(const int32_t (&x)[kIxFan], int g, int upto, int32_t v)
-{
-    int hit = -1;
-#pragma unroll
-    for (int i = 0; i < kIxFan; ++i)
-        if (i <= upto && x[i] <= v) hit = i;
-    return hit >= 0 ? g + hit : -1;
-}
-
 // First block position whose E is below v after the group of position i
 // (that group already searched), or -1.
 __device__ __forceinline__ int ix_lds_first_below(const IxBlockMins& b, int i, int32_t v)
@@ -488,26 +448,6 @@ __device__ __forceinline__ int ix_lds_first_below(const IxBlockMins& b, int i, i
     return ix_first_lt(x, kIxFan * h1, 0, v);
 }
 
-// Last block position whose E is at most v before the group of position i
-// (that group already searched), or -1.
-__device__ __forceinline__ int ix_lds_last_at_most(const IxBlockMins& b, int i, int32_t v)
-{
-    int32_t x[kIxFan];
-    const int g1 = i / kIxFan;
-    ix_lds_group(b.m1, g1 & ~(kIxFan - 1), x);
-    int h1 = ix_last_le(x, g1 & ~(kIxFan - 1), (g1 & (kIxFan - 1)) - 1, v);
-    if (h1 < 0) {
-        ix_lds_group(b.m2, 0, x);
-        const int h2 = ix_last_le(x, 0, g1 / kIxFan - 1, v);
-        if (h2 < 0) return -1;
-        ix_lds_group(b.m1, kIxFan * h2, x);
-        h1 = ix_last_le(x, kIxFan * h2, kIxFan - 1, v);
-        if (h1 < 0) return -1;
-    }
-    ix_lds_group(b.e0, kIxFan * h1, x);
-    return ix_last_le(x, kIxFan * h1, kIxFan - 1, v);
-}
-
 // tfirst[b] = the tree holding the first position of scan block b (bsum,
 // free once the block offsets are summed, holds them).
 __global__ __launch_bounds__(256) void k_ix_tfirst(IxParams q, int32_t* tfirst, int64_t nb)
@@ -518,81 +458,90 @@ __global__ __launch_bounds__(256) void k_ix_tfirst(IxParams q, int32_t* tfirst, 
 
 constexpr int kIxQueue = 1024;            // block-leaving searches shared out per workgroup
 
-// A search that left the block, continued in the global min-tree from the
-// level whose entries are whole blocks (or the top): the end (parent = false)
-// or the parent of position k of tree [s, e), whose E is v.
-__device__ __forceinline__ int32_t ix_global_link(const IxParams& q, int64_t B, int64_t k, int64_t s, int64_t e,
-                                                  int32_t v, bool parent)
+// The end of position k of tree [s, e), whose E is v, when the search left
+// the block: continued in the global min-tree from the level whose entries
+// are whole blocks (or the top).
+__device__ __forceinline__ int32_t ix_global_end(const IxParams& q, int64_t B, int64_t k, int64_t s, int64_t e,
+                                                 int32_t v)
 {
     const int L = q.top < 3 ? q.top : 3;
-    if (!parent) {
-        const int64_t J = ix_first_below_at(q, L, (B + kIxBlock) >> (4 * L), v);
-        return J > k && J <= e ? (int32_t)(J - s) : -1;
-    }
-    const int64_t P = B > 0 ? ix_last_at_most_at(q, L, (B >> (4 * L)) - 1, v) : -1;
-    return P >= s && P < k ? (int32_t)(P - s) : -1;
+    const int64_t J = ix_first_below_at(q, L, (B + kIxBlock) >> (4 * L), v);
+    return J > k && J <= e ? (int32_t)(J - s) : -1;
 }
 
+// Results of a block in LDS: a word in 16 left out, so that threads that
+// write 16 positions each and threads that read consecutive ones both spread
+// over the banks.
+__device__ __forceinline__ int ix_slot(int i) { return i + (i >> 4); }
+
 // Subtree end and parent of every position, one scan block per workgroup.
-// The end of function k is the first j > k with E(j) < E(k); its parent (any
-// non-root k) is the last i < k with E(i) <= E(k): the previous position when
-// that is a function (k is its first child), else the function whose first
-// child's subtree ends at k, since every position strictly between that
-// function and k has a larger E.  Ends, then parents: each thread settles
-// what its own positions answer (in registers); the searches that go past
-// them are listed and shared out over the workgroup, which runs them in the
-// block's minima in LDS with every lane busy (run where they arise, a wave
+// The end of function k is the first j > k with E(j) < E(k).  Each thread
+// settles what its own positions answer (in registers); the searches that go
+// past them are listed and shared out over the workgroup, which runs them in
+// the block's minima in LDS with every lane busy (run where they arise, a wave
 // would step through every search any of its lanes needs); those that leave
 // the block (for a random walk about the square root of the block's length)
 // are queued and continued in the global min-tree, and a search that finds
-// the queue full continues at once.  Results are gathered in LDS and written
-// out in whole lines: written per position, a wave's stores spread over 64
-// lines and reach memory one partial line at a time.
+// the queue full continues at once.
+//
+// Parents need no search.  A position after a function is its first child,
+// and the position where that child's subtree ends is the second: the thread
+// that holds a first child hands the parent on, through LDS, or in memory
+// where the second child lies in a later block (whose own workgroup leaves
+// the position out).  Results are gathered in LDS and written out in whole
+// lines: written per position, a wave's stores spread over 64 lines and reach
+// memory one partial line at a time.
+//
+// Bound by the searches' chains of LDS reads and by 9 bytes a node of memory.
+// 1000 trees of 10000 to 1000000 nodes (215 million), the whole index: 2.19 ms
+// with parents searched like the ends, 1.71 handed on; 10 million nodes 637 -> 608
+// us with Strahler numbers.  36 KiB of LDS: four workgroups on a compute unit.
 __global__ __launch_bounds__(256) void k_ix_links(IxParams q, const int32_t* tfirst)
 {
     __shared__ IxBlockMins bm;
     __shared__ uint16_t work[kIxBlock];       // block positions searched in the block minima
     __shared__ uint16_t queue[kIxQueue];      // block positions searched in the global min-tree
-    __shared__ int32_t res[kIxBlock];         // this pass's results, tree-local
+    __shared__ int32_t res[kIxBlock + kIxBlock / 16];         // ends, then parents, tree-local (ix_slot)
     __shared__ int32_t n_work, queued;
-    const int tid = threadIdx.x;
-    const int64_t B = (int64_t)blockIdx.x * kIxBlock, k0 = B + (int64_t)tid * kIxFan;
+    const int tid = threadIdx.x, p0 = tid * kIxFan;
+    const int64_t B = (int64_t)blockIdx.x * kIxBlock, k0 = B + p0;
     const int64_t nb = (q.n + kIxBlock - 1) / kIxBlock;
     const int64_t t_lo = tfirst[blockIdx.x], t_hi = blockIdx.x + 1 < nb ? tfirst[blockIdx.x + 1] : q.n_trees - 1;
     const int here = (int)min<int64_t>(kIxBlock, q.n - B);
     uint32_t w[4];
     ix_bytes16(q.ops, k0, q.n, w);
-    int32_t ev[kIxFan];
-    int32_t run = q.el[k0];                   // as the scan: positions past n step by 0
+    if (tid == 0) n_work = queued = 0;
+    uint64_t nxt = 0;
+    uint32_t fns = 0;                         // functions
+    {
+        int32_t ev[kIxFan];
+        int32_t run = q.el[k0];               // as the scan: positions past n step by 0
 #pragma unroll
-    for (int j = 0; j < kIxFan; ++j) {
-        ev[j] = run;
-        const uint32_t b = (w[j >> 2] >> (8 * (j & 3))) & 0xffu;
-        run += k0 + j < q.n ? ((b & 0x80u) ? 1 : -1) : 0;
-    }
-    int32_t mn = ev[0];
+        for (int j = 0; j < kIxFan; ++j) {
+            ev[j] = run;
+            const uint32_t f = (w[j >> 2] >> (8 * (j & 3) + 7)) & 1u;
+            fns |= f << j;
+            run += k0 + j < q.n ? (f ? 1 : -1) : 0;
+        }
+        int32_t mn = ev[0];
 #pragma unroll
-    for (int j = 1; j < kIxFan; ++j) mn = min(mn, ev[j]);
+        for (int j = 1; j < kIxFan; ++j) mn = min(mn, ev[j]);
 #pragma unroll
-    for (int j = 0; j < kIxFan; j += 8)
-        *(int4*)&bm.e0[tid * kIxFan + j] =
-            make_int4((ev[j] & 0xffff) | (ev[j + 1] << 16), (ev[j + 2] & 0xffff) | (ev[j + 3] << 16),
-                      (ev[j + 4] & 0xffff) | (ev[j + 5] << 16), (ev[j + 6] & 0xffff) | (ev[j + 7] << 16));
-    bm.m1[tid] = (int16_t)mn;
-    // both searches within the thread's own positions, four bits per
-    // position: the distance less one, 15 when the answer lies outside
-    uint64_t nxt = 0, prv = 0;
+        for (int j = 0; j < kIxFan; j += 8)
+            *(int4*)&bm.e0[p0 + j] =
+                make_int4((ev[j] & 0xffff) | (ev[j + 1] << 16), (ev[j + 2] & 0xffff) | (ev[j + 3] << 16),
+                          (ev[j + 4] & 0xffff) | (ev[j + 5] << 16), (ev[j + 6] & 0xffff) | (ev[j + 7] << 16));
+        bm.m1[tid] = (int16_t)mn;
+        // the search within the thread's own positions, four bits per
+        // position: the distance less one, 15 when the answer lies outside
 #pragma unroll
-    for (int j = 0; j < kIxFan; ++j) {
-        uint32_t f = 15, b = 15;
+        for (int j = 0; j < kIxFan; ++j) {
+            uint32_t f = 15;
 #pragma unroll
-        for (int m = kIxFan - 1; m > j; --m)
-            if (ev[m] < ev[j]) f = (uint32_t)(m - j - 1);
-#pragma unroll
-        for (int m = 0; m < j; ++m)
-            if (ev[m] <= ev[j]) b = (uint32_t)(j - m - 1);
-        nxt |= (uint64_t)f << (4 * j);
-        prv |= (uint64_t)b << (4 * j);
+            for (int m = kIxFan - 1; m > j; --m)
+                if (ev[m] < ev[j]) f = (uint32_t)(m - j - 1);
+            nxt |= (uint64_t)f << (4 * j);
+        }
     }
     __syncthreads();
     if (tid < kIxFan) {
@@ -601,89 +550,124 @@ __global__ __launch_bounds__(256) void k_ix_links(IxParams q, const int32_t* tfi
         bm.m2[tid] = (int16_t)x;
     }
     const int32_t boff = q.boff[blockIdx.x];
-    for (int pass = 0; pass < 2; ++pass) {
-        const bool parent = pass == 1;
-        if (tid == 0) n_work = queued = 0;
-        __syncthreads();
-        if (k0 < q.n) {
-            const uint64_t near = parent ? prv : nxt;
-            int64_t t = ix_tree_in(q, t_lo, t_hi, k0);
-            int64_t s = q.offsets[t], e = q.offsets[t + 1];
-            bool ok = q.valid[t] != 0;
-            const bool one_tree = ok && 0 <= s && s <= k0 && k0 + kIxFan <= e && e <= q.n;
-            if (one_tree) {
-                // the common case: all 16 positions in one valid tree
-                const int32_t base = (int32_t)(k0 - s);
+    int64_t t0 = 0, s0 = 0, e0 = 0;           // the tree of the thread's first position
+    bool one_tree = false;                    // the common case: all 16 positions in one valid tree
+    if (k0 < q.n) {
+        t0 = ix_tree_in(q, t_lo, t_hi, k0);
+        s0 = q.offsets[t0];
+        e0 = q.offsets[t0 + 1];
+        one_tree = q.valid[t0] != 0 && 0 <= s0 && s0 <= k0 && k0 + kIxFan <= e0 && e0 <= q.n;
+    }
+    // the other threads' positions, one at a time: body(j, k, in a valid tree, its start and end)
+    const auto each = [&](auto body) {
+        int64_t t = t0, s = s0, e = e0;
+        bool ok = q.valid[t] != 0;
+#pragma unroll 1
+        for (int j = 0; j < kIxFan; ++j) {
+            const int64_t k = k0 + j;
+            if (k >= q.n) break;
+            while (k >= e && t + 1 < q.n_trees) {
+                ++t;
+                s = q.offsets[t];
+                e = q.offsets[t + 1];
+                ok = q.valid[t] != 0;
+            }
+            body(j, k, ok && 0 <= s && s <= k && k < e && e <= q.n, s, e);
+        }
+    };
+    const auto fn_at = [&](int j) -> bool { return ((fns >> j) & 1u) != 0; };
+    if (one_tree) {
+        const int32_t base = (int32_t)(k0 - s0);
 #pragma unroll
-                for (int j = 0; j < kIxFan; ++j) {
-                    const uint32_t d = (uint32_t)(near >> (4 * j)) & 15u;
-                    const bool fn = ((w[j >> 2] >> (8 * (j & 3))) & 0x80u) != 0;
-                    int32_t r = -1;
-                    if (!parent) {
-                        if (!fn) r = base + j + 1;
-                        else if (d < 15) r = base + j + 1 + (int32_t)d;
-                        else work[atomicAdd(&n_work, 1)] = (uint16_t)(tid * kIxFan + j);
-                    } else if (base + j > 0) {
-                        if (d < 15) r = base + j - 1 - (int32_t)d;
-                        else work[atomicAdd(&n_work, 1)] = (uint16_t)(tid * kIxFan + j);
-                    }
-                    res[tid * kIxFan + j] = r;
+        for (int j = 0; j < kIxFan; ++j) {
+            const uint32_t d = (uint32_t)(nxt >> (4 * j)) & 15u;
+            int32_t r = base + j + 1;
+            if (fn_at(j)) {
+                r += (int32_t)d;
+                if (d == 15) work[atomicAdd(&n_work, 1)] = (uint16_t)(p0 + j);      // overwrites it
+            }
+            res[ix_slot(p0 + j)] = r;
+        }
+    } else if (k0 < q.n) {
+        each([&](int j, int64_t k, bool in, int64_t s, int64_t) {
+            int32_t r = -1;
+            if (in) {
+                const uint32_t d = (uint32_t)(nxt >> (4 * j)) & 15u;
+                r = (int32_t)(k + 1 - s);
+                if (fn_at(j)) {
+                    r += (int32_t)d;
+                    if (d == 15) work[atomicAdd(&n_work, 1)] = (uint16_t)(p0 + j);
                 }
             }
-            for (int j = 0; j < kIxFan && !one_tree; ++j) {
-                const int64_t k = k0 + j;
-                if (k >= q.n) break;
-                while (k >= e && t + 1 < q.n_trees) {
-                    ++t;
-                    s = q.offsets[t];
-                    e = q.offsets[t + 1];
-                    ok = q.valid[t] != 0;
-                }
-                int32_t r = -1;
-                if (ok && 0 <= s && s <= k && k < e && e <= q.n) {
-                    const uint32_t d = (uint32_t)(near >> (4 * j)) & 15u;
-                    const uint32_t wj = j < 8 ? (j < 4 ? w[0] : w[1]) : (j < 12 ? w[2] : w[3]);
-                    const bool fn = ((wj >> (8 * (j & 3))) & 0x80u) != 0;
-                    if (!parent) {
-                        if (!fn) r = (int32_t)(k + 1 - s);
-                        else if (d < 15) r = (int32_t)(k + 1 + d - s);
-                        else work[atomicAdd(&n_work, 1)] = (uint16_t)(tid * kIxFan + j);
-                    } else if (k > s) {
-                        if (d < 15) r = (int32_t)(k - 1 - d - s);
-                        else work[atomicAdd(&n_work, 1)] = (uint16_t)(tid * kIxFan + j);
-                    }
-                }
-                res[tid * kIxFan + j] = r;          // a listed search overwrites it
-            }
+            res[ix_slot(p0 + j)] = r;
+        });
+    }
+    __syncthreads();
+    const int nw = n_work;
+    for (int x = tid; x < nw; x += 256) {
+        const int i = work[x];
+        const int64_t k = B + i;
+        const int32_t v = bm.e0[i];
+        const int m = ix_lds_first_below(bm, i, v);
+        const int64_t t = ix_tree_in(q, t_lo, t_hi, k);
+        const int64_t s = q.offsets[t], e = q.offsets[t + 1];
+        if (m >= 0) {
+            res[ix_slot(i)] = B + m <= e ? (int32_t)(B + m - s) : -1;
+        } else {
+            const int slot = atomicAdd(&queued, 1);
+            if (slot < kIxQueue) queue[slot] = (uint16_t)i;
+            else res[ix_slot(i)] = ix_global_end(q, B, k, s, e, v + boff);
         }
-        __syncthreads();
-        const int nw = n_work;
-        for (int x = tid; x < nw; x += 256) {
-            const int i = work[x];
-            const int64_t k = B + i;
-            const int32_t v = bm.e0[i];
-            const int m = parent ? ix_lds_last_at_most(bm, i, v) : ix_lds_first_below(bm, i, v);
-            const int64_t t = ix_tree_in(q, t_lo, t_hi, k);
-            const int64_t s = q.offsets[t], e = q.offsets[t + 1];
-            if (m >= 0) {
-                const int64_t J = B + m;
-                res[i] = (parent ? J >= s : J <= e) ? (int32_t)(J - s) : -1;
-            } else {
-                const int slot = atomicAdd(&queued, 1);
-                if (slot < kIxQueue) queue[slot] = (uint16_t)i;
-                else res[i] = ix_global_link(q, B, k, s, e, v + boff, parent);
-            }
+    }
+    __syncthreads();
+    const int nq = min(queued, kIxQueue);
+    for (int x = tid; x < nq; x += 256) {
+        const int i = queue[x];
+        const int64_t t = ix_tree_in(q, t_lo, t_hi, B + i);
+        res[ix_slot(i)] = ix_global_end(q, B, B + i, q.offsets[t], q.offsets[t + 1], bm.e0[i] + boff);
+    }
+    __syncthreads();
+    for (int x = tid; x < here; x += 256) q.end[B + x] = res[ix_slot(x)];
+    int32_t en[kIxFan];
+#pragma unroll
+    for (int j = 0; j < kIxFan; ++j) en[j] = one_tree ? res[ix_slot(p0 + j)] : 0;
+    __syncthreads();                          // the ends read; q.end written
+    // First children, from the byte before; -2 where another thread hands the
+    // parent on.
+    const bool fn_before = k0 > 0 && k0 < q.n && (q.ops[k0 - 1] & 0x80) != 0;
+    if (one_tree) {
+        const int32_t base = (int32_t)(k0 - s0);
+#pragma unroll
+        for (int j = 0; j < kIxFan; ++j) {
+            const bool first = j > 0 ? fn_at(j - 1) : fn_before && base > 0;
+            res[ix_slot(p0 + j)] = first ? base + j - 1 : base + j > 0 ? -2 : -1;
         }
-        __syncthreads();
-        const int nq = min(queued, kIxQueue);
-        for (int x = tid; x < nq; x += 256) {
-            const int i = queue[x];
-            const int64_t t = ix_tree_in(q, t_lo, t_hi, B + i);
-            res[i] = ix_global_link(q, B, B + i, q.offsets[t], q.offsets[t + 1], bm.e0[i] + boff, parent);
-        }
-        __syncthreads();
-        int32_t* out = parent ? q.parent : q.end;
-        for (int x = tid; x < here; x += 256) out[B + x] = res[x];
+    } else if (k0 < q.n) {
+        each([&](int j, int64_t k, bool in, int64_t s, int64_t) {
+            const bool first = in && k > s && (j > 0 ? fn_at(j - 1) : fn_before);
+            res[ix_slot(p0 + j)] = first ? (int32_t)(k - 1 - s) : in && k > s ? -2 : -1;
+        });
+    }
+    __syncthreads();
+    // position k of [s, e), a first child whose subtree ends at r
+    const auto hand_on = [&](int64_t k, int64_t s, int64_t e, int64_t r) {
+        if (r <= k || r >= e) return;
+        if (r < B + kIxBlock) res[ix_slot((int)(r - B))] = (int32_t)(k - 1 - s);
+        else q.parent[r] = (int32_t)(k - 1 - s);
+    };
+    if (one_tree) {
+#pragma unroll
+        for (int j = 0; j < kIxFan; ++j)
+            if (j > 0 ? fn_at(j - 1) : fn_before && k0 > s0) hand_on(k0 + j, s0, e0, s0 + en[j]);
+    } else if (k0 < q.n) {
+        each([&](int j, int64_t k, bool in, int64_t s, int64_t e) {
+            if (in && k > s && (j > 0 ? fn_at(j - 1) : fn_before)) hand_on(k, s, e, s + q.end[k]);
+        });
+    }
+    __syncthreads();
+    for (int x = tid; x < here; x += 256) {
+        const int32_t r = res[ix_slot(x)];
+        if (r != -2) q.parent[B + x] = r;
     }
 }
 

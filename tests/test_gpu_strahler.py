@@ -1,5 +1,5 @@
-"""Strahler numbers of subtrees that leave their block of 4096 positions, against the oracle: ends at and beside block edges,
-numbers that rise only across blocks, spines over many blocks, and invalid neighbours."""
+"""Strahler numbers and parents of subtrees that leave their block of 4096 positions, against the oracle: ends at and beside
+block edges, numbers that rise only across blocks, spines over many blocks, and invalid neighbours."""
 import numpy as np
 import pytest
 
@@ -53,7 +53,8 @@ def test_numbers_across_blocks(ctx, seed, shift):
         offs[1:] = np.cumsum([len(t) for t in trees])
         ops = torch.from_numpy(np.concatenate(trees)).to("cuda:0")
         valid, end, parent, sn, _ = ctx.index_trees(ops, torch.from_numpy(offs).to("cuda:0"), 1, strahler=True)
-        sn, valid = sn.cpu().numpy(), valid.cpu().numpy()
+        sn, valid, parent = sn.cpu().numpy(), valid.cpu().numpy(), parent.cpu().numpy()
         assert valid[:-2].all() and not valid[-2:].any()
         want = np.concatenate([oracle.strahler(t) for t in trees[:-2]] + [np.zeros(5, np.uint8)])
         assert np.array_equal(sn, want), (seed, shift, len(ops))
+        assert np.array_equal(parent, np.concatenate([oracle.parents(t) for t in trees[:-2]] + [np.full(5, -1)]))
