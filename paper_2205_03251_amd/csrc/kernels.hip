@@ -593,7 +593,7 @@ __device__ double halving_sum(double (&e)[R], int64_t P, double* red)
 // The counters of the interpreter launch before this one, set back for the
 // next run of its plan by all blocks of the scoring launch.  Small evaluations
 // are bound by launches and the gaps between them: with the scoring launch also
-// writing the caller's arrays, 100 trees of at most 15 nodes on 20 cases take
+// writing the caller's arrays, 100 trees of 3 to 127 nodes on 48 cases take
 // 26 us a call in two launches, against 51 us in four (counters, interpreter,
 // scores, copies out), replayed as a graph or not.
 __device__ void reset_counters(const FitParams& p)

@@ -1029,6 +1029,12 @@ int enqueue_coeval(Ctx* c, const std::vector<IncJob>& jobs, gp_handle cases_h, c
     std::vector<int64_t> active(n);
     for (int64_t i = 0; i < n; ++i) active[i] = i;
     const size_t row = (size_t)cs->stride * esz;
+    // Nodes a child may execute in a round.  A sibling that has to be compiled
+    // counts as kSiblingCost more: where side chunks leave little of each to
+    // compile, nodes alone let a child take 800 levels into its first round,
+    // though most differences die out within 60 (100 children of trees of 10^6 to
+    // 10^7 nodes in 2048-node chunks, 47 -> 7.0 ms).
+    constexpr int64_t kSiblingCost = 128;
     int64_t budget = 16384;
     int64_t r = 0;
     for (; !active.empty(); ++r, budget = std::min<int64_t>(budget * 8, int64_t(1) << 40)) {
@@ -1110,13 +1116,15 @@ int enqueue_coeval(Ctx* c, const std::vector<IncJob>& jobs, gp_handle cases_h, c
                 offs.push_back((int64_t)ops.size());
                 pk.donor = Ref{(int64_t)offs.size() - 2, -1};
             }
-            int64_t k = done[i], sum = 0;
+            int64_t k = done[i], sum = 0, cost = 0;
             while (k < (int64_t)path[i].size()) {
                 Ref rf;
-                sum += add_sub(i, path[i][k].sib_begin, path[i][k].sib_end, &rf);
+                const int64_t nodes = add_sub(i, path[i][k].sib_begin, path[i][k].sib_end, &rf);
+                sum += nodes;
+                cost += nodes + (rf.slot >= 0 ? kSiblingCost : 0);
                 refs.push_back(rf);
                 ++k;
-                if (sum > budget) break;
+                if (cost > budget) break;
             }
             pk.count = k - pk.first;
             interp[i] += sum;
@@ -2606,6 +2614,8 @@ int gp_autotune(gp_ctx* ctx, gp_handle pop, gp_handle cases, int* best_variant, 
         for (int64_t c : cand)
             if (c <= std::max<int64_t>(256, 4 * mean)) chunk_sizes.push_back(c);
     }
+    int best = -1, best_w = 0;
+    float best_t = 1e30f;
     auto time_variant = [&](Pop* q, Launch L, float* out) -> int {
         RC(enqueue_full(ctx, q, cases, cs, L, false, true, ctx->stream, nullptr));   // warm-up
         float tmin = 1e30f;
@@ -2617,12 +2627,11 @@ int gp_autotune(gp_ctx* ctx, gp_handle pop, gp_handle cases, int* best_variant, 
             float ms = 0.f;
             HIPC(ctx, hipEventElapsedTime(&ms, ctx->ev0, ctx->ev1));
             tmin = std::min(tmin, ms);
+            if (tmin > 1.25f * best_t) break;   // runs of one launch differ by a few in a hundred
         }
         *out = tmin;
         return GP_OK;
     };
-    int best = -1, best_w = 0;
-    float best_t = 1e30f;
     std::shared_ptr<Pop> best_pop;
     for (int64_t cn : chunk_sizes) {
         std::shared_ptr<Pop> q;
