@@ -120,6 +120,13 @@ struct Server {
 
 namespace {
 
+// Chunk size of a job.  Jobs share the device with the others of their batch,
+// so what a chunk costs the host and the memory (tables, a vector per chunk)
+// counts for more than the length of one job's chain of chunks.
+// 20000 jobs of 10 to 10^7 nodes: 2540 jobs a second at saturation and 135 GB at
+// the chunk sizes of a lone population (512 and 1024), 3069 and 76 GB at these.
+int64_t serve_chunk_nodes(int64_t n) { return n < 200000 ? 1024 : 4096; }
+
 uint64_t estimate_full(const TreeProg& pg, const CaseSet* cs)
 {
     const uint64_t esz = cs->vtype == GP_BOOL ? 8 : 4;
@@ -159,7 +166,7 @@ int compile_on_device(Server* S, SJob* j, hipStream_t st, DevArena* arena)
     rc = device_compile_population(c, cs->vtype, cs->n_inputs, 1, dops.as<uint8_t>(), doffs.as<int64_t>(), offs,
                                    j->ops.data(), np ? j->points.data() : nullptr, np ? roffs : nullptr,
                                    np ? j->caller_points.data() : nullptr,
-                                   auto_chunk_nodes(cs->vtype, n, 1, cs->T), 0, nullptr, &progs, arena, st,
+                                   serve_chunk_nodes(n), 0, nullptr, &progs, arena, st,
                                    kPrepBlocks);
     if (rc != GP_OK) {
         (void)hipStreamSynchronize(st);        // nothing may still use the arena
@@ -232,7 +239,7 @@ void prep_worker(Server* S, int idx)
             CompileOptions opt;
             opt.vtype = cs->vtype;
             opt.n_inputs = cs->n_inputs;
-            opt.chunk_nodes = auto_chunk_nodes(cs->vtype, (int64_t)j->ops.size(), 1, cs->T);
+            opt.chunk_nodes = serve_chunk_nodes((int64_t)j->ops.size());
             opt.stack_slots = compile_stack_slots();
             // a large tree is compiled on a few threads (its latency is mostly this)
             if (j->ops.size() >= 1000000) opt.threads = 4;
