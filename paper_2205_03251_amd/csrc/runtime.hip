@@ -1053,10 +1053,11 @@ int enqueue_coeval(Ctx* c, const std::vector<IncJob>& jobs, gp_handle cases_h, c
         std::vector<Ref> refs;                  // level siblings, pick after pick
         std::vector<uint8_t> ops;
         std::vector<int32_t> ext;               // per byte of ops: -1 or the input row it stands for
-        std::vector<int64_t> ext_src;           // mother rows behind input rows n_inputs, n_inputs + 1, ...
+        std::vector<int64_t> ext_src;           // mother rows, appended to the case set's input rows (which may be
+                                                // more than the population reads)
         std::vector<int64_t> offs{0};
         const bool ckpt = vtype == GP_F32 && p->cuts.size() == (size_t)p->n_trees;
-        const int64_t row_cap = ((int64_t(1) << 31) / (int64_t)row) - p->n_inputs - 1;   // row offsets stay < 2^31
+        const int64_t row_cap = ((int64_t(1) << 31) / (int64_t)row) - cs->n_inputs - 1;  // row offsets stay < 2^31
         // Subtree [b, e) of child i's mother: chunks of the mother inside it are
         // read from her vectors (a placeholder terminal pushed from a gathered
         // input row); only the rest is compiled.  Returns the nodes executed.
@@ -1088,7 +1089,7 @@ int enqueue_coeval(Ctx* c, const std::vector<IncJob>& jobs, gp_handle cases_h, c
                     if (u == e) break;
                     if ((int64_t)ext_src.size() < row_cap) {
                         ops.push_back(0);
-                        ext.push_back((int32_t)(p->n_inputs + (int64_t)ext_src.size()));
+                        ext.push_back((int32_t)(cs->n_inputs + (int64_t)ext_src.size()));
                         ext_src.push_back(it->slot);
                     } else {                    // no input row left: compile that chunk too
                         ops.insert(ops.end(), t + u, t + it->end);
