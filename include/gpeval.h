@@ -152,7 +152,15 @@ int gp_set_cases(gp_ctx* ctx, int vtype, int n_inputs, int64_t n_cases, const vo
  * record_points[record_offsets[i] .. record_offsets[i+1]) (node indices in
  * the given layout) whose parent caches every full evaluation must record,
  * for later incremental evaluation of children made at those points.
- * chunk_nodes: target nodes per chunk (0 = automatic).  flags: GP_KEEP_TREES
+ * chunk_nodes: target nodes per chunk (0 = automatic).  A full evaluation
+ * holds a vector of all cases per chunk; besides the chunks of about
+ * chunk_nodes, subtrees that can run while an operand beside them waits root
+ * chunks too, so that a random tree has one per 90, 190, 270, 1070 and 2150
+ * nodes at 128, 512, 1024, 4096 and 8192 (gp_population_info counts them).  A
+ * call that finds the budget or the device exhausted is tried once more
+ * without those further chunks (one per 150, 600, 1200, 4800 and 9600 nodes):
+ * the context's populations are recompiled in place and stay so, evaluated
+ * ones keep their results and parent caches.  flags: GP_KEEP_TREES
  * keeps a device copy of ops for gp_splice_children.  GP_DEVICE_COMPILE
  * (prefix layout only) validates and compiles the trees on the device: the
  * same checks, and programs, chunk tables and parent-cache records identical

@@ -822,6 +822,8 @@ int device_compile_population(Ctx* c, int vtype, int n_inputs, int64_t n_trees, 
     q.boolean = vtype == GP_BOOL ? 1 : 0;
     q.S = compile_stack_slots();
     q.C = C;
+    q.no_side = !side_chunks_wanted();
+    if (out) out->side_chunks = side_chunks_wanted();
     if (packed) {
         // open and cnt are not in use yet: the listed nodes and their words
         uint32_t* n_walks = counter.as<uint32_t>();

@@ -61,6 +61,9 @@ constexpr int64_t kPathSiblingChunk = 64;
 // a piece takes as long as its hand-off, C / 32 keeps the number of chunks
 // (one per 270 nodes at C = 1024, one per 1100 at 4096) falling with C, so
 // that the choice of C still trades chain length against chunk count.
+// Every chunk owns a vector of device memory; without side chunks it is 1.7, 4.4
+// and 4.5 times as many nodes to a chunk at C = 128, 1024 and 4096, which is what
+// calls that run short of memory fall back to (CompileOptions::side_chunks).
 constexpr int64_t kSideChunkMin = 32;
 constexpr int64_t side_chunk_nodes(int64_t C) { return C / 32 > kSideChunkMin ? C / 32 : kSideChunkMin; }
 
@@ -121,6 +124,7 @@ struct CompileOptions {
     int stack_slots = 16;        // register-stack slots available
     int64_t index_min_size = 0;  // > 0: list (node, end) of subtrees this large, sorted by node
     int threads = 1;             // threads for compiling a large tree (same program for any count)
+    bool side_chunks = true;     // operands beside one that waits root chunks (see side_chunk_nodes)
 };
 
 // Section 3.1 format check of one prefix array.

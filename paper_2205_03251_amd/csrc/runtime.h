@@ -9,6 +9,7 @@
 #include <cstdlib>
 #include <new>
 #include <cstdint>
+#include <functional>
 #include <map>
 #include <memory>
 #include <mutex>
@@ -162,7 +163,8 @@ struct Pop {
     int layout = 0;
     bool auto_chunk = false;                // chunk size may be re-tuned
     bool device_compiled = false;           // compiled on the device (re-chunked there too)
-    // host copy of the trees, for re-chunking by the autotuner
+    bool side_chunks = true;                // compiled with side chunks (see side_chunk_nodes)
+    // host copy of the trees and record points, for re-chunking
     std::vector<uint8_t, NoInitAlloc<uint8_t>> host_ops;
     std::vector<int64_t> host_offsets, host_rec_points, host_rec_offsets;
     int64_t n_trees = 0;
@@ -264,6 +266,16 @@ struct PoolScope {
     PoolScope& operator=(const PoolScope&) = delete;
     Ctx* before;
 };
+// Populations built by this thread have no side chunks while it lives: the
+// second attempt of a call that ran short of device memory.
+struct NoSideChunks {
+    NoSideChunks();
+    ~NoSideChunks();
+    NoSideChunks(const NoSideChunks&) = delete;
+    NoSideChunks& operator=(const NoSideChunks&) = delete;
+    bool before;
+};
+bool side_chunks_wanted();
 constexpr size_t kStageBytes = size_t(4) << 20;
 
 // ------------------------------------------------------------ internals
@@ -283,10 +295,13 @@ int hip_check(Ctx* c, hipError_t e, const char* what);
 // for co-evaluation.
 // ext_rows (prefix layout, may be null): per byte of ops, -1 or the input row
 // a terminal stands for (see compile_tree).
+// before_upload (may be empty): called once the trees are compiled, before any
+// device memory is asked for; not when an error is returned ahead of that.
 int build_population(Ctx* c, int vtype, int layout, int n_inputs, int64_t n_trees,
                      const uint8_t* ops, const int64_t* offsets, const int64_t* rec_points,
                      const int64_t* rec_offsets, int64_t chunk_nodes, Pop* out, hipStream_t s,
-                     bool index_subtrees = false, const int32_t* ext_rows = nullptr);
+                     bool index_subtrees = false, const int32_t* ext_rows = nullptr,
+                     const std::function<void()>& before_upload = {});
 // Assemble already compiled trees into a population and upload it on s.
 // Chunks with dev_src >= 0 take their code from dev_code_src (device words).
 int assemble_population(Ctx* c, int vtype, int n_inputs, std::vector<TreeProg>& progs,

@@ -49,6 +49,13 @@ static thread_local Ctx* t_pool = nullptr;     // the context whose PoolScope th
 PoolScope::PoolScope(Ctx* c) : before(t_pool) { t_pool = c->server ? nullptr : c; }
 PoolScope::~PoolScope() { t_pool = before; }
 
+static thread_local bool t_no_side = false;    // inside a NoSideChunks
+static thread_local uint64_t t_need = 0, t_left = 0;   // the last refused allocation: its bytes, what was left
+
+NoSideChunks::NoSideChunks() : before(t_no_side) { t_no_side = true; }
+NoSideChunks::~NoSideChunks() { t_no_side = before; }
+bool side_chunks_wanted() { return !t_no_side; }
+
 // The smallest kept block that holds `need` without wasting more than an eighth (and 64 KiB).
 void* DevPool::take(size_t need, size_t* got)
 {
@@ -127,10 +134,13 @@ int dev_alloc(Ctx* c, DevBuf& b, size_t bytes)
         if (c->used + bytes <= c->budget) p = c->pool.take(bytes, &block);
         if (!p && c->used + bytes + c->pool.bytes > c->budget) c->pool.trim();
     }
-    if (!p && c->used + bytes > c->budget)
+    if (!p && c->used + bytes > c->budget) {
+        t_need = bytes;
+        t_left = c->budget - std::min<uint64_t>(c->budget, c->used);
         return set_err(c, GP_EBUDGET,
                        "device memory budget exceeded: need " + std::to_string(bytes) + " more bytes, " +
-                           std::to_string(c->budget - std::min<uint64_t>(c->budget, c->used)) + " left");
+                           std::to_string(t_left) + " left");
+    }
     if (!p) {
         hipError_t e = hipMalloc(&p, bytes);
         if (e != hipSuccess && pooled && c->pool.bytes > 0) {
@@ -140,6 +150,10 @@ int dev_alloc(Ctx* c, DevBuf& b, size_t bytes)
         }
         if (e != hipSuccess) {
             (void)hipGetLastError();
+            size_t free_b = 0, total_b = 0;
+            (void)hipMemGetInfo(&free_b, &total_b);
+            t_need = bytes;
+            t_left = free_b;
             return set_err(c, GP_ENOMEM, std::string("hipMalloc failed: ") + hipGetErrorString(e));
         }
     }
@@ -270,7 +284,7 @@ static constexpr int64_t kBigSubtree = 4096;
 int build_population(Ctx* c, int vtype, int layout, int n_inputs, int64_t n_trees, const uint8_t* ops,
                      const int64_t* offsets, const int64_t* rec_points, const int64_t* rec_offsets,
                      int64_t chunk_nodes, Pop* out, hipStream_t stream, bool index_subtrees,
-                     const int32_t* ext_rows)
+                     const int32_t* ext_rows, const std::function<void()>& before_upload)
 {
     if (vtype != GP_F32 && vtype != GP_BOOL) return set_err(c, GP_EINVAL, "unknown value type");
     if (layout != GP_PREFIX && layout != GP_POSTFIX) return set_err(c, GP_EINVAL, "unknown layout");
@@ -294,6 +308,7 @@ int build_population(Ctx* c, int vtype, int layout, int n_inputs, int64_t n_tree
     opt.chunk_nodes = chunk_nodes;
     opt.stack_slots = compile_stack_slots();
     opt.index_min_size = index_subtrees && layout == GP_PREFIX ? kBigSubtree : 0;
+    opt.side_chunks = out->side_chunks = side_chunks_wanted();
 
     std::vector<TreeProg> progs(n_trees);
     std::vector<std::string> errs(n_trees);
@@ -362,6 +377,7 @@ int build_population(Ctx* c, int vtype, int layout, int n_inputs, int64_t n_tree
     for (auto& x : th) x.join();
     for (int64_t t = 0; t < n_trees; ++t)
         if (bad[t]) return set_err(c, GP_EINVAL, "tree " + std::to_string(t) + ": " + errs[t]);
+    if (before_upload) before_upload();
     out->layout = layout;
     if (opt.index_min_size > 0) {
         out->big_ends.resize(n_trees);
@@ -1231,6 +1247,94 @@ int enqueue_coeval(Ctx* c, const std::vector<IncJob>& jobs, gp_handle cases_h, c
     return GP_OK;
 }
 
+// The re-chunked copy q replaces population p under the same handle; it takes
+// over the host and device copies of the trees.
+static Pop* replace_population(Ctx* ctx, gp_handle pop, Pop* p, const std::shared_ptr<Pop>& q)
+{
+    q->auto_chunk = p->auto_chunk;
+    q->host_ops.swap(p->host_ops);
+    q->host_offsets.swap(p->host_offsets);
+    q->host_rec_points.swap(p->host_rec_points);
+    q->host_rec_offsets.swap(p->host_rec_offsets);
+    q->tree_ops.swap(p->tree_ops);
+    q->tree_off.swap(p->tree_off);
+    ctx->pops[pop] = q;
+    return q.get();
+}
+
+// ------------------------------------------------ short of device memory
+// Side chunks cost memory: every chunk owns a vector of all cases, and they
+// make 1.7 to 4.5 times as many chunks of the same trees (see
+// side_chunk_nodes).  A call that finds the budget or the device exhausted
+// therefore makes a second attempt without them, so that what fits without side
+// chunks is not refused: the context's populations are recompiled at their
+// chunk sizes, the evaluated ones evaluated again (the same values, records and
+// scores), and what the call builds itself has no side chunks either.
+
+// Population h recompiled without side chunks, in place.  The trees are compiled
+// on the host first; then the old program and vectors are released, so that the
+// new ones, which are smaller, fit where the old ones did.
+static int drop_side_chunks(Ctx* ctx, gp_handle h, const std::shared_ptr<Pop>& p)
+{
+    const gp_handle eval_h = p->evaluated_with;
+    const bool rec = !p->host_rec_offsets.empty();
+    bool released = false;
+    auto release = [&]() {
+        p->plans.clear();
+        for (DevBuf* b : {&p->vecs, &p->recs, &p->fit, &p->code, &p->chunks, &p->chunk_in, &p->levels}) b->release();
+        released = true;
+    };
+    auto q = std::make_shared<Pop>();
+    int rc = GP_OK;
+    try {
+        rc = build_population(ctx, p->vtype, p->layout, p->n_inputs, p->n_trees, p->host_ops.data(),
+                              p->host_offsets.data(), rec ? p->host_rec_points.data() : nullptr,
+                              rec ? p->host_rec_offsets.data() : nullptr, p->chunk_nodes, q.get(), ctx->stream, true,
+                              nullptr, release);
+    } catch (const std::bad_alloc&) {
+        rc = set_err(ctx, GP_ENOMEM, "out of host memory while recompiling without side chunks");
+    }
+    if (rc != GP_OK) {
+        if (released) ctx->pops.erase(h);        // nothing is left of it on the device
+        return rc;
+    }
+    q->device_compiled = p->device_compiled;
+    replace_population(ctx, h, p.get(), q);
+    auto ic = ctx->cases.find(eval_h);
+    if (ic == ctx->cases.end()) return GP_OK;
+    const CaseSet* cs = ic->second.get();
+    const Launch L = choose_launch(ctx, q->vtype, cs, q.get());
+    if (L.variant < 0) return set_err(ctx, GP_EINVAL, "no interpreter variant fits this population");
+    RC(enqueue_full(ctx, q.get(), eval_h, cs, L, false, false, ctx->stream, nullptr));
+    HIPC(ctx, hipStreamSynchronize(ctx->stream));
+    return GP_OK;
+}
+
+// call(), and once more without side chunks if it runs short of memory.
+template <class Call>
+static int retry_if_short(Ctx* ctx, Call call)
+{
+    t_need = 0;
+    const int rc = call();
+    if ((rc != GP_EBUDGET && rc != GP_ENOMEM) || t_need == 0) return rc;
+    std::vector<std::pair<gp_handle, std::shared_ptr<Pop>>> with;
+    uint64_t held = 0;
+    for (const auto& kv : ctx->pops)
+        if (kv.second->side_chunks && kv.second->n_chunks > kv.second->n_trees && !kv.second->host_ops.empty()) {
+            with.emplace_back(kv.first, kv.second);
+            held += kv.second->vecs.bytes;
+        }
+    // not for a request that could not fit even with four fifths of the vectors, its own among them, gone
+    if (t_need / 5 > t_left + held / 5 * 4) return rc;
+    NoSideChunks scope;
+    (void)hipStreamSynchronize(ctx->stream);
+    for (auto& hp : with) {
+        RC(drop_side_chunks(ctx, hp.first, hp.second));
+        hp.second.reset();
+    }
+    return call();
+}
+
 }  // namespace gpe
 
 using namespace gpe;
@@ -1339,13 +1443,9 @@ const char* gp_last_error(const gp_ctx* ctx)
 
 uint64_t gp_memory_used(const gp_ctx* ctx) { return ctx ? ctx->used.load() : 0; }
 
-int gp_set_cases(gp_ctx* ctx, int vtype, int n_inputs, int64_t n_cases, const void* inputs,
-                 const void* target, uint32_t flags, gp_handle* cases_out)
+static int set_cases(gp_ctx* ctx, int vtype, int n_inputs, int64_t n_cases, const void* inputs, const void* target,
+                     uint32_t flags, gp_handle* cases_out)
 {
-    if (!ctx || !cases_out) return GP_EINVAL;
-    std::lock_guard<std::mutex> lk(ctx->mu);
-    PoolScope pool(ctx);
-    HIPC(ctx, hipSetDevice(ctx->device));
     if (vtype != GP_F32 && vtype != GP_BOOL) return set_err(ctx, GP_EINVAL, "unknown value type");
     if (n_inputs < 1 || n_inputs > kMaxInputs) return set_err(ctx, GP_EINVAL, "n_inputs must be 1..64");
     if (n_cases < 1) return set_err(ctx, GP_EINVAL, "need at least one test case");
@@ -1381,6 +1481,18 @@ int gp_set_cases(gp_ctx* ctx, int vtype, int n_inputs, int64_t n_cases, const vo
     return GP_OK;
 }
 
+int gp_set_cases(gp_ctx* ctx, int vtype, int n_inputs, int64_t n_cases, const void* inputs,
+                 const void* target, uint32_t flags, gp_handle* cases_out)
+{
+    if (!ctx || !cases_out) return GP_EINVAL;
+    std::lock_guard<std::mutex> lk(ctx->mu);
+    PoolScope pool(ctx);
+    HIPC(ctx, hipSetDevice(ctx->device));
+    return retry_if_short(ctx, [&] {
+        return set_cases(ctx, vtype, n_inputs, n_cases, inputs, target, flags, cases_out);
+    });
+}
+
 // dst = src[0 .. n), in slices on up to 16 threads when large.
 static void copy_host_bytes(std::vector<uint8_t, NoInitAlloc<uint8_t>>& dst, const uint8_t* src, size_t n)
 {
@@ -1400,14 +1512,10 @@ static void copy_host_bytes(std::vector<uint8_t, NoInitAlloc<uint8_t>>& dst, con
     for (auto& x : th) x.join();
 }
 
-int gp_load_population(gp_ctx* ctx, int vtype, int layout, int n_inputs, int64_t n_trees, const uint8_t* ops,
-                       const int64_t* offsets, const int64_t* record_points, const int64_t* record_offsets,
-                       int64_t chunk_nodes, uint32_t flags, gp_handle* pop_out)
+static int load_population(gp_ctx* ctx, int vtype, int layout, int n_inputs, int64_t n_trees, const uint8_t* ops,
+                           const int64_t* offsets, const int64_t* record_points, const int64_t* record_offsets,
+                           int64_t chunk_nodes, uint32_t flags, gp_handle* pop_out)
 {
-    if (!ctx || !pop_out) return GP_EINVAL;
-    std::lock_guard<std::mutex> lk(ctx->mu);
-    PoolScope pool(ctx);
-    HIPC(ctx, hipSetDevice(ctx->device));
     auto p = std::make_shared<Pop>();
     if (flags & (GP_DEVICE_PTR | GP_DEVICE_COMPILE)) {
         if (layout != GP_PREFIX) return set_err(ctx, GP_EINVAL, "device compilation takes prefix trees");
@@ -1444,7 +1552,7 @@ int gp_load_population(gp_ctx* ctx, int vtype, int layout, int n_inputs, int64_t
             p->tree_ops.swap(keep);
             p->tree_off = p->host_offsets;
         }
-        if (p->auto_chunk && record_points) {
+        if (record_points) {
             p->host_rec_offsets.assign(record_offsets, record_offsets + n_trees + 1);
             p->host_rec_points.assign(record_points, record_points + record_offsets[n_trees]);
         }
@@ -1456,8 +1564,7 @@ int gp_load_population(gp_ctx* ctx, int vtype, int layout, int n_inputs, int64_t
     RC(build_population(ctx, vtype, layout, n_inputs, n_trees, ops, offsets, record_points, record_offsets,
                         chunk_nodes, p.get(), ctx->stream, true));
     p->auto_chunk = chunk_nodes <= 0;
-    // host copy of the trees: re-chunking by the autotuner, sibling subtrees
-    // for co-evaluation
+    // host copy of the trees: re-chunking, sibling subtrees for co-evaluation
     copy_host_bytes(p->host_ops, ops, (size_t)offsets[n_trees]);
     p->host_offsets.assign(offsets, offsets + n_trees + 1);
     if (flags & GP_KEEP_TREES) {
@@ -1467,16 +1574,28 @@ int gp_load_population(gp_ctx* ctx, int vtype, int layout, int n_inputs, int64_t
         p->tree_off.assign(offsets, offsets + n_trees + 1);
         HIPC(ctx, hipStreamSynchronize(ctx->stream));
     }
-    if (p->auto_chunk) {
-        if (record_points) {
-            p->host_rec_offsets.assign(record_offsets, record_offsets + n_trees + 1);
-            p->host_rec_points.assign(record_points, record_points + record_offsets[n_trees]);
-        }
+    if (record_points) {
+        p->host_rec_offsets.assign(record_offsets, record_offsets + n_trees + 1);
+        p->host_rec_points.assign(record_points, record_points + record_offsets[n_trees]);
     }
     gp_handle h = ctx->next_handle++;
     ctx->pops[h] = p;
     *pop_out = h;
     return GP_OK;
+}
+
+int gp_load_population(gp_ctx* ctx, int vtype, int layout, int n_inputs, int64_t n_trees, const uint8_t* ops,
+                       const int64_t* offsets, const int64_t* record_points, const int64_t* record_offsets,
+                       int64_t chunk_nodes, uint32_t flags, gp_handle* pop_out)
+{
+    if (!ctx || !pop_out) return GP_EINVAL;
+    std::lock_guard<std::mutex> lk(ctx->mu);
+    PoolScope pool(ctx);
+    HIPC(ctx, hipSetDevice(ctx->device));
+    return retry_if_short(ctx, [&] {
+        return load_population(ctx, vtype, layout, n_inputs, n_trees, ops, offsets, record_points, record_offsets,
+                               chunk_nodes, flags, pop_out);
+    });
 }
 
 int gp_population_info(gp_ctx* ctx, gp_handle pop, gp_pop_info* out)
@@ -1765,14 +1884,9 @@ private:
     int64_t used_ = 0;
 };
 
-int gp_evaluate_full(gp_ctx* ctx, gp_handle pop, gp_handle cases, uint32_t flags, void* root_out,
-                     void* fitness_out, gp_stats* st)
+static int evaluate_full(gp_ctx* ctx, gp_handle pop, gp_handle cases, uint32_t flags, void* root_out,
+                         void* fitness_out, gp_stats* st, double t0)
 {
-    if (!ctx) return GP_EINVAL;
-    const double t0 = now_ms();
-    std::lock_guard<std::mutex> lk(ctx->mu);
-    PoolScope pool(ctx);
-    HIPC(ctx, hipSetDevice(ctx->device));
     Pop* p;
     CaseSet* cs;
     RC(lookup(ctx, pop, cases, &p, &cs));
@@ -1818,12 +1932,20 @@ int gp_evaluate_full(gp_ctx* ctx, gp_handle pop, gp_handle cases, uint32_t flags
     return GP_OK;
 }
 
-int gp_fitness(gp_ctx* ctx, gp_handle cases, const void* outputs, int64_t n, uint32_t flags, void* fitness_out)
+int gp_evaluate_full(gp_ctx* ctx, gp_handle pop, gp_handle cases, uint32_t flags, void* root_out,
+                     void* fitness_out, gp_stats* st)
 {
     if (!ctx) return GP_EINVAL;
+    const double t0 = now_ms();
     std::lock_guard<std::mutex> lk(ctx->mu);
     PoolScope pool(ctx);
     HIPC(ctx, hipSetDevice(ctx->device));
+    return retry_if_short(ctx, [&] { return evaluate_full(ctx, pop, cases, flags, root_out, fitness_out, st, t0); });
+}
+
+static int score_outputs(gp_ctx* ctx, gp_handle cases, const void* outputs, int64_t n, uint32_t flags,
+                         void* fitness_out)
+{
     auto ic = ctx->cases.find(cases);
     if (ic == ctx->cases.end()) return set_err(ctx, GP_EINVAL, "unknown case-set handle");
     CaseSet* cs = ic->second.get();
@@ -1851,16 +1973,20 @@ int gp_fitness(gp_ctx* ctx, gp_handle cases, const void* outputs, int64_t n, uin
     return GP_OK;
 }
 
-int gp_evaluate_incremental_batch(gp_ctx* ctx, gp_handle pop, gp_handle cases, int64_t n_children,
-                                  const int64_t* parent, const int64_t* point, const uint8_t* donor_ops,
-                                  const int64_t* donor_offsets, uint32_t flags, void* root_out,
-                                  void* fitness_out, gp_inc_result* res, gp_stats* st)
+int gp_fitness(gp_ctx* ctx, gp_handle cases, const void* outputs, int64_t n, uint32_t flags, void* fitness_out)
 {
     if (!ctx) return GP_EINVAL;
-    const double t0 = now_ms();
     std::lock_guard<std::mutex> lk(ctx->mu);
     PoolScope pool(ctx);
     HIPC(ctx, hipSetDevice(ctx->device));
+    return retry_if_short(ctx, [&] { return score_outputs(ctx, cases, outputs, n, flags, fitness_out); });
+}
+
+static int evaluate_incremental(gp_ctx* ctx, gp_handle pop, gp_handle cases, int64_t n_children, const int64_t* parent,
+                                const int64_t* point, const uint8_t* donor_ops, const int64_t* donor_offsets,
+                                uint32_t flags, void* root_out, void* fitness_out, gp_inc_result* res, gp_stats* st,
+                                double t0)
+{
     Pop* p;
     CaseSet* cs;
     RC(lookup(ctx, pop, cases, &p, &cs));
@@ -1932,16 +2058,26 @@ int gp_evaluate_incremental_batch(gp_ctx* ctx, gp_handle pop, gp_handle cases, i
     return GP_OK;
 }
 
-int gp_splice_children(gp_ctx* ctx, gp_handle pop, int64_t n_children, const int64_t* parent,
-                       const int64_t* point, const uint8_t* donor_ops, const int64_t* donor_offsets,
-                       uint32_t flags, uint8_t* child_ops, int64_t child_cap, int64_t* child_offsets,
-                       gp_stats* st)
+int gp_evaluate_incremental_batch(gp_ctx* ctx, gp_handle pop, gp_handle cases, int64_t n_children,
+                                  const int64_t* parent, const int64_t* point, const uint8_t* donor_ops,
+                                  const int64_t* donor_offsets, uint32_t flags, void* root_out,
+                                  void* fitness_out, gp_inc_result* res, gp_stats* st)
 {
     if (!ctx) return GP_EINVAL;
     const double t0 = now_ms();
     std::lock_guard<std::mutex> lk(ctx->mu);
     PoolScope pool(ctx);
     HIPC(ctx, hipSetDevice(ctx->device));
+    return retry_if_short(ctx, [&] {
+        return evaluate_incremental(ctx, pop, cases, n_children, parent, point, donor_ops, donor_offsets, flags,
+                                    root_out, fitness_out, res, st, t0);
+    });
+}
+
+static int splice_children(gp_ctx* ctx, gp_handle pop, int64_t n_children, const int64_t* parent, const int64_t* point,
+                           const uint8_t* donor_ops, const int64_t* donor_offsets, uint32_t flags, uint8_t* child_ops,
+                           int64_t child_cap, int64_t* child_offsets, gp_stats* st, double t0)
+{
     auto ip = ctx->pops.find(pop);
     if (ip == ctx->pops.end()) return set_err(ctx, GP_EINVAL, "unknown population handle");
     Pop* p = ip->second.get();
@@ -2035,6 +2171,22 @@ int gp_splice_children(gp_ctx* ctx, gp_handle pop, int64_t n_children, const int
     return GP_OK;
 }
 
+int gp_splice_children(gp_ctx* ctx, gp_handle pop, int64_t n_children, const int64_t* parent,
+                       const int64_t* point, const uint8_t* donor_ops, const int64_t* donor_offsets,
+                       uint32_t flags, uint8_t* child_ops, int64_t child_cap, int64_t* child_offsets,
+                       gp_stats* st)
+{
+    if (!ctx) return GP_EINVAL;
+    const double t0 = now_ms();
+    std::lock_guard<std::mutex> lk(ctx->mu);
+    PoolScope pool(ctx);
+    HIPC(ctx, hipSetDevice(ctx->device));
+    return retry_if_short(ctx, [&] {
+        return splice_children(ctx, pop, n_children, parent, point, donor_ops, donor_offsets, flags, child_ops,
+                               child_cap, child_offsets, st, t0);
+    });
+}
+
 int gp_population_ops(gp_ctx* ctx, gp_handle pop, uint8_t* ops_out, int64_t ops_cap, int64_t* offsets_out)
 {
     if (!ctx || !offsets_out) return GP_EINVAL;
@@ -2074,13 +2226,9 @@ int gp_population_results(gp_ctx* ctx, gp_handle pop, gp_handle cases, uint32_t 
     return rc.finish();
 }
 
-int gp_evolve(gp_ctx* ctx, gp_handle pop, gp_handle cases, const gp_evolve_cfg* cfg, gp_gen_stats* stats,
-              gp_gen_child* children, gp_handle* out_pop)
+static int evolve(gp_ctx* ctx, gp_handle pop, gp_handle cases, const gp_evolve_cfg* cfg, gp_gen_stats* stats,
+                  gp_gen_child* children, gp_handle* out_pop)
 {
-    if (!ctx || !cfg || !out_pop) return GP_EINVAL;
-    std::lock_guard<std::mutex> lk(ctx->mu);
-    PoolScope pool(ctx);
-    HIPC(ctx, hipSetDevice(ctx->device));
     Pop* p0;
     CaseSet* cs;
     RC(lookup(ctx, pop, cases, &p0, &cs));
@@ -2235,6 +2383,7 @@ int gp_evolve(gp_ctx* ctx, gp_handle pop, gp_handle cases, const gp_evolve_cfg* 
             opt.chunk_nodes = cur->chunk_nodes;
             opt.stack_slots = compile_stack_slots();
             opt.index_min_size = kBigSubtree;
+            opt.side_chunks = np->side_chunks = cur->side_chunks && side_chunks_wanted();
             std::atomic<int64_t> next{0};
             auto work = [&]() {
                 for (int64_t k; (k = next++) < nb;) {
@@ -2364,6 +2513,16 @@ int gp_evolve(gp_ctx* ctx, gp_handle pop, gp_handle cases, const gp_evolve_cfg* 
     ctx->pops[h] = holder;
     *out_pop = h;
     return GP_OK;
+}
+
+int gp_evolve(gp_ctx* ctx, gp_handle pop, gp_handle cases, const gp_evolve_cfg* cfg, gp_gen_stats* stats,
+              gp_gen_child* children, gp_handle* out_pop)
+{
+    if (!ctx || !cfg || !out_pop) return GP_EINVAL;
+    std::lock_guard<std::mutex> lk(ctx->mu);
+    PoolScope pool(ctx);
+    HIPC(ctx, hipSetDevice(ctx->device));
+    return retry_if_short(ctx, [&] { return evolve(ctx, pop, cases, cfg, stats, children, out_pop); });
 }
 
 int gp_evaluate_incremental(gp_ctx* ctx, gp_handle pop, gp_handle cases, int64_t parent, int64_t point,
@@ -2529,10 +2688,6 @@ int gp_set_launch_width(gp_ctx* ctx, int waves_per_cu)
     return GP_OK;
 }
 
-// Time every interpreter variant, and for automatically chunked populations
-// every candidate chunk size, on this population and case set; keep the
-// fastest (chunk size: recompiled in place; variant: remembered per value
-// type, case-count bucket and tree-size bucket).
 // The population p recompiled at chunk size cn into a new Pop (from the kept
 // device copy of the trees, else from the host copy).
 static int rechunk(Ctx* ctx, Pop* p, int64_t cn, std::shared_ptr<Pop>* out)
@@ -2554,27 +2709,12 @@ static int rechunk(Ctx* ctx, Pop* p, int64_t cn, std::shared_ptr<Pop>* out)
     return GP_OK;
 }
 
-// The re-chunked copy q replaces population p under the same handle; it takes
-// over the host and device copies of the trees.
-static Pop* replace_population(Ctx* ctx, gp_handle pop, Pop* p, const std::shared_ptr<Pop>& q)
+// Time every interpreter variant, and for automatically chunked populations
+// every candidate chunk size, on this population and case set; keep the
+// fastest (chunk size: recompiled in place; variant: remembered per value
+// type, case-count bucket and tree-size bucket).
+static int autotune(gp_ctx* ctx, gp_handle pop, gp_handle cases, int* best_variant, double* best_ms)
 {
-    q->auto_chunk = true;
-    q->host_ops.swap(p->host_ops);
-    q->host_offsets.swap(p->host_offsets);
-    q->host_rec_points.swap(p->host_rec_points);
-    q->host_rec_offsets.swap(p->host_rec_offsets);
-    q->tree_ops.swap(p->tree_ops);
-    q->tree_off.swap(p->tree_off);
-    ctx->pops[pop] = q;
-    return q.get();
-}
-
-int gp_autotune(gp_ctx* ctx, gp_handle pop, gp_handle cases, int* best_variant, double* best_ms)
-{
-    if (!ctx) return GP_EINVAL;
-    std::lock_guard<std::mutex> lk(ctx->mu);
-    PoolScope pool(ctx);
-    HIPC(ctx, hipSetDevice(ctx->device));
     Pop* p;
     CaseSet* cs;
     RC(lookup(ctx, pop, cases, &p, &cs));
@@ -2615,7 +2755,7 @@ int gp_autotune(gp_ctx* ctx, gp_handle pop, gp_handle cases, int* best_variant, 
         for (int64_t c : cand)
             if (c <= std::max<int64_t>(256, 4 * mean)) chunk_sizes.push_back(c);
     }
-    int best = -1, best_w = 0;
+    int best = -1, best_w = 0, refused = GP_OK;
     float best_t = 1e30f;
     auto time_variant = [&](Pop* q, Launch L, float* out) -> int {
         RC(enqueue_full(ctx, q, cases, cs, L, false, true, ctx->stream, nullptr));   // warm-up
@@ -2634,7 +2774,8 @@ int gp_autotune(gp_ctx* ctx, gp_handle pop, gp_handle cases, int* best_variant, 
         return GP_OK;
     };
     std::shared_ptr<Pop> best_pop;
-    for (int64_t cn : chunk_sizes) {
+    // one chunk size; its copy of the population goes when it is not the best so far
+    auto try_size = [&](int64_t cn) -> int {
         std::shared_ptr<Pop> q;
         Pop* qp = p;
         if (cn != p->chunk_nodes) {
@@ -2686,7 +2827,27 @@ int gp_autotune(gp_ctx* ctx, gp_handle pop, gp_handle cases, int* best_variant, 
         }
         // keep only the compiled copy of the best chunk size so far
         if (improved) best_pop = q;
+        return GP_OK;
+    };
+    for (int64_t cn : chunk_sizes) {
+        const int best0 = best, best_w0 = best_w;
+        const float best_t0 = best_t;
+        const int rc = try_size(cn);
+        if (rc != GP_EBUDGET && rc != GP_ENOMEM) RC(rc);
+        if (rc == GP_OK) continue;
+        // smaller chunks take more memory, a vector each: a size that does not fit is passed over
+        refused = rc;
+        best = best0;
+        best_w = best_w0;
+        best_t = best_t0;
+        HIPC(ctx, hipStreamSynchronize(ctx->stream));
+        if (cn == p->chunk_nodes) {
+            p->plans.clear();
+            p->evaluated_with = 0;
+            for (DevBuf* b : {&p->vecs, &p->recs, &p->fit}) b->release();
+        }
     }
+    if (best < 0 && refused != GP_OK) return refused;
     if (best < 0) return set_err(ctx, GP_EINVAL, "no interpreter variant fits this population");
     if (best_pop) p = replace_population(ctx, pop, p, best_pop);
     // keep only the chosen launch's plans
@@ -2703,6 +2864,15 @@ int gp_autotune(gp_ctx* ctx, gp_handle pop, gp_handle cases, int* best_variant, 
     if (best_variant) *best_variant = best;
     if (best_ms) *best_ms = best_t;
     return GP_OK;
+}
+
+int gp_autotune(gp_ctx* ctx, gp_handle pop, gp_handle cases, int* best_variant, double* best_ms)
+{
+    if (!ctx) return GP_EINVAL;
+    std::lock_guard<std::mutex> lk(ctx->mu);
+    PoolScope pool(ctx);
+    HIPC(ctx, hipSetDevice(ctx->device));
+    return retry_if_short(ctx, [&] { return autotune(ctx, pop, cases, best_variant, best_ms); });
 }
 
 // Arguments shared by both index entry points.
@@ -2834,8 +3004,10 @@ int gp_index_trees(gp_ctx* ctx, int n_inputs, int64_t n_trees, const uint8_t* op
     std::lock_guard<std::mutex> lk(ctx->mu);
     PoolScope pool(ctx);
     HIPC(ctx, hipSetDevice(ctx->device));
-    return index_trees(ctx, n_inputs, n_trees, ops, offsets, n_nodes, valid, end, parent, strahler, device_ms,
-                       ctx->stream);
+    return retry_if_short(ctx, [&] {
+        return index_trees(ctx, n_inputs, n_trees, ops, offsets, n_nodes, valid, end, parent, strahler, device_ms,
+                           ctx->stream);
+    });
 }
 
 static_assert(GP_INDEX_NOALLOC_MAX_NODES == kIxStaticMaxNodes, "header and scratch array disagree");
