@@ -23,7 +23,7 @@ struct DevChunk {            // 32 bytes
 };
 
 // Counters that hand out a launch's work items (see next_item): one cache line
-// each, kCursors of them per launch.
+// each, up to kCursors of them per launch.
 constexpr int kCursors = 16;
 constexpr int kCursorStride = 32;         // in words
 
@@ -129,7 +129,7 @@ struct FitParams {
     const int32_t* pending_init = nullptr;
     int64_t n_pending = 0;
     unsigned int* cursor = nullptr;
-    int64_t n_cursors = 0;
+    int64_t cursor_words = 0;
     int64_t n_rows = 0;          // set by the launcher
 };
 
@@ -177,9 +177,9 @@ inline size_t variant_lds(const Variant& v, int n_inputs)
 int variant_count();
 Variant* variant_table();
 
-// pending = init; counter i at cursor[i * kCursorStride], i < n_cursors, = 0.
+// pending = init; cursor[0 .. cursor_words) = 0.
 hipError_t launch_init(int32_t* pending, const int32_t* init, int64_t n, unsigned int* cursor,
-                       int64_t n_cursors, hipStream_t s);
+                       int64_t cursor_words, hipStream_t s);
 hipError_t launch_eval(int variant, const EvalParams& p, int grid, hipStream_t s);
 hipError_t launch_fitness(int vtype, const FitParams& p, int64_t n, hipStream_t s);
 hipError_t launch_walk(int vtype, const WalkParams& p, int64_t n_children, hipStream_t s);

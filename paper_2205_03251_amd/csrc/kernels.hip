@@ -556,11 +556,11 @@ __global__ __launch_bounds__(64) void k_eval_bool_tbl(EvalParams p)
 
 // ------------------------------------------------------------- init
 __global__ void k_init(int32_t* pending, const int32_t* init, int64_t n, unsigned int* cursor,
-                       int64_t n_cursors)
+                       int64_t cursor_words)
 {
     const int64_t i0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     for (int64_t i = i0; i < n; i += (int64_t)gridDim.x * blockDim.x) pending[i] = init[i];
-    for (int64_t i = i0; i < n_cursors; i += (int64_t)gridDim.x * blockDim.x) cursor[i * kCursorStride] = 0u;
+    for (int64_t i = i0; i < cursor_words; i += (int64_t)gridDim.x * blockDim.x) cursor[i] = 0u;
 }
 
 // ---------------------------------------------------------- fitness
@@ -601,7 +601,7 @@ __device__ void reset_counters(const FitParams& p)
     if (!p.pending) return;
     const int64_t i0 = (int64_t)blockIdx.x * 256 + threadIdx.x, step = (int64_t)gridDim.x * 256;
     for (int64_t i = i0; i < p.n_pending; i += step) p.pending[i] = p.pending_init[i];
-    for (int64_t i = i0; i < p.n_cursors; i += step) p.cursor[i * kCursorStride] = 0u;
+    for (int64_t i = i0; i < p.cursor_words; i += step) p.cursor[i] = 0u;
 }
 
 template <int R>
@@ -966,11 +966,11 @@ hipError_t launch_eval(int variant, const EvalParams& p, int grid, hipStream_t s
 }
 
 hipError_t launch_init(int32_t* pending, const int32_t* init, int64_t n, unsigned int* cursor,
-                       int64_t n_cursors, hipStream_t s)
+                       int64_t cursor_words, hipStream_t s)
 {
-    int64_t need = std::max<int64_t>(n, n_cursors);
+    int64_t need = std::max<int64_t>(n, cursor_words);
     int grid = (int)std::min<int64_t>(4096, std::max<int64_t>(1, (need + 255) / 256));
-    hipLaunchKernelGGL(k_init, dim3(grid), dim3(256), 0, s, pending, init, n, cursor, n_cursors);
+    hipLaunchKernelGGL(k_init, dim3(grid), dim3(256), 0, s, pending, init, n, cursor, cursor_words);
     return hipGetLastError();
 }
 

@@ -113,8 +113,9 @@ struct Plan {
     DevBuf items;                // int64 work items
     DevBuf pending_init;         // int32 [n_chunks * n_slices]
     DevBuf pending;
-    DevBuf cursor;               // kCursors counters per launch (per tree in per-tree mode)
-    std::vector<int64_t> tree_item_begin, tree_item_count;
+    DevBuf cursor;               // item counters: kCursors, or each tree's in per-tree mode
+    int64_t cursor_words = 0;
+    std::vector<int64_t> tree_item_begin, tree_item_count, tree_cursor;    // tree_cursor: in words
     hipGraphExec_t graph = nullptr;
     gp_handle graph_cases = 0;
     ~Plan();

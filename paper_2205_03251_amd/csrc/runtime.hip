@@ -640,12 +640,28 @@ int ensure_eval_buffers(Ctx* c, Pop* p, const CaseSet* cs)
     return GP_OK;
 }
 
+// The item counters of a launch of n_items on at most `grid` workgroups.
+// Sixteen when a wave takes few items, since all ask for their first at once: 300 trees of 10..10^4
+// nodes (1.2 items a wave) 0.21 ms with 4, 0.13 with 16; 1000 of 10^3..10^4 (1.7) 0.22 and 0.14; 20 of up to
+// 10^6 (9) 0.63 and 0.53; Boolean, 400 trees on 4096 cases (4) 0.32 and 0.25.  Four when it takes many, which
+// keep the order better: three inputs, 1500 cases (18) 0.71 and 0.94 ms; 1000 large trees (77) 5.57 and 5.89.
+// A launch per tree keeps its counters beside every other tree's: one, in a
+// word of its own, up to kOneCursor items (2.4 us of one counter at most), so
+// that a thousand small trees hold 4 KB of counters and not 2 MB.
+constexpr int64_t kOneCursor = 256;
+static int32_t item_cursors(int64_t n_items, int64_t grid, bool per_tree)
+{
+    if (per_tree && n_items <= kOneCursor) return 1;
+    static_assert(kCursors == 16, "counters allocated per launch");
+    return n_items <= 12 * grid ? 16 : 4;
+}
+
 // Counters of a plan to their initial values, in front of a run that no
 // completed run left them set for.
 static int set_counters(Ctx* c, Pop* p, Plan* pl, hipStream_t s)
 {
     HIPC(c, launch_init(pl->pending.as<int32_t>(), pl->pending_init.as<int32_t>(), p->n_chunks * pl->n_slices,
-                        pl->cursor.as<unsigned int>(), (pl->per_tree ? p->n_trees : 1) * kCursors, s));
+                        pl->cursor.as<unsigned int>(), pl->cursor_words, s));
     pl->counters_set = true;
     return GP_OK;
 }
@@ -692,7 +708,12 @@ static int make_plan(Ctx* c, Pop* p, const CaseSet* cs, Launch L, bool per_tree,
     RC(upload(c, pl->items, items.data(), items.size() * sizeof(int64_t), stream));
     RC(upload(c, pl->pending_init, pend.data(), pend.size() * sizeof(int32_t), stream));
     RC(dev_alloc(c, pl->pending, pend.size() * sizeof(int32_t)));
-    RC(dev_alloc(c, pl->cursor, (size_t)(per_tree ? p->n_trees : 1) * kCursors * kCursorStride * sizeof(unsigned int)));
+    pl->cursor_words = per_tree ? 0 : kCursors * kCursorStride;
+    for (int64_t n : pl->tree_item_count) {
+        pl->tree_cursor.push_back(pl->cursor_words);
+        pl->cursor_words += item_cursors(n, 1, true) == 1 ? 1 : kCursors * kCursorStride;
+    }
+    RC(dev_alloc(c, pl->cursor, (size_t)pl->cursor_words * sizeof(unsigned int)));
     pl->grid = (int)std::max<int64_t>(1, std::min<int64_t>(resident_grid(c, v, pl->waves_per_cu), pl->n_items));
     RC(set_counters(c, p, pl.get(), stream));
     HIPC(c, hipStreamSynchronize(stream));
@@ -717,12 +738,7 @@ static EvalParams eval_params(Pop* p, const CaseSet* cs, Plan* pl)
     e.stride = cs->stride;
     e.n_slices = pl->n_slices;
     e.n_inputs = cs->n_inputs;
-    // Sixteen counters when a wave takes few items, since all ask for their first at once: 300 trees of 10..10^4
-    // nodes (1.2 items a wave) 0.21 ms with 4, 0.13 with 16; 1000 of 10^3..10^4 (1.7) 0.22 and 0.14; 20 of up to
-    // 10^6 (9) 0.63 and 0.53; Boolean, 400 trees on 4096 cases (4) 0.32 and 0.25.  Four when it takes many, which
-    // keep the order better: three inputs, 1500 cases (18) 0.71 and 0.94 ms; 1000 large trees (77) 5.57 and 5.89.
-    e.n_cursors = pl->n_items <= 12 * (int64_t)pl->grid ? 16 : 4;
-    static_assert(kCursors == 16, "counters allocated per launch");
+    e.n_cursors = item_cursors(pl->n_items, pl->grid, false);
     return e;
 }
 
@@ -744,7 +760,7 @@ static FitParams fit_params(Pop* p, const CaseSet* cs)
 static int enqueue_body(Ctx* c, Pop* p, const CaseSet* cs, Plan* pl, hipStream_t s, int64_t* launches,
                         bool time_kernel, const FullOut* out)
 {
-    const int64_t n_pend = p->n_chunks * pl->n_slices, n_cur = (pl->per_tree ? p->n_trees : 1) * kCursors;
+    const int64_t n_pend = p->n_chunks * pl->n_slices;
     int64_t nl = 0;
     if (!pl->counters_set) {
         RC(set_counters(c, p, pl, s));
@@ -762,8 +778,9 @@ static int enqueue_body(Ctx* c, Pop* p, const CaseSet* cs, Plan* pl, hipStream_t
             EvalParams et = e;
             et.items = e.items + pl->tree_item_begin[t];
             et.n_items = pl->tree_item_count[t];
-            et.cursor = e.cursor + t * kCursors * kCursorStride;
+            et.cursor = e.cursor + pl->tree_cursor[t];
             const int grid = (int)std::max<int64_t>(1, std::min<int64_t>(full, et.n_items));
+            et.n_cursors = item_cursors(et.n_items, grid, true);
             HIPC(c, launch_eval(pl->variant, et, grid, s));
             ++nl;
         }
@@ -774,7 +791,7 @@ static int enqueue_body(Ctx* c, Pop* p, const CaseSet* cs, Plan* pl, hipStream_t
     f.pending_init = pl->pending_init.as<int32_t>();
     f.n_pending = n_pend;
     f.cursor = pl->cursor.as<unsigned int>();
-    f.n_cursors = n_cur;
+    f.cursor_words = pl->cursor_words;
     if (out) {
         f.rows_dst = out->rows;
         f.fit_dst = out->fit;
@@ -877,7 +894,8 @@ int enqueue_promoted(Ctx* c, Pop* p, const Pop* src, gp_handle cases_h, const Ca
         RC(upload(c, pl.items, items.data(), items.size() * sizeof(int64_t), s));
         RC(upload(c, pl.pending_init, pend.data(), pend.size() * sizeof(int32_t), s));
         RC(dev_alloc(c, pl.pending, pend.size() * sizeof(int32_t)));
-        RC(dev_alloc(c, pl.cursor, kCursors * kCursorStride * sizeof(unsigned int)));
+        pl.cursor_words = kCursors * kCursorStride;
+        RC(dev_alloc(c, pl.cursor, (size_t)pl.cursor_words * sizeof(unsigned int)));
         pl.grid = (int)std::max<int64_t>(1, std::min<int64_t>(resident_grid(c, v, pl.waves_per_cu), pl.n_items));
         RC(enqueue_body(c, p, cs, &pl, s, nullptr, false, nullptr));
     } else {
