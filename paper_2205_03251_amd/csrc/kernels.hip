@@ -928,7 +928,8 @@ __global__ __launch_bounds__(256) void k_walk_bool(WalkParams p)
 // ---------------------------------------------------------- variants
 // Interpreter variants: K test cases (words) per lane and S stack slots.
 // Fewer slots free registers for more resident waves; a population can use
-// a variant when its programs need at most S slots.
+// a variant when its programs need at most S slots.  Callers name variants by
+// index: new ones go to the end.
 static Variant g_variants[] = {
     {"f32_k1_s16", 0, 1, 16, (const void*)k_eval_f32<1, 16>, 0},
     {"f32_k2_s16", 0, 2, 16, (const void*)k_eval_f32<2, 16>, 0},
@@ -940,18 +941,18 @@ static Variant g_variants[] = {
     {"f32t_k8_s10", 0, 8, 10, (const void*)k_eval_f32_tbl<8, 10, Form::Table>, 0, 1, 0},
     {"f32d_k4_s10", 0, 4, 10, (const void*)k_eval_f32_tbl<4, 10, Form::Direct>, 0, 1, 0, 0, 1},
     {"f32d_k8_s10", 0, 8, 10, (const void*)k_eval_f32_tbl<8, 10, Form::Direct>, 0, 1, 0, 0, 1},
-    {"f32d_k1_s10", 0, 1, 10, (const void*)k_eval_f32_tbl<1, 10, Form::Direct>, 0, 1, 0, 0, 1},
-    {"f32d_k2_s10", 0, 2, 10, (const void*)k_eval_f32_tbl<2, 10, Form::Direct>, 0, 1, 0, 0, 1},
-    {"f32r_k1_s10", 0, 1, 10, (const void*)k_eval_f32_tbl<1, 10, Form::Rows>, 0, 1, 0, 0, 2},
-    {"f32r_k2_s10", 0, 2, 10, (const void*)k_eval_f32_tbl<2, 10, Form::Rows>, 0, 1, 0, 0, 2},
-    {"f32r_k4_s10", 0, 4, 10, (const void*)k_eval_f32_tbl<4, 10, Form::Rows>, 0, 1, 0, 0, 2},
-    {"f32r_k8_s10", 0, 8, 10, (const void*)k_eval_f32_tbl<8, 10, Form::Rows>, 0, 1, 0, 0, 2},
     {"bool_k1_s16", 1, 1, 16, (const void*)k_eval_bool<1, 16>, 0},
     {"bool_k2_s16", 1, 2, 16, (const void*)k_eval_bool<2, 16>, 0},
     {"bool_k1_s10", 1, 1, 10, (const void*)k_eval_bool<1, 10>, 0},
     {"boolw_s10", 1, 1, 10, (const void*)k_eval_bool_tbl<1, 10, true>, 0, 1, kBoolWordInputs, 1},
     {"boolt_k1_s10", 1, 1, 10, (const void*)k_eval_bool_tbl<1, 10>, 0, 1, kBoolRegInputs},
     {"boolt_k2_s10", 1, 2, 10, (const void*)k_eval_bool_tbl<2, 10>, 0, 1, kBoolRegInputs},
+    {"f32d_k1_s10", 0, 1, 10, (const void*)k_eval_f32_tbl<1, 10, Form::Direct>, 0, 1, 0, 0, 1},
+    {"f32d_k2_s10", 0, 2, 10, (const void*)k_eval_f32_tbl<2, 10, Form::Direct>, 0, 1, 0, 0, 1},
+    {"f32r_k1_s10", 0, 1, 10, (const void*)k_eval_f32_tbl<1, 10, Form::Rows>, 0, 1, 0, 0, 2},
+    {"f32r_k2_s10", 0, 2, 10, (const void*)k_eval_f32_tbl<2, 10, Form::Rows>, 0, 1, 0, 0, 2},
+    {"f32r_k4_s10", 0, 4, 10, (const void*)k_eval_f32_tbl<4, 10, Form::Rows>, 0, 1, 0, 0, 2},
+    {"f32r_k8_s10", 0, 8, 10, (const void*)k_eval_f32_tbl<8, 10, Form::Rows>, 0, 1, 0, 0, 2},
 };
 
 int variant_count() { return (int)(sizeof(g_variants) / sizeof(g_variants[0])); }
