@@ -63,6 +63,22 @@ __device__ __forceinline__ uint64_t bop(uint64_t a, uint64_t b)
     else return ~(a | b);
 }
 
+__device__ __forceinline__ uint64_t bop_rt(int f, uint64_t v, uint64_t s)
+{
+    switch (f) {
+    case 0: return bop<0>(v, s);
+    case 1: return bop<1>(v, s);
+    case 2: return bop<2>(v, s);
+    default: return bop<3>(v, s);
+    }
+}
+
+// Equal on the test cases: of the last word only the bits in tail are any.
+__device__ __forceinline__ bool same_bits(uint64_t a, uint64_t b, bool last, uint64_t tail)
+{
+    return ((a ^ b) & (last ? tail : ~0ull)) == 0;
+}
+
 // Bit-equal, or both NaN.
 __device__ __forceinline__ bool same_f32(float a, float b)
 {
@@ -671,24 +687,66 @@ __global__ __launch_bounds__(256) void k_fit_bool(FitParams p)
 }
 
 // ------------------------------------------------------ incremental walk
-// Levels are taken in groups: the vectors of a whole group are loaded before
-// its first level is computed (their addresses do not depend on the walk), and
-// the group's levels are compared by one exchange between the waves instead of
+// Levels are taken in groups: the vectors of G levels are loaded before the
+// first is computed (their addresses do not depend on the walk), and the
+// group's levels are compared by one exchange between the waves instead of
 // one a level.  Levels past the stop within its group are computed for
 // nothing; what they leave is not used (on a stop the child's values are the
-// mother's).  The chain is bound by memory latency: a trip and two barriers
-// per group instead of per level.  300 children of trees of 10^4..10^6 nodes
-// on 1024 cases (up to 1000 levels): 0.55 -> 0.10 ms.
-template <int R> constexpr int walk_group() { return R <= 2 ? 16 : R <= 4 ? 8 : R <= 8 ? 4 : R <= 16 ? 2 : 1; }
+// mother's).  A thread holds R values; where G levels of all of them do not
+// fit the registers they go through B at a time, each block through its G
+// levels (a block's values depend on its own only).  Threads past the last case
+// carry that case along, so that a comparison needs no test for the end.
+//
+// One chain is bound by memory latency: a trip and two barriers per group
+// instead of per level (300 children of trees of 10^4..10^6 nodes on 1024 cases,
+// up to 1000 levels, 0.55 -> 0.10 ms).  Many chains on many cases are bound by
+// memory and by how many waves are resident, 2 at least.  Kernel times in us of
+// walks of 200 levels, cached, a level at a time against these shapes:
+//   children         64          256          700         1500
+//   1024 cases    155   77    191   79    236  122    371  244
+//   4096          365  184    406  243    476  450    859  905
+//   8192          927  451    957  479    990  902   2120 1830
+//   16384        1830  875   1866  950   3630 2630   5715 4370
+//   2^16 words    174   91    209  131    337  275    430  444
+//   2^17          355  179    381  256    489  483   1023 1001
+//   2^18          576  424    597  465    712  693   1470 1427
+// and co-evaluated 181 79, 183 80, 211 96, 292 137 on 1024 cases; 2290 682, 2330
+// 718, 6840 1470, 13740 2560 on 16384; 706 272, 720 283, 750 470, 1490 900 on 2^18.
+//
+// MANY: from a number of children that fills the chip on, the shapes that keep
+// more waves resident, which for words is a level at a time (2^18 cases, 1500
+// children: 1990 us with two levels of 8 words).  For 32 values 1024 us with
+// the first shape and 902 with the second at 700 children, 480 and 635 at 256.
+template <int R, bool MANY> struct WalkShape {
+    static constexpr int G = R <= 2 ? 16 : R <= 4 ? 8 : R <= 8 ? 4 : R <= 16 ? 2 : R <= 32 ? 4 : 2;
+    static constexpr int B = R <= 16 ? R : R <= 32 ? 8 : 16;
+};
+template <> struct WalkShape<32, true> {
+    static constexpr int G = 4, B = 4;
+};
+template <> struct WalkShape<64, true> {
+    static constexpr int G = 1, B = 16;
+};
+template <int R> struct WalkWordShape {
+    static constexpr int G = R <= 1 ? 16 : R <= 2 ? 8 : R <= 4 ? 4 : 2, B = R <= 4 ? R : 8;
+};
+template <int R> struct CoevalShape {
+    static constexpr int G = R <= 2 ? 16 : R <= 8 ? 8 : 1, B = R <= 32 ? R : 32;
+};
+template <int R> struct CoevalWordShape {
+    static constexpr int G = R <= 1 ? 16 : R <= 2 ? 8 : R <= 4 ? 4 : 2, B = R <= 4 ? R : 8;
+};
 
-// v = f(v, s), the walked operand v on the right when `right`.
-template <int R>
-__device__ __forceinline__ void walk_apply(int f, bool right, float (&v)[R], const float (&s)[R])
+// v = f(v, s) for the B values of v from b, the walked operand v on the right
+// when `right`.
+template <int R, int B>
+__device__ __forceinline__ void walk_apply(int f, bool right, float (&v)[R], int b, const float (&s)[B])
 {
     switch (f) {
 #define GP_WALK(F)                                                                            \
     case F:                                                                                   \
-        UNROLL for (int m = 0; m < R; ++m) v[m] = right ? fop<F>(s[m], v[m]) : fop<F>(v[m], s[m]); \
+        UNROLL for (int j = 0; j < B; ++j)                                                    \
+            v[b + j] = right ? fop<F>(s[j], v[b + j]) : fop<F>(v[b + j], s[j]);               \
         break;
         GP_WALK(0)
         GP_WALK(1)
@@ -699,13 +757,13 @@ __device__ __forceinline__ void walk_apply(int f, bool right, float (&v)[R], con
     }
 }
 
-template <int R>
-__device__ __forceinline__ void walk_apply(int f, uint64_t (&v)[R], const uint64_t (&s)[R])
+template <int R, int B>
+__device__ __forceinline__ void walk_apply(int f, uint64_t (&v)[R], int b, const uint64_t (&s)[B])
 {
     switch (f) {
 #define GP_WALK(F)                                                                            \
     case F:                                                                                   \
-        UNROLL for (int m = 0; m < R; ++m) v[m] = bop<F>(v[m], s[m]);                         \
+        UNROLL for (int j = 0; j < B; ++j) v[b + j] = bop<F>(v[b + j], s[j]);                 \
         break;
         GP_WALK(0)
         GP_WALK(1)
@@ -714,6 +772,16 @@ __device__ __forceinline__ void walk_apply(int f, uint64_t (&v)[R], const uint64
         GP_WALK(3)
 #undef GP_WALK
     }
+}
+
+// This thread's number, not known to be the same in every pass of a loop: what
+// is derived from it per value (clamped index, whether it is past the end) is
+// computed again for each group of levels instead of held for all of them.
+__device__ __forceinline__ int walk_tid()
+{
+    int t = threadIdx.x;
+    asm volatile("" : "+v"(t));
+    return t;
 }
 
 // The first level of a group (0 .. G - 1) at which every thread's bit of eq is
@@ -736,8 +804,8 @@ __device__ __forceinline__ int walk_first_equal(uint32_t eq, int G, int n, int t
 // child's running vector and the other operand taken from the mother's
 // recorded sibling vector, then compares with the mother's vector at that
 // ancestor.  A workgroup-wide AND over the test cases decides the stop.
-template <int R>
-__global__ __launch_bounds__(256) void k_walk_f32(WalkParams p)
+template <int R, bool MANY = false>
+__global__ __launch_bounds__(256, R == 64 ? 2 : 1) void k_walk_f32(WalkParams p)
 {
     __shared__ double red[256];
     __shared__ uint32_t ex[2][4];
@@ -757,45 +825,46 @@ __global__ __launch_bounds__(256) void k_walk_f32(WalkParams p)
     const float* recs = (const float*)w_recs;
     const float* dv = (const float*)p.donor_vecs + (int64_t)donor_slot * p.stride;
     float v[R];
-    UNROLL for (int m = 0; m < R; ++m) {
-        const int64_t i = tid + 256 * m;
-        v[m] = (i < T) ? dv[i] : 0.0f;
-    }
+    UNROLL for (int m = 0; m < R; ++m) v[m] = dv[min((int64_t)(tid + 256 * m), T - 1)];
     const float* a0 = at_point >= 0 ? recs + (int64_t)at_point * p.stride
                                     : in + (int64_t)(-at_point - 1) * p.stride;
     bool eq = true;
-    UNROLL for (int m = 0; m < R; ++m) {
-        const int64_t i = tid + 256 * m;
-        if (i < T) eq = eq && same_f32(v[m], a0[i]);
-    }
+    UNROLL for (int m = 0; m < R; ++m) eq = eq && same_f32(v[m], a0[min((int64_t)(tid + 256 * m), T - 1)]);
     int stop = -1;
     if (__syncthreads_and(eq)) {
         stop = 0;
     } else {
-        constexpr int G = walk_group<R>();
-        uint32_t at[R];                         // threads past the last case read it again
-        UNROLL for (int m = 0; m < R; ++m) at[m] = (uint32_t)min((int64_t)(tid + 256 * m), T - 1);
+        constexpr int G = WalkShape<R, MANY>::G, B = WalkShape<R, MANY>::B;
+        static_assert(R % B == 0, "whole blocks");
         for (int k = 0; k < n_levels && stop < 0; k += G) {
-            float sv[G][R], pv[G][R];
-            int fs[G];
-            UNROLL for (int g = 0; g < G; ++g) {
-                const GP_CONST SpineLvl* lp = cst(levels) + min(k + g, n_levels - 1);
-                const int32_t sib = lp->sib, par = lp->par;
-                fs[g] = lp->fside;
-                const float* sb = sib >= 0 ? recs + (int64_t)sib * p.stride : in + (int64_t)(-sib - 1) * p.stride;
-                const float* pr = recs + (int64_t)par * p.stride;
-                UNROLL for (int m = 0; m < R; ++m) {
-                    sv[g][m] = sb[at[m]];
-                    pv[g][m] = pr[at[m]];
+            uint32_t same = ~0u;
+            UNROLL for (int b = 0; b < R; b += B) {
+                if (b > 0 && 256 * b >= T) break;
+                const int t = R > B ? walk_tid() : tid;
+                float sv[G][B], pv[G][B];
+                uint32_t at[B];                 // threads past the last case read it again
+                UNROLL for (int j = 0; j < B; ++j) at[j] = (uint32_t)min((int64_t)(t + 256 * (b + j)), T - 1);
+                int fs[G];
+                UNROLL for (int g = 0; g < G; ++g) {
+                    const GP_CONST SpineLvl* lp = cst(levels) + min(k + g, n_levels - 1);
+                    const int32_t sib = lp->sib, par = lp->par;
+                    fs[g] = lp->fside;
+                    const float* sb = sib >= 0 ? recs + (int64_t)sib * p.stride : in + (int64_t)(-sib - 1) * p.stride;
+                    const float* pr = recs + (int64_t)par * p.stride;
+                    UNROLL for (int j = 0; j < B; ++j) {
+                        sv[g][j] = sb[at[j]];
+                        pv[g][j] = pr[at[j]];
+                    }
                 }
-            }
-            uint32_t same = 0;
-            UNROLL for (int g = 0; g < G; ++g) {
-                if (k + g >= n_levels) break;
-                walk_apply<R>(fs[g] & 3, (fs[g] & 4) != 0, v, sv[g]);
-                uint32_t e = 1;
-                UNROLL for (int m = 0; m < R; ++m) e &= tid + 256 * m >= T || same_f32(v[m], pv[g][m]) ? 1u : 0u;
-                same |= e << g;
+                uint32_t mine = 0;
+                UNROLL for (int g = 0; g < G; ++g) {
+                    if (k + g >= n_levels) break;
+                    walk_apply<R, B>(fs[g] & 3, (fs[g] & 4) != 0, v, b, sv[g]);
+                    uint32_t e = 1;
+                    UNROLL for (int j = 0; j < B; ++j) e &= same_f32(v[b + j], pv[g][j]) ? 1u : 0u;
+                    mine |= e << g;
+                }
+                same &= mine;
             }
             const int first = walk_first_equal(same, G, n_levels - k, k / G, ex);
             if (first >= 0) stop = k + first + 1;
@@ -831,7 +900,7 @@ __global__ __launch_bounds__(256) void k_walk_f32(WalkParams p)
     }
 }
 
-template <int R>
+template <int R, bool MANY = false>
 __global__ __launch_bounds__(256) void k_walk_bool(WalkParams p)
 {
     __shared__ int64_t red[256];
@@ -853,48 +922,67 @@ __global__ __launch_bounds__(256) void k_walk_bool(WalkParams p)
     const uint64_t* recs = (const uint64_t*)w_recs;
     const uint64_t* dv = (const uint64_t*)p.donor_vecs + (int64_t)donor_slot * p.stride;
     uint64_t v[R];
-    UNROLL for (int m = 0; m < R; ++m) {
-        const int64_t i = tid + 256 * m;
-        v[m] = (i < W) ? dv[i] : 0ull;
-    }
+    const uint64_t tail = valid_bits(W - 1, T);
+    UNROLL for (int m = 0; m < R; ++m) v[m] = dv[min((int64_t)(tid + 256 * m), W - 1)];
     const uint64_t* a0 = at_point >= 0 ? recs + (int64_t)at_point * p.stride
                                        : in + (int64_t)(-at_point - 1) * p.stride;
     bool eq = true;
     UNROLL for (int m = 0; m < R; ++m) {
-        const int64_t i = tid + 256 * m;
-        if (i < W) eq = eq && (((v[m] ^ a0[i]) & valid_bits(i, T)) == 0);
+        const int64_t i = min((int64_t)(tid + 256 * m), W - 1);
+        eq = eq && same_bits(v[m], a0[i], i == W - 1, tail);
     }
     int stop = -1;
     if (__syncthreads_and(eq)) {
         stop = 0;
-    } else {
-        constexpr int G = walk_group<2 * R>();
-        uint32_t at[R];                         // threads past the last word read it again
-        UNROLL for (int m = 0; m < R; ++m) at[m] = (uint32_t)min((int64_t)(tid + 256 * m), W - 1);
-        for (int k = 0; k < n_levels && stop < 0; k += G) {
-            uint64_t sv[G][R], pv[G][R];
-            int fs[G];
-            UNROLL for (int g = 0; g < G; ++g) {
-                const GP_CONST SpineLvl* lp = cst(levels) + min(k + g, n_levels - 1);
-                const int32_t sib = lp->sib, par = lp->par;
-                fs[g] = lp->fside;
-                const uint64_t* sb = sib >= 0 ? recs + (int64_t)sib * p.stride : in + (int64_t)(-sib - 1) * p.stride;
-                const uint64_t* pr = recs + (int64_t)par * p.stride;
-                UNROLL for (int m = 0; m < R; ++m) {
-                    sv[g][m] = sb[at[m]];
-                    pv[g][m] = pr[at[m]];
+    } else if constexpr (MANY) {
+        for (int k = 0; k < n_levels && stop < 0; ++k) {
+            const GP_CONST SpineLvl* lp = cst(levels) + k;
+            const int32_t sib = lp->sib, par = lp->par, fs = lp->fside;
+            const uint64_t* sb = sib >= 0 ? recs + (int64_t)sib * p.stride : in + (int64_t)(-sib - 1) * p.stride;
+            const uint64_t* pr = recs + (int64_t)par * p.stride;
+            eq = true;
+            UNROLL for (int m = 0; m < R; ++m) {
+                const int64_t i = tid + 256 * m;
+                if (i < W) {
+                    v[m] = bop_rt(fs & 3, v[m], sb[i]);
+                    eq = eq && same_bits(v[m], pr[i], i == W - 1, tail);
                 }
             }
-            uint32_t same = 0;
-            UNROLL for (int g = 0; g < G; ++g) {
-                if (k + g >= n_levels) break;
-                walk_apply<R>(fs[g] & 3, v, sv[g]);
-                uint32_t e = 1;
-                UNROLL for (int m = 0; m < R; ++m) {
-                    const int64_t i = tid + 256 * m;
-                    e &= i >= W || ((v[m] ^ pv[g][m]) & valid_bits(i, T)) == 0 ? 1u : 0u;
+            if (__syncthreads_and(eq)) stop = k + 1;
+        }
+    } else {
+        constexpr int G = WalkWordShape<R>::G, B = WalkWordShape<R>::B;
+        static_assert(R % B == 0, "whole blocks");
+        for (int k = 0; k < n_levels && stop < 0; k += G) {
+            uint32_t same = ~0u;
+            UNROLL for (int b = 0; b < R; b += B) {
+                if (b > 0 && 256 * b >= W) break;
+                const int t = R > B ? walk_tid() : tid;
+                uint64_t sv[G][B], pv[G][B];
+                uint32_t at[B];                 // threads past the last word read it again
+                UNROLL for (int j = 0; j < B; ++j) at[j] = (uint32_t)min((int64_t)(t + 256 * (b + j)), W - 1);
+                int fs[G];
+                UNROLL for (int g = 0; g < G; ++g) {
+                    const GP_CONST SpineLvl* lp = cst(levels) + min(k + g, n_levels - 1);
+                    const int32_t sib = lp->sib, par = lp->par;
+                    fs[g] = lp->fside;
+                    const uint64_t* sb = sib >= 0 ? recs + (int64_t)sib * p.stride : in + (int64_t)(-sib - 1) * p.stride;
+                    const uint64_t* pr = recs + (int64_t)par * p.stride;
+                    UNROLL for (int j = 0; j < B; ++j) {
+                        sv[g][j] = sb[at[j]];
+                        pv[g][j] = pr[at[j]];
+                    }
                 }
-                same |= e << g;
+                uint32_t mine = 0;
+                UNROLL for (int g = 0; g < G; ++g) {
+                    if (k + g >= n_levels) break;
+                    walk_apply<R, B>(fs[g] & 3, v, b, sv[g]);
+                    uint32_t e = 1;
+                    UNROLL for (int j = 0; j < B; ++j)
+                        e &= same_bits(v[b + j], pv[g][j], at[j] == (uint32_t)(W - 1), tail) ? 1u : 0u;
+                    mine |= e << g;
+                }
+                same &= mine;
             }
             const int first = walk_first_equal(same, G, n_levels - k, k / G, ex);
             if (first >= 0) stop = k + first + 1;
@@ -1013,7 +1101,7 @@ hipError_t launch_fitness(int vtype, const FitParams& q, int64_t n, hipStream_t 
 // the removed subtree's.  A walk that neither stops nor reaches the root in
 // this round leaves v and m for the next one.
 template <int R>
-__global__ __launch_bounds__(256) void k_coeval_f32(CoParams p)
+__global__ __launch_bounds__(256, R >= 32 ? 2 : 1) void k_coeval_f32(CoParams p)
 {
     __shared__ double red[256];
     __shared__ uint32_t ex[2][4];
@@ -1031,37 +1119,43 @@ __global__ __launch_bounds__(256) void k_coeval_f32(CoParams p)
     const int64_t T = p.n_valid;
     float v[R], m[R];
     UNROLL for (int k = 0; k < R; ++k) {
-        const int64_t i = tid + 256 * k;
-        v[k] = (i < T) ? vin[i] : 0.0f;
-        m[k] = (i < T) ? min_[i] : 0.0f;
+        const int64_t i = min((int64_t)(tid + 256 * k), T - 1);
+        v[k] = vin[i];
+        m[k] = min_[i];
     }
     int stop = -2;
     if (check0) {
         bool eq = true;
-        UNROLL for (int k = 0; k < R; ++k)
-            if (tid + 256 * k < T) eq = eq && same_f32(v[k], m[k]);
+        UNROLL for (int k = 0; k < R; ++k) eq = eq && same_f32(v[k], m[k]);
         if (__syncthreads_and(eq)) stop = 0;
     }
-    constexpr int G = walk_group<R>();
-    uint32_t at[R];                             // threads past the last case read it again
-    UNROLL for (int k = 0; k < R; ++k) at[k] = (uint32_t)min((int64_t)(tid + 256 * k), T - 1);
+    constexpr int G = CoevalShape<R>::G, B = CoevalShape<R>::B;
+    static_assert(R % B == 0, "whole blocks");
     for (int l = 0; stop == -2 && l < n_levels; l += G) {
-        float sv[G][R];
-        int fs[G];
-        UNROLL for (int g = 0; g < G; ++g) {
-            const GP_CONST CoLevel* lp = cst(levels) + min(l + g, n_levels - 1);
-            const float* sb = (const float*)lp->sib;
-            fs[g] = lp->fside;
-            UNROLL for (int k = 0; k < R; ++k) sv[g][k] = sb[at[k]];
-        }
-        uint32_t same = 0;
-        UNROLL for (int g = 0; g < G; ++g) {
-            if (l + g >= n_levels) break;
-            walk_apply<R>(fs[g] & 3, (fs[g] & 4) != 0, v, sv[g]);
-            walk_apply<R>(fs[g] & 3, (fs[g] & 4) != 0, m, sv[g]);
-            uint32_t e = 1;
-            UNROLL for (int k = 0; k < R; ++k) e &= tid + 256 * k >= T || same_f32(v[k], m[k]) ? 1u : 0u;
-            same |= e << g;
+        uint32_t same = ~0u;
+        UNROLL for (int b = 0; b < R; b += B) {
+            if (b > 0 && 256 * b >= T) break;
+            const int t = R > B ? walk_tid() : tid;
+            float sv[G][B];
+            uint32_t at[B];                     // threads past the last case read it again
+            UNROLL for (int j = 0; j < B; ++j) at[j] = (uint32_t)min((int64_t)(t + 256 * (b + j)), T - 1);
+            int fs[G];
+            UNROLL for (int g = 0; g < G; ++g) {
+                const GP_CONST CoLevel* lp = cst(levels) + min(l + g, n_levels - 1);
+                const float* sb = (const float*)lp->sib;
+                fs[g] = lp->fside;
+                UNROLL for (int j = 0; j < B; ++j) sv[g][j] = sb[at[j]];
+            }
+            uint32_t mine = 0;
+            UNROLL for (int g = 0; g < G; ++g) {
+                if (l + g >= n_levels) break;
+                walk_apply<R, B>(fs[g] & 3, (fs[g] & 4) != 0, v, b, sv[g]);
+                walk_apply<R, B>(fs[g] & 3, (fs[g] & 4) != 0, m, b, sv[g]);
+                uint32_t e = 1;
+                UNROLL for (int j = 0; j < B; ++j) e &= same_f32(v[b + j], m[b + j]) ? 1u : 0u;
+                mine |= e << g;
+            }
+            same &= mine;
         }
         const int first = walk_first_equal(same, G, n_levels - l, l / G, ex);
         if (first >= 0) stop = level_base + l + first + 1;
@@ -1118,43 +1212,46 @@ __global__ __launch_bounds__(256) void k_coeval_bool(CoParams p)
     const int64_t T = p.n_valid;
     const int64_t W = (T + 63) / 64;
     uint64_t v[R], m[R];
+    const uint64_t tail = valid_bits(W - 1, T);
     UNROLL for (int k = 0; k < R; ++k) {
-        const int64_t i = tid + 256 * k;
-        v[k] = (i < W) ? vin[i] : 0ull;
-        m[k] = (i < W) ? min_[i] : 0ull;
+        const int64_t i = min((int64_t)(tid + 256 * k), W - 1);
+        v[k] = vin[i];
+        m[k] = min_[i];
     }
     int stop = -2;
     if (check0) {
         bool eq = true;
-        UNROLL for (int k = 0; k < R; ++k) {
-            const int64_t i = tid + 256 * k;
-            if (i < W) eq = eq && (((v[k] ^ m[k]) & valid_bits(i, T)) == 0);
-        }
+        UNROLL for (int k = 0; k < R; ++k) eq = eq && same_bits(v[k], m[k], tid + 256 * k >= W - 1, tail);
         if (__syncthreads_and(eq)) stop = 0;
     }
-    constexpr int G = walk_group<2 * R>();
-    uint32_t at[R];                             // threads past the last word read it again
-    UNROLL for (int k = 0; k < R; ++k) at[k] = (uint32_t)min((int64_t)(tid + 256 * k), W - 1);
+    constexpr int G = CoevalWordShape<R>::G, B = CoevalWordShape<R>::B;
+    static_assert(R % B == 0, "whole blocks");
     for (int l = 0; stop == -2 && l < n_levels; l += G) {
-        uint64_t sv[G][R];
-        int fs[G];
-        UNROLL for (int g = 0; g < G; ++g) {
-            const GP_CONST CoLevel* lp = cst(levels) + min(l + g, n_levels - 1);
-            const uint64_t* sb = (const uint64_t*)lp->sib;
-            fs[g] = lp->fside;
-            UNROLL for (int k = 0; k < R; ++k) sv[g][k] = sb[at[k]];
-        }
-        uint32_t same = 0;
-        UNROLL for (int g = 0; g < G; ++g) {
-            if (l + g >= n_levels) break;
-            walk_apply<R>(fs[g] & 3, v, sv[g]);
-            walk_apply<R>(fs[g] & 3, m, sv[g]);
-            uint32_t e = 1;
-            UNROLL for (int k = 0; k < R; ++k) {
-                const int64_t i = tid + 256 * k;
-                e &= i >= W || ((v[k] ^ m[k]) & valid_bits(i, T)) == 0 ? 1u : 0u;
+        uint32_t same = ~0u;
+        UNROLL for (int b = 0; b < R; b += B) {
+            if (b > 0 && 256 * b >= W) break;
+            const int t = R > B ? walk_tid() : tid;
+            uint64_t sv[G][B];
+            uint32_t at[B];                     // threads past the last word read it again
+            UNROLL for (int j = 0; j < B; ++j) at[j] = (uint32_t)min((int64_t)(t + 256 * (b + j)), W - 1);
+            int fs[G];
+            UNROLL for (int g = 0; g < G; ++g) {
+                const GP_CONST CoLevel* lp = cst(levels) + min(l + g, n_levels - 1);
+                const uint64_t* sb = (const uint64_t*)lp->sib;
+                fs[g] = lp->fside;
+                UNROLL for (int j = 0; j < B; ++j) sv[g][j] = sb[at[j]];
             }
-            same |= e << g;
+            uint32_t mine = 0;
+            UNROLL for (int g = 0; g < G; ++g) {
+                if (l + g >= n_levels) break;
+                walk_apply<R, B>(fs[g] & 3, v, b, sv[g]);
+                walk_apply<R, B>(fs[g] & 3, m, b, sv[g]);
+                uint32_t e = 1;
+                UNROLL for (int j = 0; j < B; ++j)
+                    e &= same_bits(v[b + j], m[b + j], at[j] == (uint32_t)(W - 1), tail) ? 1u : 0u;
+                mine |= e << g;
+            }
+            same &= mine;
         }
         const int first = walk_first_equal(same, G, n_levels - l, l / G, ex);
         if (first >= 0) stop = level_base + l + first + 1;
@@ -1559,33 +1656,36 @@ hipError_t launch_pack(PackParams& p, hipStream_t s)
 hipError_t launch_walk(int vtype, const WalkParams& p, int64_t n_children, hipStream_t s)
 {
     if (n_children <= 0) return hipSuccess;
+    const dim3 grid((unsigned)n_children);
+    // two and four workgroups a compute unit (see WalkShape)
+    const bool fill2 = n_children > 512, fill4 = n_children > 1024;
+#define GP_WALK_LAUNCH(k) hipLaunchKernelGGL(k, grid, dim3(256), 0, s, p)
+#define GP_WALK_MANY(k, R, many)                                                     \
+    do {                                                                             \
+        if (many) GP_WALK_LAUNCH((k<R, true>));                                      \
+        else GP_WALK_LAUNCH((k<R, false>));                                          \
+    } while (0)
     if (vtype == 1) {
-        const int64_t W = (p.n_valid + 63) / 64;
-        const int rows = W <= 256 ? 1 : (int)((W + 255) / 256);
-        switch (rows) {
-        case 1: hipLaunchKernelGGL(k_walk_bool<1>, dim3((unsigned)n_children), dim3(256), 0, s, p); break;
-        case 2: hipLaunchKernelGGL(k_walk_bool<2>, dim3((unsigned)n_children), dim3(256), 0, s, p); break;
-        case 3:
-        case 4: hipLaunchKernelGGL(k_walk_bool<4>, dim3((unsigned)n_children), dim3(256), 0, s, p); break;
-        default:
-            if (rows <= 16) {
-                hipLaunchKernelGGL(k_walk_bool<16>, dim3((unsigned)n_children), dim3(256), 0, s, p);
-                break;
-            }
-            return hipErrorInvalidValue;
-        }
+        const int64_t W = (p.n_valid + 63) / 64, rows = (W + 255) / 256;
+        if (rows <= 1) GP_WALK_LAUNCH(k_walk_bool<1>);
+        else if (rows <= 2) GP_WALK_LAUNCH(k_walk_bool<2>);
+        else if (rows <= 4) GP_WALK_MANY(k_walk_bool, 4, fill4);
+        else if (rows <= 16) GP_WALK_MANY(k_walk_bool, 16, fill2);
+        else return hipErrorInvalidValue;
         return hipGetLastError();
     }
     switch (halving_rows(p.P)) {
-    case 1: hipLaunchKernelGGL(k_walk_f32<1>, dim3((unsigned)n_children), dim3(256), 0, s, p); break;
-    case 2: hipLaunchKernelGGL(k_walk_f32<2>, dim3((unsigned)n_children), dim3(256), 0, s, p); break;
-    case 4: hipLaunchKernelGGL(k_walk_f32<4>, dim3((unsigned)n_children), dim3(256), 0, s, p); break;
-    case 8: hipLaunchKernelGGL(k_walk_f32<8>, dim3((unsigned)n_children), dim3(256), 0, s, p); break;
-    case 16: hipLaunchKernelGGL(k_walk_f32<16>, dim3((unsigned)n_children), dim3(256), 0, s, p); break;
-    case 32: hipLaunchKernelGGL(k_walk_f32<32>, dim3((unsigned)n_children), dim3(256), 0, s, p); break;
-    case 64: hipLaunchKernelGGL(k_walk_f32<64>, dim3((unsigned)n_children), dim3(256), 0, s, p); break;
+    case 1: GP_WALK_LAUNCH(k_walk_f32<1>); break;
+    case 2: GP_WALK_LAUNCH(k_walk_f32<2>); break;
+    case 4: GP_WALK_LAUNCH(k_walk_f32<4>); break;
+    case 8: GP_WALK_LAUNCH(k_walk_f32<8>); break;
+    case 16: GP_WALK_LAUNCH(k_walk_f32<16>); break;
+    case 32: GP_WALK_MANY(k_walk_f32, 32, fill2); break;
+    case 64: GP_WALK_MANY(k_walk_f32, 64, fill2); break;
     default: return hipErrorInvalidValue;
     }
+#undef GP_WALK_MANY
+#undef GP_WALK_LAUNCH
     return hipGetLastError();
 }
 
