@@ -466,7 +466,14 @@ __global__ __launch_bounds__(256) void k_dc_emit(DcNodes q, DcChunks c, unsigned
 // One thread per chunk walking its nodes in order (k_dc_emit) waits for three
 // dependent loads per node, 4 us, for as many nodes as the largest chunk has:
 // 9.2 ms for 4.3e7 nodes in 2048-node chunks, 6.9 ms in 1024-node ones.
+//
+// The chunk graph is then put together on the host, by one thread, where the
+// thread per chunk leaves it behind: from eight nodes a chunk on.  A million
+// trees of 1 to 7 nodes load in 93 ms with a thread per node, in 53 with one per
+// chunk; 2e5 of 3 to 31 (11 nodes a chunk) in 14.5 and 14.3; 6e4 of 63 to 255 in
+// 5.9 and 6.5; 2e4 of 100 to 1000 in 3.5 and 5.4.
 constexpr int64_t kDcPerNode = 65536;           // nodes from which a thread per node emits
+constexpr int64_t kDcPerNodeChunk = 8;          // and nodes per chunk
 
 __global__ __launch_bounds__(256) void k_dc_steps(DcNodes q, uint32_t* step)
 {
@@ -956,7 +963,7 @@ int device_compile_population(Ctx* c, int vtype, int n_inputs, int64_t n_trees, 
         return set_err(c, GP_EINVAL, "internal error: a tree without its root chunk");
     std::vector<int32_t> rlen(nch), rend(nch);
     std::vector<int64_t> key;                   // per chunk in ascending root order (k_dc_root_info)
-    const bool per_node = n >= kDcPerNode && C <= kDcPlaceMaxC;
+    const bool per_node = n >= kDcPerNode && nch <= n / kDcPerNodeChunk && C <= kDcPlaceMaxC;
     {
         DevBuf ids_d, rlen_d, rend_d, key_d;
         if (per_node) {
