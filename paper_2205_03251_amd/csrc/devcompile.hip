@@ -1299,10 +1299,7 @@ int device_compile_population(Ctx* c, int vtype, int n_inputs, int64_t n_trees, 
         });
     }
     tr.mark("large-subtree lists");
-    std::stable_sort(out->leaves.begin(), out->leaves.end(),
-                     [](const std::pair<int64_t, int32_t>& x, const std::pair<int64_t, int32_t>& y) {
-                         return x.first > y.first;
-                     });
+    sort_longest_first(&out->leaves);
     tr.mark("leaf order");
     RC(up(c, nullptr, out->chunks, dch.data(), dch.size() * sizeof(DevChunk), s));
     RC(up(c, nullptr, out->chunk_in, chunk_in.data(), chunk_in.size() * 4, s));

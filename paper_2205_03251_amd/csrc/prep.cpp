@@ -49,6 +49,40 @@ struct CompileScratch {
 
 }  // namespace
 
+void sort_longest_first(std::vector<std::pair<int64_t, int32_t>>* v)
+{
+    using Item = std::pair<int64_t, int32_t>;
+    const size_t n = v->size();
+    int64_t most = 0;
+    bool sorted = true;
+    for (size_t i = 0; i < n; ++i) {
+        most = std::max(most, (*v)[i].first);
+        sorted = sorted && (i == 0 || (*v)[i - 1].first >= (*v)[i].first);
+    }
+    if (sorted) return;
+    if (n < 256) {
+        std::stable_sort(v->begin(), v->end(), [](const Item& x, const Item& y) { return x.first > y.first; });
+        return;
+    }
+    // 11 bits at a time, least first, of the distance from the longest (lengths are at least 0)
+    constexpr int kBits = 11;
+    std::vector<Item> to(n);
+    std::vector<size_t> at(size_t(1) << kBits);
+    for (int shift = 0; most >> shift > 0; shift += kBits) {
+        auto digit = [&](const Item& x) { return (size_t)((most - x.first) >> shift) & ((size_t(1) << kBits) - 1); };
+        std::fill(at.begin(), at.end(), 0);
+        for (const Item& x : *v) ++at[digit(x)];
+        size_t sum = 0;
+        for (size_t& c : at) {
+            const size_t k = c;
+            c = sum;
+            sum += k;
+        }
+        for (const Item& x : *v) to[at[digit(x)]++] = x;
+        v->swap(to);
+    }
+}
+
 bool validate_prefix(const uint8_t* ops, int64_t n, int n_inputs, std::string* why)
 {
     if (n < 1) {
@@ -219,6 +253,30 @@ bool compile_tree(const uint8_t* ops, int64_t n, const CompileOptions& opt, cons
             bigs.push_back({(int32_t)full(i), (int32_t)full(x.end)});
         x.cut = 0;
         const bool fol = foldable(l), fo_r = foldable(r);
+        // Most functions have no operand that is a LOAD or reads one, so that
+        // nothing is cut beside it: the rules below without the cuts.  The
+        // pass is the larger half of a host load; asking every function for
+        // cuts cost it a tenth.
+        if (((L.cut | R.cut) | ((L.form | R.form) & kWaits)) == 0) {
+            const int nl = L.need, nr = R.need;
+            const int need = fol ? (fo_r ? 1 : nr) : fo_r ? nl : nl == nr ? nl + 1 : std::max(nl, nr);
+            if (need <= S) {
+                x.need = (uint8_t)need;
+                if (fol || fo_r) {
+                    x.form = (uint8_t)(fol && fo_r ? (int)M_XX : (boolean || fol ? M_XS : M_SX) | (fol ? 16 : 0));
+                    x.len = fol && fo_r ? 1 : (fol ? R.len : L.len) + 1;
+                } else {
+                    x.form = (uint8_t)(nl >= nr ? (int)M_SS : (boolean ? M_SS : M_RS) | 8);
+                    x.len = L.len + R.len + 1;
+                }
+                x.open = (int32_t)std::min<int64_t>(1 + (int64_t)L.open + R.open, INT32_MAX);
+                if ((x.open >= C || forced(i)) && i != 0) {
+                    x.cut = 1;
+                    cuts.push_back(i);
+                }
+                return;
+            }
+        }
         // an operand beside one that waits for LOADs (see side_chunk_nodes)
         const bool wl = L.cut || (L.form & kWaits), wr = R.cut || (R.form & kWaits);
         if (wr && !L.cut && L.open >= G) {
@@ -434,6 +492,8 @@ bool compile_tree(const uint8_t* ops, int64_t n, const CompileOptions& opt, cons
         Chunk& ch = out->chunks[k];
         uint32_t* code = out->code.data() + ch.code_off;
         const int64_t root = roots[k], end = nd[root].end;
+        static thread_local std::vector<int32_t> ins;          // ch.inputs, until their number is known
+        ins.clear();
         int32_t max_slot = 0;
         ch.root_node = full(root);
         ch.end_node = index ? full(end) : -1;
@@ -449,8 +509,8 @@ bool compile_tree(const uint8_t* ops, int64_t n, const CompileOptions& opt, cons
                     out->chunks[id].parent = id_base + (int32_t)k;
                     id += id_base;
                 }
-                code[q] = ins_word(0, M_LOAD, (uint32_t)d, (uint32_t)ch.inputs.size());
-                ch.inputs.push_back(id);
+                code[q] = ins_word(0, M_LOAD, (uint32_t)d, (uint32_t)ins.size());
+                ins.push_back(id);
             } else {
                 nd[c].open = q;
                 nd[c].slot = (uint8_t)d;
@@ -510,6 +570,7 @@ bool compile_tree(const uint8_t* ops, int64_t n, const CompileOptions& opt, cons
             ++v;
         }
         code[ch.code_len - 1] = kEndWord;
+        ch.inputs = ins;
         slot_hi[k] = max_slot;
         if (ch.inputs.size() > kMaxPayload) too_many[k] = 1;
     };

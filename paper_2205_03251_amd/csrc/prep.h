@@ -127,6 +127,12 @@ struct CompileOptions {
     bool side_chunks = true;     // operands beside one that waits root chunks (see side_chunk_nodes)
 };
 
+// Sorts (chain length, chunk) pairs by descending length, equal ones in their
+// order.  By digits of the length: side chunks make most chunks leaves, and a
+// sort by comparisons was the larger part of what they added to a load (7000
+// pairs 372 us, 51 000 3.0 ms; now 66 us and 0.5 ms).
+void sort_longest_first(std::vector<std::pair<int64_t, int32_t>>* v);
+
 // Section 3.1 format check of one prefix array.
 bool validate_prefix(const uint8_t* ops, int64_t n, int n_inputs, std::string* why);
 

@@ -469,9 +469,9 @@ int assemble_population(Ctx* c, int vtype, int n_inputs, std::vector<TreeProg>& 
         for (auto& ch : pg.chunks) {
             if (ch.dev_src >= 0) n_dev += ch.code_len;
             if (ch.src_vec >= 0) promo = true;
+            n_in += (int64_t)ch.inputs.size();
         }
         n_rec += pg.n_records;
-        for (auto& ch : pg.chunks) n_in += (int64_t)ch.inputs.size();
         for (auto& sp : pg.spines) n_lv += (int64_t)sp.levels.size();
     }
     if (n_chunks > INT32_MAX / 2 || n_rec > INT32_MAX / 2 || n_in > INT32_MAX / 2)
@@ -486,7 +486,7 @@ int assemble_population(Ctx* c, int vtype, int n_inputs, std::vector<TreeProg>& 
         out->kept_chunks.resize(n_trees);
         out->kept_max_stack.assign(n_trees, 0);
     }
-    std::vector<uint32_t> code;
+    std::vector<uint32_t, NoInitAlloc<uint32_t>> code;
     code.reserve(n_code + 64);
     std::vector<DevChunk> dch(n_chunks);
     std::vector<int32_t> chunk_in;
@@ -506,6 +506,7 @@ int assemble_population(Ctx* c, int vtype, int n_inputs, std::vector<TreeProg>& 
     }
     out->rec_base.assign(n_trees, 0);
     out->leaves.clear();
+    out->leaves.reserve(n_chunks);
     out->spines.clear();
     out->spine_of.clear();
     out->cuts.clear();
@@ -526,10 +527,12 @@ int assemble_population(Ctx* c, int vtype, int n_inputs, std::vector<TreeProg>& 
             if (out->cuts.size() != (size_t)n_trees) out->cuts.assign(n_trees, {});
             auto& cl = out->cuts[t];
             cl.reserve(nc);
-            for (int64_t k = 0; k < nc; ++k)
+            for (int64_t k = nc - 1; k >= 0; --k)
                 cl.push_back(Pop::CutSlot{(int32_t)progs[t].chunks[k].root_node, (int32_t)progs[t].chunks[k].end_node,
                                           slot[k]});
-            std::sort(cl.begin(), cl.end(), [](const Pop::CutSlot& a, const Pop::CutSlot& b) { return a.node < b.node; });
+            // compiled trees number their chunks from the last node down, composed ones need not
+            auto before = [](const Pop::CutSlot& a, const Pop::CutSlot& b) { return a.node < b.node; };
+            if (!std::is_sorted(cl.begin(), cl.end(), before)) std::sort(cl.begin(), cl.end(), before);
         }
         for (int64_t k = 0; k < nc; ++k) {
             const Chunk& ch = pg.chunks[k];
@@ -548,7 +551,9 @@ int assemble_population(Ctx* c, int vtype, int n_inputs, std::vector<TreeProg>& 
             d.in_off = (int32_t)chunk_in.size();
             d.rec_base = (int32_t)rbase;
             d.n_in = (int32_t)ch.inputs.size();
-            for (int32_t in : ch.inputs) chunk_in.push_back(slot[in]);
+            chunk_in.resize(chunk_in.size() + ch.inputs.size());
+            int32_t* to = chunk_in.data() + d.in_off;
+            for (int32_t in : ch.inputs) *to++ = slot[in];
             out->chunk_n_in[cbase + k] = (int32_t)ch.inputs.size();
             out->chunk_tree[cbase + k] = (int32_t)t;
             if (promo) {
@@ -592,10 +597,7 @@ int assemble_population(Ctx* c, int vtype, int n_inputs, std::vector<TreeProg>& 
         std::vector<Chunk>().swap(pg.chunks);
     }
     // Longest remaining chain first.
-    std::stable_sort(out->leaves.begin(), out->leaves.end(),
-                     [](const std::pair<int64_t, int32_t>& x, const std::pair<int64_t, int32_t>& y) {
-                         return x.first > y.first;
-                     });
+    sort_longest_first(&out->leaves);
     out->n_chunks = n_chunks;
     out->n_code = n_code + n_dev;
     out->n_records = n_rec;
@@ -874,10 +876,7 @@ int enqueue_promoted(Ctx* c, Pop* p, const Pop* src, gp_handle cases_h, const Ca
         for (int32_t sl = 0; sl < pl.n_slices; ++sl) pend[(size_t)k * pl.n_slices + sl] = left;
         if (left == 0) ready.emplace_back(p->chunk_path[k], (int32_t)k);
     }
-    std::stable_sort(ready.begin(), ready.end(),
-                     [](const std::pair<int64_t, int32_t>& x, const std::pair<int64_t, int32_t>& y) {
-                         return x.first > y.first;
-                     });
+    sort_longest_first(&ready);
     std::vector<int64_t> items;
     items.reserve(ready.size() * pl.n_slices);
     for (auto& r : ready)
