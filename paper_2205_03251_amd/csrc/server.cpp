@@ -531,13 +531,6 @@ int gp_server_start(gp_ctx* ctxp, const gp_server_cfg* cfg)
     S->cfg.device_compile_nodes = cfg ? cfg->device_compile_nodes : 0;
     S->device_compile_nodes = std::max<int64_t>(0, S->cfg.device_compile_nodes);
     S->budget = S->cfg.budget_bytes ? std::min<uint64_t>(S->cfg.budget_bytes, ctx->budget) : ctx->budget;
-    {
-        std::lock_guard<std::mutex> lk(ctx->mu);
-        ctx->pool.trim();                        // its threads allocate for themselves
-        S->tuned = ctx->tuned;
-        S->forced_variant = ctx->forced_variant;
-        S->forced_waves = ctx->forced_waves;
-    }
     S->pinned_bytes = (size_t)S->cfg.max_batch_jobs * (20 + (size_t)16384 * 8);
     for (int i = 0; i < S->cfg.n_streams; ++i) {
         hipStream_t s = nullptr;
@@ -563,7 +556,14 @@ int gp_server_start(gp_ctx* ctxp, const gp_server_cfg* cfg)
         S->prep_arenas.push_back(std::make_unique<DevArena>());
     }
     S->slot_busy.assign(S->cfg.n_streams, 0);
-    ctx->server = S;
+    {
+        std::lock_guard<std::mutex> lk(ctx->mu);
+        S->tuned = ctx->tuned;
+        S->forced_variant = ctx->forced_variant;
+        S->forced_waves = ctx->forced_waves;
+        ctx->pool.trim();                        // its threads allocate for themselves; calls keep no blocks from here on
+        ctx->server = S;
+    }
     for (int i = 0; i < S->cfg.prep_threads; ++i) S->workers.emplace_back(prep_worker, S, i);
     S->dispatcher = std::thread(dispatch_loop, S);
     S->completer = std::thread(complete_loop, S);
