@@ -31,8 +31,8 @@ struct Ctx;
 struct DevBuf {
     Ctx* ctx = nullptr;
     void* p = nullptr;
-    size_t bytes = 0;
-    size_t block = 0;            // size of the block behind it (a reused one may be larger)
+    size_t bytes = 0;            // of the block behind it
+    size_t waste = 0;            // of which not asked for (a reused block may be larger)
     bool borrowed = false;       // memory of a DevArena: not freed by release()
     bool pooled = false;         // allocated inside a PoolScope: may go back to the context's pool
     DevBuf() = default;
@@ -45,7 +45,7 @@ struct DevBuf {
         std::swap(ctx, o.ctx);
         std::swap(p, o.p);
         std::swap(bytes, o.bytes);
-        std::swap(block, o.block);
+        std::swap(waste, o.waste);
         std::swap(borrowed, o.borrowed);
         std::swap(pooled, o.pooled);
     }
@@ -70,13 +70,21 @@ struct DevArena {
 // Used only by the
 // thread that holds Ctx::mu inside a PoolScope, whose work all goes to the
 // context stream: a block handed out again is overwritten after everything
-// that used it before.  Holds at most `limit` bytes; trimmed when the budget
-// or the device runs short, when a server starts, and by gp_destroy.
+// that used it before.  Holds at most `limit` bytes in kBlocks blocks, the last
+// ones given; trimmed when the budget or the device runs short, when the
+// context holds no population and no case set any more, when a server starts,
+// and by gp_destroy.
 struct DevPool {
-    std::multimap<size_t, void*> blocks;     // by size
+    static constexpr size_t kBlocks = 256;
+    struct Block {
+        void* p;
+        uint64_t since;
+    };
+    std::multimap<size_t, Block> blocks;     // by size
     size_t bytes = 0;
     size_t limit = 0;
-    void* take(size_t need, size_t* got);
+    uint64_t clock = 0;
+    void* take(size_t need, size_t most, size_t* got);
     bool give(void* p, size_t n);
     void trim();
 };
@@ -235,6 +243,7 @@ struct Ctx {
     bool own_stream = false;
     uint64_t budget = 0;
     std::atomic<uint64_t> used{0};
+    std::atomic<uint64_t> waste{0};         // of used: what reused blocks hold beyond what was asked for
     int n_cu = 0;
     std::string err;
     std::mutex err_mu;                      // server threads may report errors too
@@ -267,14 +276,16 @@ struct PoolScope {
     PoolScope& operator=(const PoolScope&) = delete;
     Ctx* before;
 };
-// Populations built by this thread have no side chunks while it lives: the
-// second attempt of a call that ran short of device memory.
+// The second attempt of a call that ran short of device memory: while it lives,
+// populations built by this thread have no side chunks, and its allocations
+// are of the size asked for (no kept blocks).
 struct NoSideChunks {
     NoSideChunks();
     ~NoSideChunks();
     NoSideChunks(const NoSideChunks&) = delete;
     NoSideChunks& operator=(const NoSideChunks&) = delete;
     bool before;
+    Ctx* pool_before;
 };
 bool side_chunks_wanted();
 constexpr size_t kStageBytes = size_t(4) << 20;

@@ -52,33 +52,51 @@ PoolScope::~PoolScope() { t_pool = before; }
 static thread_local bool t_no_side = false;    // inside a NoSideChunks
 static thread_local uint64_t t_need = 0, t_left = 0;   // the last refused allocation: its bytes, what was left
 
-NoSideChunks::NoSideChunks() : before(t_no_side) { t_no_side = true; }
-NoSideChunks::~NoSideChunks() { t_no_side = before; }
+NoSideChunks::NoSideChunks() : before(t_no_side), pool_before(t_pool)
+{
+    t_no_side = true;
+    if (t_pool) t_pool->pool.trim();
+    t_pool = nullptr;
+}
+NoSideChunks::~NoSideChunks()
+{
+    t_no_side = before;
+    t_pool = pool_before;
+}
 bool side_chunks_wanted() { return !t_no_side; }
 
-// The smallest kept block that holds `need` without wasting more than an eighth (and 64 KiB).
-void* DevPool::take(size_t need, size_t* got)
+// The smallest kept block that holds `need` without wasting more than an eighth
+// (and 64 KiB), of at most `most` bytes.
+void* DevPool::take(size_t need, size_t most, size_t* got)
 {
     auto it = blocks.lower_bound(need);
-    if (it == blocks.end() || it->first > need + need / 8 + 65536) return nullptr;
-    void* p = it->second;
+    if (it == blocks.end() || it->first > std::min(need + need / 8 + 65536, most)) return nullptr;
+    void* p = it->second.p;
     *got = it->first;
     bytes -= it->first;
     blocks.erase(it);
     return p;
 }
 
+// Keeps the block; the ones kept longest make room for it.
 bool DevPool::give(void* p, size_t n)
 {
-    if (n > limit || bytes > limit - n) return false;
-    blocks.emplace(n, p);
+    if (n > limit) return false;
+    while (bytes > limit - n || blocks.size() >= kBlocks) {
+        auto old = std::min_element(blocks.begin(), blocks.end(),
+                                    [](const auto& x, const auto& y) { return x.second.since < y.second.since; });
+        (void)hipFree(old->second.p);
+        bytes -= old->first;
+        blocks.erase(old);
+    }
+    blocks.emplace(n, Block{p, ++clock});
     bytes += n;
     return true;
 }
 
 void DevPool::trim()
 {
-    for (auto& b : blocks) (void)hipFree(b.second);
+    for (auto& b : blocks) (void)hipFree(b.second.p);
     blocks.clear();
     bytes = 0;
 }
@@ -88,11 +106,14 @@ DevBuf::~DevBuf() { release(); }
 void DevBuf::release()
 {
     if (p && !borrowed) {
-        if (!(pooled && ctx && t_pool == ctx && ctx->pool.give(p, block))) (void)hipFree(p);
-        if (ctx) ctx->used -= bytes;
+        if (!(pooled && ctx && t_pool == ctx && ctx->pool.give(p, bytes))) (void)hipFree(p);
+        if (ctx) {
+            ctx->used -= bytes;
+            ctx->waste -= waste;
+        }
     }
     p = nullptr;
-    bytes = 0;
+    bytes = waste = 0;
     borrowed = false;
     pooled = false;
 }
@@ -131,7 +152,10 @@ int dev_alloc(Ctx* c, DevBuf& b, size_t bytes)
     void* p = nullptr;
     size_t block = bytes;
     if (pooled) {
-        if (c->used + bytes <= c->budget) p = c->pool.take(bytes, &block);
+        // a larger block counts whole, and what it wastes is missing later: at most 1/256 of the budget in all
+        const uint64_t used = c->used, waste = c->budget / 256 - std::min<uint64_t>(c->budget / 256, c->waste);
+        if (used + bytes <= c->budget)
+            p = c->pool.take(bytes, (size_t)std::min<uint64_t>(c->budget - used, bytes + waste), &block);
         if (!p && c->used + bytes + c->pool.bytes > c->budget) c->pool.trim();
     }
     if (!p && c->used + bytes > c->budget) {
@@ -159,10 +183,11 @@ int dev_alloc(Ctx* c, DevBuf& b, size_t bytes)
     }
     b.ctx = c;
     b.p = p;
-    b.bytes = bytes;
-    b.block = block;
+    b.bytes = block;
+    b.waste = block - bytes;
     b.pooled = pooled;
-    c->used += bytes;
+    c->used += block;
+    c->waste += block - bytes;
     return GP_OK;
 }
 
@@ -1746,8 +1771,12 @@ int gp_free(gp_ctx* ctx, gp_handle h)
     PoolScope pool(ctx);
     (void)hipSetDevice(ctx->device);
     (void)hipStreamSynchronize(ctx->stream);
-    if (ctx->pops.erase(h)) return GP_OK;
+    if (ctx->pops.erase(h)) {
+        if (ctx->pops.empty() && ctx->cases.empty()) ctx->pool.trim();
+        return GP_OK;
+    }
     if (ctx->cases.erase(h)) {
+        if (ctx->pops.empty() && ctx->cases.empty()) ctx->pool.trim();
         for (auto& kv : ctx->pops) {
             if (kv.second->evaluated_with == h) kv.second->evaluated_with = 0;
             for (auto& pk : kv.second->plans)
