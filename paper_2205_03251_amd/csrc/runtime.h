@@ -33,6 +33,7 @@ struct DevBuf {
     void* p = nullptr;
     size_t bytes = 0;            // of the block behind it
     size_t waste = 0;            // of which not asked for (a reused block may be larger)
+    size_t asked() const { return bytes - waste; }
     bool borrowed = false;       // memory of a DevArena: not freed by release()
     bool pooled = false;         // allocated inside a PoolScope: may go back to the context's pool
     DevBuf() = default;

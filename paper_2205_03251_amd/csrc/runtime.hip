@@ -1653,10 +1653,11 @@ int gp_population_info(gp_ctx* ctx, gp_handle pop, gp_pop_info* out)
     out->n_instructions = p->n_code;
     out->n_records = p->n_records;
     out->n_spines = (int64_t)p->spines.size();
-    uint64_t b = p->code.bytes + p->chunks.bytes + p->chunk_in.bytes + p->levels.bytes + p->vecs.bytes +
-                 p->recs.bytes + p->fit.bytes;
+    uint64_t b = 0;
+    for (const DevBuf* d : {&p->code, &p->chunks, &p->chunk_in, &p->levels, &p->vecs, &p->recs, &p->fit}) b += d->asked();
     for (auto& kv : p->plans)
-        b += kv.second->items.bytes + kv.second->pending.bytes + kv.second->pending_init.bytes + kv.second->cursor.bytes;
+        for (const DevBuf* d : {&kv.second->items, &kv.second->pending, &kv.second->pending_init, &kv.second->cursor})
+            b += d->asked();
     out->device_bytes = (int64_t)b;
     out->max_stack = p->max_stack;
     out->chunk_nodes = (int32_t)p->chunk_nodes;
