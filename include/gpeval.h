@@ -131,9 +131,9 @@ const char* gp_last_error(const gp_ctx* ctx);
 /* Device memory currently held by the context's populations, cases and calls,
  * in bytes.  Freed blocks of at most 1/16 of the budget and 8 GiB in all are
  * kept for the next calls and not counted, until they are used again; they are
- * given back when the budget or the device runs short, when gp_free has released
- * the context's last population and case set, by gp_server_start and by
- * gp_destroy. */
+ * given back when the budget or the device runs short, but for 256 MiB when
+ * gp_free has released the context's last population and case set, and by
+ * gp_server_start and gp_destroy. */
 uint64_t gp_memory_used(const gp_ctx* ctx);
 
 /* ------------------------------------------------------------------- data */

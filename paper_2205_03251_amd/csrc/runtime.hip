@@ -94,11 +94,15 @@ bool DevPool::give(void* p, size_t n)
     return true;
 }
 
-void DevPool::trim()
+// The largest blocks go until `keep` bytes are left.
+void DevPool::trim(size_t keep)
 {
-    for (auto& b : blocks) (void)hipFree(b.second.p);
-    blocks.clear();
-    bytes = 0;
+    while (bytes > keep || (keep == 0 && !blocks.empty())) {
+        auto last = std::prev(blocks.end());
+        (void)hipFree(last->second.p);
+        bytes -= last->first;
+        blocks.erase(last);
+    }
 }
 
 DevBuf::~DevBuf() { release(); }
@@ -1773,11 +1777,11 @@ int gp_free(gp_ctx* ctx, gp_handle h)
     (void)hipSetDevice(ctx->device);
     (void)hipStreamSynchronize(ctx->stream);
     if (ctx->pops.erase(h)) {
-        if (ctx->pops.empty() && ctx->cases.empty()) ctx->pool.trim();
+        if (ctx->pops.empty() && ctx->cases.empty()) ctx->pool.trim(DevPool::kIdle);
         return GP_OK;
     }
     if (ctx->cases.erase(h)) {
-        if (ctx->pops.empty() && ctx->cases.empty()) ctx->pool.trim();
+        if (ctx->pops.empty() && ctx->cases.empty()) ctx->pool.trim(DevPool::kIdle);
         for (auto& kv : ctx->pops) {
             if (kv.second->evaluated_with == h) kv.second->evaluated_with = 0;
             for (auto& pk : kv.second->plans)
