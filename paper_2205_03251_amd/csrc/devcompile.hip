@@ -70,6 +70,19 @@ struct DevMemPacked : DevMem {
     __device__ static void st(int32_t* p, int32_t v) { *p = v; }
 };
 
+// The hand-off within a workgroup, through LDS.
+struct LdsMem {
+    __device__ static uint32_t exchange(uint32_t* p, uint32_t v)
+    {
+        return __hip_atomic_exchange(p, v, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+    __device__ static void fetch_or(uint32_t* p, uint32_t v) { atomicOr(p, v); }
+};
+
+struct DevSum {
+    __device__ static void add(uint32_t* p, uint32_t v) { atomicAdd(p, v); }
+};
+
 __device__ __forceinline__ int64_t dc_uniform(int64_t x)
 {
     const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)x);
@@ -109,12 +122,10 @@ __device__ __forceinline__ bool dc_take_batch(unsigned long long* cursor, int64_
 // 6.3 ms; walking on from the block with those steps, 9.9 ms.
 constexpr int kDcSpan = 4096;
 constexpr int kDcList = 256;                    // listed arrivals of one wave
-constexpr uint16_t kDcOutside = 0xffff;         // a parent before the block; a function not finished in it
-constexpr uint16_t kDcTop = 0xfffe;             // no parent: a tree's root
 
 __global__ __launch_bounds__(256) void k_dc_up_block(DcNodes q, uint32_t* n_walks, uint32_t* walk_v, uint32_t* walk_w)
 {
-    __shared__ uint32_t word[kDcSpan];          // 0, then the first operand's word, then info | len << 13
+    __shared__ uint32_t word[kDcSpan];          // see DcBlock
     __shared__ uint16_t par[kDcSpan], rgt[kDcSpan];
     __shared__ uint8_t op[kDcSpan];
     __shared__ uint32_t lw[4][kDcList];
@@ -149,15 +160,10 @@ __global__ __launch_bounds__(256) void k_dc_up_block(DcNodes q, uint32_t* n_walk
             }
             const int i = 16 * tid + j;
             const uint8_t o = q.ops[v];
-            const int32_t pl = q.parl[v];
-            const int64_t last = s + q.endl[v];
-            uint16_t r = kDcOutside;
-            if ((o & kFuncBit) && last <= end) r = (uint16_t)(s + q.endl[v + 1] - base);
             op[i] = o;
-            par[i] = pl < 0 ? kDcTop : s + pl >= base ? (uint16_t)(s + pl - base) : kDcOutside;
-            rgt[i] = r;
+            dc_block_node(q, s, v, base, end, par + i, rgt + i);
             word[i] = 0;
-            if ((o & kFuncBit) && last - v >= q.big_min) big |= 1u << j;
+            if ((o & kFuncBit) && s + q.endl[v] - v >= q.big_min) big |= 1u << j;
         }
     }
     __syncthreads();
@@ -174,6 +180,7 @@ __global__ __launch_bounds__(256) void k_dc_up_block(DcNodes q, uint32_t* n_walk
         n_list = 0;
     };
     const uint64_t below = (1ull << lane) - 1;
+    const DcBlock blk{word, par, rgt};
     int pb = wave * (kDcSpan / 4);
     const int pe = (int)(end - base) < pb + kDcSpan / 4 ? (int)(end - base) : pb + kDcSpan / 4;
     int v = -1;
@@ -183,7 +190,7 @@ __global__ __launch_bounds__(256) void k_dc_up_block(DcNodes q, uint32_t* n_walk
         if (v < 0) {
             const int g = pb + __popcll(idle & below);
             if (g < pe && !(op[g] & kFuncBit)) {
-                word[g] = 1u | (1u << 13);
+                word[g] = kDcBlockLeaf;
                 w = dc_leaf_word(dc_foldable_op(q, op[g]));
                 v = g;
             }
@@ -191,32 +198,9 @@ __global__ __launch_bounds__(256) void k_dc_up_block(DcNodes q, uint32_t* n_walk
         if (pb < pe) pb += __popcll(idle);
         int list = 0;                           // integers across the branches, not lane-mask booleans
         if (v >= 0) {
-            const int p = par[v];
-            if (p == kDcTop) {
-                v = -1;
-            } else if (p == kDcOutside) {
-                list = 1;
-            } else if (rgt[p] == kDcOutside) {
-                // v is p's left operand (the right one ends with p, past the block)
-                ((uint32_t*)q.slot64)[2 * (base + p)] = w;
-                v = -1;
-            } else {
-                const uint32_t other =
-                    __hip_atomic_exchange(&word[p], w, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_WORKGROUP);
-                if (other == 0) {
-                    v = -1;                     // the other operand is not done yet
-                } else {
-                    const int l = p + 1, r = rgt[p];
-                    const int left = v == l;
-                    const DcNode o = dc_combine(q, par[p] == kDcTop, dc_unpack(left ? w : other),
-                                                dc_unpack(left ? other : w));
-                    word[p] = (uint32_t)dc_info(o) | ((uint32_t)o.len << 13);
-                    if (o.cut_kids & 1) atomicOr(&word[l], (uint32_t)kDcCut);
-                    if (o.cut_kids & 2) atomicOr(&word[r], (uint32_t)kDcCut);
-                    w = o.cut ? kDcPackCut : dc_pack(o.need, o.waits, o.len, o.open);
-                    v = p;
-                }
-            }
+            const int at = dc_block_step<LdsMem>(q, blk, base, v, &w);
+            if (at == -2) list = 1;
+            else v = at;
         }
         const uint64_t listed = __ballot(list);
         if (list) {
@@ -253,17 +237,12 @@ __global__ __launch_bounds__(256) void k_dc_up_block(DcNodes q, uint32_t* n_walk
     for (int j = 0; j < 16; ++j) {
         const int i = 16 * tid + j;
         if (v0 + j >= end || ((op[i] & kFuncBit) && rgt[i] == kDcOutside)) continue;
-        q.info[v0 + j] = word[i] & 8191;
-        q.len[v0 + j] = word[i] >> 13;
-        if (q.big) q.big[v0 + j] = big >> j & 1;
+        dc_block_result(q, v0 + j, word[i], (big >> j & 1) != 0);
     }
 }
 
-// Lane i walks up from listed node i.  At each parent, if the other operand's
-// word is there already (stored by the block kernel, or by an earlier arrival),
-// the lane combines without an atomic; else it leaves its own word by one and
-// ends, unless the other came in between.  The parent's slot, its own parent
-// and its end are loaded together, so a step of the chain costs one trip.
+// Lane i walks up from listed node i (dc_walk_step; a left operand's word may
+// have been stored by the block kernel).
 __global__ __launch_bounds__(256) void k_dc_up_walk(DcNodes q, const uint32_t* n_walks, const uint32_t* walk_v,
                                                     const uint32_t* walk_w)
 {
@@ -274,24 +253,8 @@ __global__ __launch_bounds__(256) void k_dc_up_walk(DcNodes q, const uint32_t* n
         const int64_t s = q.offsets[dc_tree_of(q, v)];
         int32_t p = q.parl[v];
         while (p >= 0) {
-            const int64_t pg = s + p;
-            if (pg >= v) {
-                DevMem::err(q.err, 2);
-                break;
-            }
-            const bool left = v == pg + 1;
-            const int64_t end = s + q.endl[pg];
-            const int32_t pp = q.parl[pg];
-            uint32_t* half = (uint32_t*)(q.slot64 + pg);
-            uint32_t other = __hip_atomic_load(half + (left ? 1 : 0), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if (other == 0) {
-                const uint64_t old = DevMem::fetch_or64(q.slot64 + pg, left ? (uint64_t)w : (uint64_t)w << 32);
-                other = left ? (uint32_t)(old >> 32) : (uint32_t)old;
-                if (other == 0) break;          // the other operand is not done yet
-            }
-            w = dc_finish_packed<DevMemPacked>(q, s, pg, left ? w : other, left ? other : w, end);
-            v = pg;
-            p = pp;
+            v = dc_walk_step<DevMemPacked>(q, s, v, &p, &w);
+            if (v < 0) break;
         }
     }
 }
@@ -479,11 +442,7 @@ __global__ __launch_bounds__(256) void k_dc_steps(DcNodes q, uint32_t* step)
 {
     const int64_t g = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (g >= q.n) return;
-    int64_t from, to;
-    uint32_t by;
-    if (!dc_second_operand(q, g, &from, &to, &by)) return;
-    atomicAdd(step + from, by);
-    if (to < q.n) atomicAdd(step + to, 0u - by);
+    dc_add_place_steps<DevSum>(q, g, step);
 }
 
 // Chunk k's id takes over at its root and its parent's at its end.
@@ -492,9 +451,7 @@ __global__ __launch_bounds__(256) void k_dc_id_steps(int64_t n, const int64_t* r
 {
     const int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (k >= nch) return;
-    const uint32_t by = (uint32_t)k - (parent[k] < 0 ? 0u : (uint32_t)parent[k]);
-    atomicAdd(step + root[k], by);
-    if (end[k] < n) atomicAdd(step + end[k], 0u - by);
+    dc_add_id_steps<DevSum>(n, k, root[k], end[k], parent[k], step);
 }
 
 // Inclusive prefix sums of two arrays at once, in place: sums of blocks of
@@ -598,21 +555,11 @@ __global__ __launch_bounds__(256) void k_dc_scan_apply(uint32_t* a, uint32_t* b,
     }
 }
 
-// Per chunk: its frame (its root's place), its END word, and the word by which
-// its parent LOADs it, its highest slot; stores is cleared for k_dc_emit_nodes.
 __global__ __launch_bounds__(256) void k_dc_emit_chunks(DcNodes q, DcChunks c, const uint32_t* place, uint32_t* frame)
 {
     const int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (k >= c.n) return;
-    const int64_t g = c.root[k];
-    const uint32_t at = place[g];
-    frame[k] = at;
-    c.code[c.code_off[k] + q.len[g]] = kEndWord;
-    c.stores[k] = 0;
-    c.max_slot[k] = (q.info[g] & 63) - 1;       // the slots its code uses are its root's stack need
-    const int32_t p = c.parent[k];
-    if (p >= 0) c.code[c.code_off[p] + dc_place_pos(at - place[c.root[p]])] =
-        dc_word(0, M_LOAD, dc_place_slot(at - place[c.root[p]]), (uint32_t)c.load_idx[k]);
+    dc_emit_chunk(q, c, place, k, frame);
 }
 
 // Bound by its loads: about 40 bytes read and one word written per node, the
@@ -622,17 +569,7 @@ __global__ __launch_bounds__(256) void k_dc_emit_nodes(DcNodes q, DcChunks c, co
 {
     const int64_t g = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (g >= q.n) return;
-    const uint32_t k = id[g];
-    const uint32_t at = place[g] - frame[k];
-    int64_t pos;
-    uint32_t word, store;
-    if (!dc_node_word(q, g, dc_place_pos(at), dc_place_slot(at), &pos, &word, &store)) return;
-    uint32_t* code = c.code + c.code_off[k];
-    code[pos] = word;
-    if (store != 0) {
-        code[pos + 1] = store;
-        c.stores[k] = 1;
-    }
+    dc_emit_node(q, c, place, id, frame, g);
 }
 
 inline unsigned blocks_for(int64_t n) { return (unsigned)((n + 255) / 256); }

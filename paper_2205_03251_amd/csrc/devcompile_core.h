@@ -290,7 +290,7 @@ GPE_HD inline DcKid dc_unpack(uint32_t w)
     return k;
 }
 
-// A terminal's word for its parent, and its stores.
+// A terminal's word for its parent, and its stores (in a block: kDcBlockLeaf).
 GPE_HD inline uint32_t dc_leaf_word(bool fold) { return dc_pack(1, false, fold ? 0 : 1, 1); }
 template <class Mem> GPE_HD inline uint32_t dc_leaf_packed(const DcNodes& q, int64_t g)
 {
@@ -314,24 +314,96 @@ GPE_HD inline uint32_t dc_finish_packed(const DcNodes& q, int64_t s, int64_t pg,
     return o.cut ? kDcPackCut : dc_pack(o.need, o.waits, o.len, o.open);
 }
 
-// One arrival of node v (word w) at its parent; returns the parent (and its
-// word in *w) when this was the parent's second operand, else -1.
+// One arrival of node v of the tree starting at s (word *w) at its parent *p
+// (tree-local): returns the parent (its word in *w, its own parent in *p) when
+// this was the second operand to arrive, else -1.  If the other operand's word
+// is there already, the thread combines without an atomic (the other has left
+// it and ended); else it leaves its own by one, which gives the other's back if
+// that came in between.  The parent's slot, its end and its own parent are
+// loaded together, so that a step of a walk costs one trip to memory.
 template <class Mem>
-GPE_HD inline int64_t dc_step_packed(const DcNodes& q, int64_t s, int64_t e, int64_t v, uint32_t* w)
+GPE_HD inline int64_t dc_walk_step(const DcNodes& q, int64_t s, int64_t v, int32_t* p, uint32_t* w)
 {
-    const int32_t p = q.parl[v];
-    if (p < 0) return -1;
-    const int64_t pg = s + p;
+    const int64_t pg = s + *p;
     if (pg >= v || pg < s) {
         Mem::err(q.err, 2);
         return -1;
     }
     const bool left = v == pg + 1;
-    const uint64_t old = Mem::fetch_or64(q.slot64 + pg, left ? (uint64_t)*w : (uint64_t)*w << 32);
-    if (old == 0) return -1;                        // the other operand is not done yet
-    const uint32_t other = left ? (uint32_t)(old >> 32) : (uint32_t)old;
-    *w = dc_finish_packed<Mem>(q, s, pg, left ? *w : other, left ? other : *w, s + q.endl[pg]);
+    const int64_t end = s + q.endl[pg];
+    const int32_t pp = q.parl[pg];
+    uint32_t other = (uint32_t)Mem::ld((const int32_t*)(q.slot64 + pg) + (left ? 1 : 0));
+    if (other == 0) {
+        const uint64_t old = Mem::fetch_or64(q.slot64 + pg, left ? (uint64_t)*w : (uint64_t)*w << 32);
+        other = left ? (uint32_t)(old >> 32) : (uint32_t)old;
+        if (other == 0) return -1;                  // the other operand is not done yet
+    }
+    *w = dc_finish_packed<Mem>(q, s, pg, left ? *w : other, left ? other : *w, end);
+    *p = pp;
     return pg;
+}
+
+// The same from the parent index alone.
+template <class Mem>
+GPE_HD inline int64_t dc_step_packed(const DcNodes& q, int64_t s, int64_t e, int64_t v, uint32_t* w)
+{
+    (void)e;
+    int32_t p = q.parl[v];
+    return p < 0 ? -1 : dc_walk_step<Mem>(q, s, v, &p, w);
+}
+
+// ----- a block of positions finished in LDS (see k_dc_up_block).  Positions in
+// the block; word: 0, then the first operand's word, then info | len << 13.
+constexpr uint16_t kDcOutside = 0xffff;         // a parent before the block; a function not finished in it
+constexpr uint16_t kDcTop = 0xfffe;             // no parent: a tree's root
+struct DcBlock {
+    uint32_t* word;
+    const uint16_t* par;                        // parents
+    const uint16_t* rgt;                        // right operands of the functions finished in the block
+};
+
+// Position v's entries in par and rgt, for the block [base, end) and v's tree from s.
+GPE_HD inline void dc_block_node(const DcNodes& q, int64_t s, int64_t v, int64_t base, int64_t end, uint16_t* par,
+                                 uint16_t* rgt)
+{
+    const int32_t p = q.parl[v];
+    *par = p < 0 ? kDcTop : s + p >= base ? (uint16_t)(s + p - base) : kDcOutside;
+    *rgt = (q.ops[v] & kFuncBit) && s + q.endl[v] <= end ? (uint16_t)(s + q.endl[v + 1] - base) : kDcOutside;
+}
+
+// One arrival of position v (word *w) at its parent: the parent (its word in
+// *w) when this was the second operand to arrive; -1 when the walk ends here; -2
+// when the parent lies before the block.
+template <class Mem>
+GPE_HD inline int dc_block_step(const DcNodes& q, const DcBlock& b, int64_t base, int v, uint32_t* w)
+{
+    const int p = b.par[v];
+    if (p == kDcTop) return -1;
+    if (p == kDcOutside) return -2;
+    if (b.rgt[p] == kDcOutside) {
+        // v is p's left operand (the right one ends with p, past the block)
+        ((uint32_t*)q.slot64)[2 * (base + p)] = *w;
+        return -1;
+    }
+    const uint32_t other = Mem::exchange(b.word + p, *w);
+    if (other == 0) return -1;                  // the other operand is not done yet
+    const int l = p + 1, r = b.rgt[p];
+    const int left = v == l;
+    const DcNode o = dc_combine(q, b.par[p] == kDcTop, dc_unpack(left ? *w : other), dc_unpack(left ? other : *w));
+    b.word[p] = (uint32_t)dc_info(o) | ((uint32_t)o.len << 13);
+    if (o.cut_kids & 1) Mem::fetch_or(b.word + l, (uint32_t)kDcCut);
+    if (o.cut_kids & 2) Mem::fetch_or(b.word + r, (uint32_t)kDcCut);
+    *w = o.cut ? kDcPackCut : dc_pack(o.need, o.waits, o.len, o.open);
+    return p;
+}
+
+// What a finished position leaves for the later passes.
+constexpr uint32_t kDcBlockLeaf = 1u | (1u << 13);
+GPE_HD inline void dc_block_result(const DcNodes& q, int64_t v, uint32_t word, bool large)
+{
+    q.info[v] = (int32_t)(word & 8191);
+    q.len[v] = (int32_t)(word >> 13);
+    if (q.big) q.big[v] = large ? 1 : 0;
 }
 
 // Emission of one chunk by compile_tree's scan in prefix order (an
@@ -509,6 +581,56 @@ GPE_HD inline bool dc_node_word(const DcNodes& q, int64_t g, int64_t pos, uint32
     *word = dc_word(op & 3, m, d, payload);
     if (q.rec && q.rec[g] >= 0) *store = dc_word(0, M_STORE, d, (uint32_t)q.rec[g]);
     return true;
+}
+
+// The place steps of function g, and chunk k's id steps (see k_dc_steps).
+template <class Mem> GPE_HD inline void dc_add_place_steps(const DcNodes& q, int64_t g, uint32_t* step)
+{
+    int64_t from, to;
+    uint32_t by;
+    if (!dc_second_operand(q, g, &from, &to, &by)) return;
+    Mem::add(step + from, by);
+    if (to < q.n) Mem::add(step + to, 0u - by);
+}
+
+template <class Mem>
+GPE_HD inline void dc_add_id_steps(int64_t n, int64_t k, int64_t root, int64_t end, int32_t parent, uint32_t* step)
+{
+    const uint32_t by = (uint32_t)k - (parent < 0 ? 0u : (uint32_t)parent);
+    Mem::add(step + root, by);
+    if (end < n) Mem::add(step + end, 0u - by);
+}
+
+// Chunk k: its frame (its root's place), its END word, the word by which its
+// parent LOADs it, its highest slot; stores is cleared for dc_emit_node.
+GPE_HD inline void dc_emit_chunk(const DcNodes& q, const DcChunks& c, const uint32_t* place, int64_t k, uint32_t* frame)
+{
+    const int64_t g = c.root[k];
+    const uint32_t at = place[g];
+    frame[k] = at;
+    c.code[c.code_off[k] + q.len[g]] = kEndWord;
+    c.stores[k] = 0;
+    c.max_slot[k] = (q.info[g] & 63) - 1;       // the slots its code uses are its root's stack need
+    const int32_t p = c.parent[k];
+    if (p >= 0) c.code[c.code_off[p] + dc_place_pos(at - place[c.root[p]])] =
+        dc_word(0, M_LOAD, dc_place_slot(at - place[c.root[p]]), (uint32_t)c.load_idx[k]);
+}
+
+// Node g, once its chunk's frame is there: its word and its STORE.
+GPE_HD inline void dc_emit_node(const DcNodes& q, const DcChunks& c, const uint32_t* place, const uint32_t* id,
+                                const uint32_t* frame, int64_t g)
+{
+    const uint32_t k = id[g];
+    const uint32_t at = place[g] - frame[k];
+    int64_t pos;
+    uint32_t word, store;
+    if (!dc_node_word(q, g, dc_place_pos(at), dc_place_slot(at), &pos, &word, &store)) return;
+    uint32_t* code = c.code + c.code_off[k];
+    code[pos] = word;
+    if (store != 0) {
+        code[pos + 1] = store;
+        c.stores[k] = 1;
+    }
 }
 
 // Where the LOAD of chunk root g comes among its parent chunk's: by parent in
