@@ -270,7 +270,10 @@ int default_variant(int vtype, const CaseSet* cs, const Pop* p, int forced)
     }
     // prefer a table-dispatch interpreter when one fits: the kind that holds input rows in registers for
     // populations of several inputs (for one input its registers would only cost resident waves), else the one
-    // that dispatches directly (2e8 nodes at K = 8 5.59 against 5.80 ms through the branch table)
+    // that dispatches directly (2e8 nodes at K = 8 5.59 against 5.80 ms through the branch table).  The row form is
+    // also taken for more inputs than it has registers: on 300 trees direct dispatch is the better one only at
+    // K = 8 from 16 inputs (4096 cases: 2.34 against 2.52 ms at 16 inputs, 2.41 and 2.76 at 64), and the worse one
+    // at K = 1 (64 inputs 0.60 against 0.55 ms); autotuning finds which
     for (int kind : {vtype == GP_F32 && p->n_inputs > 1 ? 2 : 1, 1, 0})
         for (int v = 0; v < variant_count(); ++v)
             if (ok(v) && vt[v].K == wantK && vt[v].table && (vtype == GP_BOOL || vt[v].kind == kind)) return v;
@@ -1859,8 +1862,12 @@ public:
             } else if (a.cpu && a.row_bytes != a.src_row_bytes && stage()) {
                 a.at = -2;                     // packed in finish()
             } else {
-                HIPC(c_, hipMemcpy2DAsync(a.dst, a.row_bytes, a.src, a.src_row_bytes, a.row_bytes, a.rows,
-                                          a.to_host ? hipMemcpyDeviceToHost : hipMemcpyDeviceToDevice, c_->stream));
+                const hipMemcpyKind kind = a.to_host ? hipMemcpyDeviceToHost : hipMemcpyDeviceToDevice;
+                if (a.rows == 1)               // a dense array may be longer than the pitch that a 2D copy takes
+                    HIPC(c_, hipMemcpyAsync(a.dst, a.src, a.row_bytes, kind, c_->stream));
+                else
+                    HIPC(c_, hipMemcpy2DAsync(a.dst, a.row_bytes, a.src, a.src_row_bytes, a.row_bytes, a.rows, kind,
+                                              c_->stream));
             }
         }
         HIPC(c_, launch_pack(p, c_->stream));

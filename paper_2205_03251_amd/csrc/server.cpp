@@ -124,10 +124,10 @@ namespace {
 // so what a chunk costs the host and the memory (tables, a vector per chunk)
 // counts for more than the length of one job's chain of chunks.
 // 20000 jobs of 10 to 10^7 nodes: 2540 jobs a second at saturation and 135 GB at
-// the chunk sizes of a lone population (512 and 1024), 3069 and 76 GB at these.
-// A job must not hold more vectors than without side chunks, when 256 and 1024
-// were the sizes, or a budget that admitted it refuses it: random trees have 0.85
-// to 0.9 as many chunks at these sizes, 1.1 times as many at 1024 and 4096.
+// the chunk sizes of a lone population (512 and 1024), 3069 and 76 GB at 1024 and
+// 4096.  A job must not hold more vectors than without side chunks, when 256 and
+// 1024 were the sizes, or a budget that admitted it refuses it: random trees have
+// 0.85 to 0.9 as many chunks at these sizes, 1.1 times as many at 1024 and 4096.
 int64_t serve_chunk_nodes(int64_t n) { return n < 200000 ? 1280 : 5120; }
 
 uint64_t estimate_full(const TreeProg& pg, const CaseSet* cs)
