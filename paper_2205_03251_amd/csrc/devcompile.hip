@@ -767,7 +767,11 @@ int device_compile_population(Ctx* c, int vtype, int n_inputs, int64_t n_trees, 
     q.S = compile_stack_slots();
     q.C = C;
     q.no_side = !side_chunks_wanted();
-    if (out) out->side_chunks = side_chunks_wanted();
+    q.wide_side = wide_side_chunks(vtype, n_trees, offsets);
+    if (out) {
+        out->side_chunks = side_chunks_wanted();
+        out->wide_side = q.wide_side;
+    }
     if (packed) {
         // open and cnt are not in use yet: the listed nodes and their words
         uint32_t* n_walks = counter.as<uint32_t>();

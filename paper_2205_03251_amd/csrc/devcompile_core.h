@@ -59,6 +59,7 @@ struct DcNodes {
     int S;                             // stack slots
     int64_t C;                         // chunk size target (at least 2)
     bool no_side;                      // no side chunks (CompileOptions::side_chunks false)
+    bool wide_side;                    // CompileOptions::wide_side
 };
 
 struct DcChunks {
@@ -131,7 +132,7 @@ struct DcNode {
 // root: the function is its tree's root.
 GPE_HD inline DcNode dc_combine(const DcNodes& q, bool root, DcKid L, DcKid R)
 {
-    const int64_t G = q.no_side ? INT64_MAX : side_chunk_nodes(q.C);
+    const int64_t G = q.no_side ? INT64_MAX : side_chunk_nodes(q.C, q.wide_side);
     const bool wl = L.cut || L.waits, wr = R.cut || R.waits;
     DcNode o;
     o.cut_kids = 0;

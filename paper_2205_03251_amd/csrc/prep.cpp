@@ -228,7 +228,7 @@ bool compile_tree(const uint8_t* ops, int64_t n, const CompileOptions& opt, cons
     NodeRec* nd = ws.node.get();
     const bool index = opt.index_min_size > 0;
     out->big_ends.clear();
-    const int64_t G = opt.side_chunks ? side_chunk_nodes(C) : INT64_MAX;
+    const int64_t G = opt.side_chunks ? side_chunk_nodes(C, opt.wide_side) : INT64_MAX;
     auto words = [&](int64_t c) -> int32_t { return nd[c].cut ? 1 : nd[c].len; };   // LOAD or the code
     std::vector<int64_t> roots;                 // the cut nodes
 

@@ -64,8 +64,15 @@ constexpr int64_t kPathSiblingChunk = 64;
 // Every chunk owns a vector of device memory; without side chunks it is 1.7, 4.4
 // and 4.5 times as many nodes to a chunk at C = 128, 1024 and 4096, which is what
 // calls that run short of memory fall back to (CompileOptions::side_chunks).
-constexpr int64_t kSideChunkMin = 32;
-constexpr int64_t side_chunk_nodes(int64_t C) { return C / 32 > kSideChunkMin ? C / 32 : kSideChunkMin; }
+// wide: fewer and larger ones, C / 4 but at least 1024 nodes, for populations
+// whose work hides all but the longest chains (wide_side_chunks): there a
+// piece costs its hand-off and gains nothing.
+constexpr int64_t kSideChunkMin = 32, kWideSideChunkMin = 1024;
+constexpr int64_t side_chunk_nodes(int64_t C, bool wide = false)
+{
+    if (wide) return C / 4 > kWideSideChunkMin ? C / 4 : kWideSideChunkMin;
+    return C / 32 > kSideChunkMin ? C / 32 : kSideChunkMin;
+}
 
 inline uint32_t ins_word(uint32_t f, uint32_t mode, uint32_t d, uint32_t payload)
 {
@@ -125,6 +132,7 @@ struct CompileOptions {
     int64_t index_min_size = 0;  // > 0: list (node, end) of subtrees this large, sorted by node
     int threads = 1;             // threads for compiling a large tree (same program for any count)
     bool side_chunks = true;     // operands beside one that waits root chunks (see side_chunk_nodes)
+    bool wide_side = false;      // fewer, larger ones
 };
 
 // Sorts (chain length, chunk) pairs by descending length, equal ones in their

@@ -176,6 +176,7 @@ struct Pop {
     bool auto_chunk = false;                // chunk size may be re-tuned
     bool device_compiled = false;           // compiled on the device (re-chunked there too)
     bool side_chunks = true;                // compiled with side chunks (see side_chunk_nodes)
+    bool wide_side = false;                 // few and large ones (see wide_side_chunks)
     // host copy of the trees and record points, for re-chunking
     std::vector<uint8_t, NoInitAlloc<uint8_t>> host_ops;
     std::vector<int64_t> host_offsets, host_rec_points, host_rec_offsets;
@@ -410,7 +411,8 @@ Launch choose_launch(Ctx* c, int vtype, const CaseSet* cs, const Pop* p);
 int64_t resident_grid(const Ctx* c, const Variant& v, int waves_per_cu);
 // The interpreter for p on cs: the forced one if it fits, else the default.
 int default_variant(int vtype, const CaseSet* cs, const Pop* p, int forced);
-int64_t auto_chunk_nodes(int vtype, int64_t total_nodes, int64_t n_trees, int64_t T);
+int64_t auto_chunk_nodes(int vtype, int64_t n_trees, const int64_t* offsets);
+bool wide_side_chunks(int vtype, int64_t n_trees, const int64_t* offsets);
 int compile_stack_slots();
 
 }  // namespace gpe

@@ -213,11 +213,28 @@ Plan::~Plan()
 // chunk of its own.
 int compile_stack_slots() { return 10; }
 
-int64_t auto_chunk_nodes(int vtype, int64_t total_nodes, int64_t n_trees, int64_t T)
+// Side chunks wide apart (see side_chunk_nodes): for float populations of 10^9
+// nodes and more in which no tree holds more than a 64th of them.  Their work,
+// 50 ms and more at 1024 cases, hides the chains of chunks, and the closer side
+// chunks only cost their hand-offs.  500 trees of 10^6..10^7 nodes (2.1e9), at
+// 1024, 2048, 4096, 8192 nodes a chunk: 53.2, 52.9, 53.0, 53.3 ms wide apart and
+// 63.7, 57.3, 54.7, 53.8 ms close; 53.2, 53.0, 53.5, 55.0 ms without side
+// chunks; on 48 cases 15.9 (4096) and 15.8 ms (8192).  Below 10^9 nodes the
+// chains count: 300 trees, 6.3e7 nodes in 4096-node chunks, 3.3 and 1.9 ms; so
+// they do for 16 trees of 6.4e7 nodes (13.1 and 10.8 ms on 48 cases) and for
+// Boolean populations, which have few slices (64 cases of the 500 trees 24.1 and
+// 22.2 ms).
+bool wide_side_chunks(int vtype, int64_t n_trees, const int64_t* offsets)
 {
-    (void)vtype;
-    (void)n_trees;
-    (void)T;
+    const int64_t total = offsets[n_trees];
+    if (vtype != GP_F32 || total < 1000000000) return false;
+    for (int64_t t = 0; t < n_trees; ++t)
+        if (offsets[t + 1] - offsets[t] > total / 64) return false;
+    return true;
+}
+
+int64_t auto_chunk_nodes(int vtype, int64_t n_trees, const int64_t* offsets)
+{
     // Small chunks keep the chain of dependent chunks in the largest trees
     // short, larger ones cost fewer hand-offs: the more nodes there are, the
     // more the hand-offs count.  Measured (float, K = 4 or 8, with the side
@@ -225,11 +242,12 @@ int64_t auto_chunk_nodes(int vtype, int64_t total_nodes, int64_t n_trees, int64_
     // at 512, 1024, 2048; 4e6 nodes 0.74, 0.61, 0.69 ms; 4e7 nodes on 256
     // cases 1.08, 0.87, 0.87 ms; 6e7 nodes 1.95, 1.89, 1.82 ms at 1024, 2048,
     // 4096; 2e8 nodes 6.1, 5.9, 5.6, 5.5 ms at 1024 ... 8192.
+    const int64_t total_nodes = offsets[n_trees];
     if (total_nodes < 500000) return 512;
     if (total_nodes < 15000000) return 1024;
     if (total_nodes < 50000000) return 2048;
     if (total_nodes < 1000000000) return 4096;
-    return 8192;
+    return wide_side_chunks(vtype, n_trees, offsets) ? 4096 : 8192;
 }
 
 static int64_t elems_of(int vtype, int64_t T) { return vtype == GP_BOOL ? (T + 63) / 64 : T; }
@@ -331,7 +349,7 @@ int build_population(Ctx* c, int vtype, int layout, int n_inputs, int64_t n_tree
     }
     if (rec_points && !rec_offsets) return set_err(c, GP_EINVAL, "record_points needs record_offsets");
     if (rec_offsets && rec_offsets[0] != 0) return set_err(c, GP_EINVAL, "record_offsets[0] must be 0");
-    if (chunk_nodes <= 0) chunk_nodes = auto_chunk_nodes(vtype, total, n_trees, 0);
+    if (chunk_nodes <= 0) chunk_nodes = auto_chunk_nodes(vtype, n_trees, offsets);
     chunk_nodes = std::max<int64_t>(chunk_nodes, 16);
 
     CompileOptions opt;
@@ -341,6 +359,7 @@ int build_population(Ctx* c, int vtype, int layout, int n_inputs, int64_t n_tree
     opt.stack_slots = compile_stack_slots();
     opt.index_min_size = index_subtrees && layout == GP_PREFIX ? kBigSubtree : 0;
     opt.side_chunks = out->side_chunks = side_chunks_wanted();
+    opt.wide_side = out->wide_side = wide_side_chunks(vtype, n_trees, offsets);
 
     std::vector<TreeProg> progs(n_trees);
     std::vector<std::string> errs(n_trees);
@@ -433,7 +452,7 @@ int build_population_device(Ctx* c, int vtype, int n_inputs, int64_t n_trees, co
     if (rec_points && !rec_offsets) return set_err(c, GP_EINVAL, "record_points needs record_offsets");
     if (rec_offsets && rec_offsets[0] != 0) return set_err(c, GP_EINVAL, "record_offsets[0] must be 0");
     const int64_t total = offsets[n_trees];
-    if (chunk_nodes <= 0) chunk_nodes = auto_chunk_nodes(vtype, total, n_trees, 0);
+    if (chunk_nodes <= 0) chunk_nodes = auto_chunk_nodes(vtype, n_trees, offsets);
     chunk_nodes = std::max<int64_t>(chunk_nodes, 16);
     hipStream_t s = c->stream;
     // the index reads the trees with 16-byte loads: a copy of our own unless
@@ -2442,6 +2461,7 @@ static int evolve(gp_ctx* ctx, gp_handle pop, gp_handle cases, const gp_evolve_c
             opt.stack_slots = compile_stack_slots();
             opt.index_min_size = kBigSubtree;
             opt.side_chunks = np->side_chunks = cur->side_chunks && side_chunks_wanted();
+            opt.wide_side = np->wide_side = cur->wide_side;
             std::atomic<int64_t> next{0};
             auto work = [&]() {
                 for (int64_t k; (k = next++) < nb;) {
