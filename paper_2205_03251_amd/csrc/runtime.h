@@ -68,16 +68,18 @@ struct DevArena {
 // waits for the device) than in its kernels.  Calls with host time, before and
 // after: the index of 2.15e8 nodes 24.3 -> 2.2 ms, load, evaluation and release
 // of 4.3e7 nodes 34.2 -> 28.5 ms, two generations of 200 trees 14.5 -> 11.6 ms.
-// Used only by the
-// thread that holds Ctx::mu inside a PoolScope, whose work all goes to the
-// context stream: a block handed out again is overwritten after everything
-// that used it before.  Holds at most `limit` bytes in kBlocks blocks, the last
-// ones given; trimmed when the budget or the device runs short, when a server
-// starts and by gp_destroy, and to kIdle bytes when the context holds no
-// population and no case set any more (none kept: a loop that loads and releases
-// 2e5 trees of 3 to 31 nodes and nothing else takes 21.7 ms a turn instead of 14.8).
+// Used only by the thread that holds Ctx::mu inside a PoolScope, whose work all
+// goes to the context stream: a block handed out again is overwritten after
+// everything that used it before.  Holds at most `limit` bytes in kBlocks blocks,
+// the last ones given (tuning hands some hundreds back at its end: with 256 blocks
+// they were freed one by one, and the GPU, idle meanwhile, ran the next call in
+// 0.95 ms instead of 0.66, 1000 Boolean trees); trimmed when the budget or the
+// device runs short, when a server starts and by gp_destroy, and to kIdle bytes
+// when the context holds no population and no case set any more (none kept: a
+// loop that loads and releases 2e5 trees of 3 to 31 nodes and nothing else takes
+// 21.7 ms a turn instead of 14.8).
 struct DevPool {
-    static constexpr size_t kBlocks = 256;
+    static constexpr size_t kBlocks = 4096;
     static constexpr size_t kIdle = size_t(256) << 20;
     struct Block {
         void* p;
